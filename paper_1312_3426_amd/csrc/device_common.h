@@ -160,6 +160,11 @@ __device__ __forceinline__ double2 gld(const double2* p) {
     const v2 v = *(gptr<const v2>)p;
     return make_double2(v.x, v.y);
 }
+__device__ __forceinline__ uint2 gld(const uint2* p) {
+    typedef unsigned v2 __attribute__((ext_vector_type(2)));
+    const v2 v = *(gptr<const v2>)p;
+    return make_uint2(v.x, v.y);
+}
 template <typename T>
 __device__ __forceinline__ T gatomic_add(T* p, T v) {
     return __hip_atomic_fetch_add((gptr<T>)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -9,6 +9,7 @@
 #pragma once
 
 #include <limits.h>
+#include <type_traits>
 
 #include "device_common.h"
 #include "fixed_point.h"
@@ -138,6 +139,93 @@ __device__ __forceinline__ bool stencil_corner(double px, double py, double pz, 
     return true;
 }
 
+// Arithmetic of the element forces.  FP64 form: the library's square root and
+// division.  FP32 forms: the hardware's reciprocal and reciprocal square root,
+// refined once (errors below one unit in the last place), without the scaling
+// for denormal and overflowing operands that the correctly rounded sequences
+// carry (10 to 15 instructions each; lengths and areas here are of order one).
+__device__ __forceinline__ double div_r(double a, double b) { return a / b; }
+__device__ __forceinline__ float div_r(float a, float b) {
+    const float r = __builtin_amdgcn_rcpf(b);
+    const float q = a * r;
+    return fmadd(fmadd(-b, q, a), r, q);
+}
+__device__ __forceinline__ double rsqrt_r(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ float rsqrt_r(float x) {
+    const float r = __builtin_amdgcn_rsqf(x), h = 0.5f * x * r;
+    return fmadd(r, fmadd(-h, r, 0.5f), r);
+}
+// length L and 1 / L from L^2; L in FP64 in every form (its differences to the
+// relaxed length cancel): two refinements of the FP64 reciprocal square root
+__device__ __forceinline__ void length_of(double L2, double& L, double& rL) {
+    L = sqrt(L2);
+    rL = 1.0 / L;
+}
+__device__ __forceinline__ void length_of(double L2, double& L, float& rL) {
+    double r = __builtin_amdgcn_rsq(L2);
+    double h = 0.5 * L2;
+    r = fmadd(r, fmadd(-h * r, r, 0.5), r);
+    r = fmadd(r, fmadd(-h * r, r, 0.5), r);
+    L = L2 * r;
+    L = fmadd(fmadd(-L, L, L2), 0.5 * r, L);
+    rL = (float)r;
+}
+// angle of (x, y).  FP32 forms: near the relaxed shape the Taylor series of
+// atan (terms to t^7 leave 7e-9 of t at |t| = 1/8), the library's atan2 beyond
+__device__ __forceinline__ double angle_of(double y, double x) { return atan2(y, x); }
+__device__ __forceinline__ float angle_of(float y, float x) {
+    if (fabsf(y) <= 0.125f * x) {
+        const float t = div_r(y, x), t2 = t * t;
+        return fmadd(t * t2, fmadd(t2, fmadd(t2, -1.0f / 7.0f, 0.2f), -1.0f / 3.0f), t);
+    }
+    return atan2f(y, x);
+}
+
+// One corner of a node (TmplDev::ring16 / ring32): the flags of ea, eb, o sit
+// in bits 0, 1, 2 of fl.
+struct Corner {
+    int a, b, t, ea, eb, o;
+    unsigned fl;
+};
+struct RawCorner16 {
+    uint2 p;
+    unsigned q;
+    __device__ __forceinline__ bool valid() const { return p.x != 0xffffffffu; }
+    __device__ __forceinline__ Corner get() const {
+        return Corner{(int)(p.x & 0xffffu), (int)(p.x >> 16), (int)(p.y & 0xffffu), (int)((p.y >> 16) & 0x7fffu),
+                      (int)(q & 0x7fffu), (int)((q >> 16) & 0x7fffu),
+                      (p.y >> 31) | ((q >> 14) & 2u) | ((q >> 29) & 4u)};
+    }
+};
+struct RawCorner32 {
+    int4 p;
+    int2 q;
+    __device__ __forceinline__ bool valid() const { return p.x >= 0; }
+    __device__ __forceinline__ Corner get() const {
+        return Corner{p.x, p.y, p.z, p.w & 0x7fffffff, q.x & 0x7fffffff, q.y & 0x7fffffff,
+                      ((unsigned)p.w >> 31) | (((unsigned)q.x >> 30) & 2u) | (((unsigned)q.y >> 29) & 4u)};
+    }
+};
+template <class TP>
+__device__ __forceinline__ void load_corner(TP T, int j, int v, RawCorner16& c) {
+    const int k = j * T->rstride + v;
+    c.p = gld(T->ring16 + k);
+    c.q = gld(T->ring16b + k);
+}
+template <class TP>
+__device__ __forceinline__ void load_corner(TP T, int j, int v, RawCorner32& c) {
+    const int k = j * T->rstride + v;
+    c.p = gld(T->ring32 + k);
+    c.q = gld(T->ring32b + k);
+}
+// triangle (a, b, c, -) and hinge (A, B, C, D) of 16- or 32-bit lists
+template <bool WIDE>
+__device__ __forceinline__ int4 load_quad(const ushort4* q16, const int4* q32, int k) {
+    if (WIDE) return gld(q32 + k);
+    const uint2 q = gld((const uint2*)q16 + k);
+    return make_int4((int)(q.x & 0xffffu), (int)(q.x >> 16), (int)(q.y & 0xffffu), (int)(q.y >> 16));
+}
+
 // Stencil marking of one object for split stepping: every lattice node inside
 // the 2x2x2 stencil of a finite node position gets its bit in `touch`.  The
 // object's stencil box is marked in the bitmask `bits` ((ucap + 31)/32 words)
@@ -219,8 +307,8 @@ __device__ void mark_object(const double* pos, const int* order, int nv, const i
 // and update of patch `slice` of the nodes, run as an LDS-resident object on
 // the patch's sub-template (T->subs[slice]: the patch's nodes first, then the
 // other nodes its triangles and hinges reach, with the triangles and hinges
-// its nodes' gathers read and incidence lists in local numbering), after the
-// area and volume are summed from the slices in a fixed order.
+// its nodes' gathers read and corners in local numbering), after the area and
+// volume are summed from the slices in a fixed order.
 // LISTS: some box of the launch has the membrane kernel clear its coupling
 // force (BoxDev::g_by_mesh); without it the list code is left out.
 // The membrane forces, coupling and update of object O by the whole
@@ -228,6 +316,7 @@ __device__ void mark_object(const double* pos, const int* order, int nv, const i
 template <int P, bool USE_LDS, bool CONS, bool CPL, int PH = PH_ALL, bool LISTS = true>
 __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O, unsigned char* smem, int parity,
                                             int mark_next, int slice = 0) {
+#pragma clang fp contract(off)
     constexpr bool SPLIT = PH != PH_ALL;
     static_assert(PH != PH_SUMS || (!USE_LDS && CPL), "sums launch: positions alone in LDS");
     static_assert(PH != PH_PATCH || (USE_LDS && !CPL), "patch launch: the patch's sub-template in LDS");
@@ -316,41 +405,40 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     // 1. triangles
     // (S - S0 is formed as (S^2 - S0^2)/(S + S0): the cancelling difference in
     // FP64 multiply-adds, the square root and division in the arithmetic type)
+    constexpr bool WIDE = !USE_LDS && PH == PH_ALL;  // mesh in the global scratch: 32-bit lists
+    const R kal = (R)T->kal;
     double sdarea = 0.0, svol = 0.0;
     {
-        // node 0 of the object: the apex of the signed tetrahedra, and the
-        // origin the triangles' edge vectors are taken from in every launch
+        // node 0 of the object: the apex of the signed tetrahedra in every launch
         const double r0x = PH == PH_PATCH ? stage(0) : xs[0], r0y = PH == PH_PATCH ? stage(1) : xs[1],
                      r0z = PH == PH_PATCH ? stage(2) : xs[2];
         const int t0 = PH == PH_SUMS ? (int)((long long)nt * slice / nsl) : 0;
         const int t1 = PH == PH_SUMS ? (int)((long long)nt * (slice + 1) / nsl) : nt;
         for (int t = t0 + (int)threadIdx.x; t < t1; t += blockDim.x) {
-            const int a = gld(T->tri + 3 * t), b = gld(T->tri + 3 * t + 1), c = gld(T->tri + 3 * t + 2);
-            const double ax = xs[3 * a] - r0x, ay = xs[3 * a + 1] - r0y, az = xs[3 * a + 2] - r0z;
-            const double bx = xs[3 * b] - r0x, by = xs[3 * b + 1] - r0y, bz = xs[3 * b + 2] - r0z;
-            const double qx = xs[3 * c] - r0x, qy = xs[3 * c + 1] - r0y, qz = xs[3 * c + 2] - r0z;
-            const double abx = bx - ax, aby = by - ay, abz = bz - az;
-            const double acx = qx - ax, acy = qy - ay, acz = qz - az;
-            const double nx_ = aby * acz - abz * acy;
-            const double ny_ = abz * acx - abx * acz;
-            const double nz_ = abx * acy - aby * acx;
-            const double n2 = nx_ * nx_ + ny_ * ny_ + nz_ * nz_;  // 4 S^2
-            const R len = sqrt((R)n2);
-            const R S = R(0.5) * len;
+            const int4 q = load_quad<WIDE>(T->tri16, T->tri32, t);
             const double S0 = gld(T->S0 + t);
-            const R dS = (R)(0.25 * n2 - S0 * S0) / (S + (R)S0);
+            const double ax = xs[3 * q.x], ay = xs[3 * q.x + 1], az = xs[3 * q.x + 2];
+            const double abx = xs[3 * q.y] - ax, aby = xs[3 * q.y + 1] - ay, abz = xs[3 * q.y + 2] - az;
+            const double acx = xs[3 * q.z] - ax, acy = xs[3 * q.z + 1] - ay, acz = xs[3 * q.z + 2] - az;
+            const double nx_ = fmadd(aby, acz, -(abz * acy));
+            const double ny_ = fmadd(abz, acx, -(abx * acz));
+            const double nz_ = fmadd(abx, acy, -(aby * acx));
+            const double n2 = fmadd(nx_, nx_, fmadd(ny_, ny_, nz_ * nz_));  // 4 S^2
+            const R rl = rsqrt_r((R)n2);
+            const R S = R(0.5) * (R)n2 * rl;
+            const R dS = div_r((R)fmadd(0.25, n2, -(S0 * S0)), S + (R)S0);
             if (PH != PH_SUMS) {  // the sums launch keeps the sums only
-                tn[4 * t + 0] = (R)nx_ / len;
-                tn[4 * t + 1] = (R)ny_ / len;
-                tn[4 * t + 2] = (R)nz_ / len;
+                tn[4 * t + 0] = (R)nx_ * rl;
+                tn[4 * t + 1] = (R)ny_ * rl;
+                tn[4 * t + 2] = (R)nz_ * rl;
                 tn[4 * t + 3] = S;
-                tr[t] = dS / S;
+                tr[t] = -kal * (R(2) * dS * rl);
             }
             sdarea += (double)dS;
-            // signed tetrahedron (node 0, a, b, c): inward orientation gives -6 V
-            const double cxx = by * qz - bz * qy, cyy = bz * qx - bx * qz, czz = bx * qy - by * qx;
-            svol -= (ax * cxx + ay * cyy + az * czz) / 6.0;
+            // signed tetrahedron (node 0, a, b, c): a . N = -6 V for inward N
+            svol = fmadd(ax - r0x, nx_, fmadd(ay - r0y, ny_, fmadd(az - r0z, nz_, svol)));
         }
+        svol *= -1.0 / 6.0;
     }
     double dSg, Vol;  // Sg - Sg0, volume
     if (PH == PH_ALL) {
@@ -382,71 +470,73 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
 
     // 2. edges: stretching coefficient and bending magnitude of each hinge
     const bool do_s = T->ks != 0.0, do_b = T->kb != 0.0;
-    if (do_s || do_b) {
-        for (int e = threadIdx.x; e < ne; e += blockDim.x) {
-            const int4 h = gld(T->hinge + e);  // (A, B, C, D): the edge is B -> C
-            const double dx = xs[3 * h.z] - xs[3 * h.y], dy = xs[3 * h.z + 1] - xs[3 * h.y + 1],
-                         dz = xs[3 * h.z + 2] - xs[3 * h.y + 2];
-            const double L2 = dx * dx + dy * dy + dz * dz;
-            const double L = sqrt(L2);
-            if (do_s) {
-                // strain (L - L0)/L0 = (L^2 - L0^2) / (L0 (L + L0))
-                const double L0 = gld(T->L0 + e);
-                const R strain = (R)(L2 - L0 * L0) / ((R)L0 * (R)(L + L0));
-                R kap = R(1);
-                if (!T->linear) {
-                    const R lam = R(1) + strain, sl = sqrt(lam), l2 = lam * lam;
-                    kap = (sl + R(1) / (l2 * sl)) / (lam + R(1) / (l2 * lam));
-                }
-                se[e] = (R)T->ks * kap * strain / (R)L;
+    for (int e = threadIdx.x; e < ne; e += blockDim.x) {
+        const int4 h = load_quad<WIDE>(T->hinge16, T->hinge32, e);  // (A, B, C, D): the edge is B -> C
+        const double L0 = gld(T->L0 + e);
+        const double bx = xs[3 * h.y], by = xs[3 * h.y + 1], bz = xs[3 * h.y + 2];
+        const double cx_ = xs[3 * h.z], cy_ = xs[3 * h.z + 1], cz_ = xs[3 * h.z + 2];
+        const double dx = cx_ - bx, dy = cy_ - by, dz = cz_ - bz;
+        const double L2 = fmadd(dx, dx, fmadd(dy, dy, dz * dz));
+        double L;
+        R rL;
+        length_of(L2, L, rL);
+        R s = R(0);
+        if (do_s) {
+            // strain (L - L0)/L0 = (L^2 - L0^2) / (L0 (L + L0)); neo-Hookean
+            // kappa = (lam^1/2 + lam^-5/2) / (lam + lam^-3)
+            //       = lam^1/2 (1 + lam^3) / (1 + lam^4)
+            const R strain = div_r((R)fmadd(-L0, L0, L2), (R)(L0 * (L + L0)));
+            R kap = R(1);
+            if (!T->linear) {
+                const R lam = R(1) + strain, l3 = lam * lam * lam;
+                kap = div_r(sqrt(lam) * (R(1) + l3), fmadd(l3, lam, R(1)));
             }
-            if (do_b) {
-                // normals of T1 = (A, B, C) and T2 = (D, C, B) (inward, unnormalised)
-                const double* pa = &xs[3 * h.x];
-                const double* pb = &xs[3 * h.y];
-                const double* pc = &xs[3 * h.z];
-                const double* pd = &xs[3 * h.w];
-                const double u1x = pb[0] - pa[0], u1y = pb[1] - pa[1], u1z = pb[2] - pa[2];
-                const double v1x = pc[0] - pa[0], v1y = pc[1] - pa[1], v1z = pc[2] - pa[2];
-                const double n1x = u1y * v1z - u1z * v1y, n1y = u1z * v1x - u1x * v1z, n1z = u1x * v1y - u1y * v1x;
-                const double u2x = pc[0] - pd[0], u2y = pc[1] - pd[1], u2z = pc[2] - pd[2];
-                const double v2x = pb[0] - pd[0], v2y = pb[1] - pd[1], v2z = pb[2] - pd[2];
-                const double n2x = u2y * v2z - u2z * v2y, n2y = u2z * v2x - u2x * v2z, n2z = u2x * v2y - u2y * v2x;
-                const double mx = n1y * n2z - n1z * n2y, my = n1z * n2x - n1x * n2z, mz = n1x * n2y - n1y * n2x;
-                // theta - pi = atan2((m . e), n1 . n2) for the unit vectors; the
-                // difference to theta0 - pi is the angle of the relative rotation,
-                // atan2(sin d, cos d), every term scaled by |N1| |N2| L > 0
-                const double md = mx * dx + my * dy + mz * dz;
-                const double dot = n1x * n2x + n1y * n2y + n1z * n2z;
-                const double2 cs = gld(T->cs0 + e);  // cos, sin of theta0 - pi
-                const R dth = atan2((R)(md * cs.x - dot * L * cs.y), (R)(dot * L * cs.x + md * cs.y));
-                const R f = (R)T->kb * dth / (R)gld(T->theta0 + e);
-                if (!cons) {
-                    fh[e] = f;
-                } else {
-                    // gradient form: the wing factors c / h (c = hbar f, h = |N| / L
-                    // the wing's distance from the edge line) and the positions a of
-                    // the wings' feet on the edge, B + a (C - B)
-                    const R c = (R)gld(T->hbar + e) * f;
-                    const R nA = (R)sqrt(n1x * n1x + n1y * n1y + n1z * n1z);
-                    const R nD = (R)sqrt(n2x * n2x + n2y * n2y + n2z * n2z);
-                    const double abx = pa[0] - pb[0], aby = pa[1] - pb[1], abz = pa[2] - pb[2];
-                    const double dbx = pd[0] - pb[0], dby = pd[1] - pb[1], dbz = pd[2] - pb[2];
-                    R* q = fh + 4 * e;
-                    q[0] = c * (R)L / nA;
-                    q[1] = c * (R)L / nD;
-                    q[2] = (R)((abx * dx + aby * dy + abz * dz) / L2);
-                    q[3] = (R)((dbx * dx + dby * dy + dbz * dz) / L2);
-                }
-            }
+            s = (R)T->ks * kap * strain * rL;
+        }
+        se[e] = s;
+        R* q = fh + (cons ? 4 : 1) * e;
+        if (!do_b) {
+            for (int k = 0; k < (cons ? 4 : 1); ++k) q[k] = R(0);
+            continue;
+        }
+        // normals of T1 = (A, B, C) and T2 = (D, C, B) (inward, unnormalised):
+        // N1 = (B - A) x (C - B), N2 = (C - B) x (C - D)
+        const double ux = bx - xs[3 * h.x], uy = by - xs[3 * h.x + 1], uz = bz - xs[3 * h.x + 2];
+        const double wx_ = cx_ - xs[3 * h.w], wy_ = cy_ - xs[3 * h.w + 1], wz_ = cz_ - xs[3 * h.w + 2];
+        const double n1x = fmadd(uy, dz, -(uz * dy)), n1y = fmadd(uz, dx, -(ux * dz)), n1z = fmadd(ux, dy, -(uy * dx));
+        const double n2x = fmadd(dy, wz_, -(dz * wy_)), n2y = fmadd(dz, wx_, -(dx * wz_)),
+                     n2z = fmadd(dx, wy_, -(dy * wx_));
+        // theta - pi = atan2((n1 x n2) . e, n1 . n2) for the unit vectors, where
+        // N1 x N2 = (C - B) ((B - A) . N2); the difference to theta0 - pi is the
+        // angle of the relative rotation, atan2(sin d, cos d), every term scaled
+        // by |N1| |N2| > 0
+        const double sn = L * fmadd(ux, n2x, fmadd(uy, n2y, uz * n2z));
+        const double cn = fmadd(n1x, n2x, fmadd(n1y, n2y, n1z * n2z));
+        const double2 cs = gld(T->cs0 + e);  // cos, sin of theta0 - pi
+        const R dth = angle_of((R)fmadd(sn, cs.x, -(cn * cs.y)), (R)fmadd(cn, cs.x, sn * cs.y));
+        const R f = (R)gld(T->kth + e) * dth;
+        if (!cons) {
+            q[0] = f;
+        } else {
+            // gradient form: the wing factors w = c / h (c = hbar f, h = |N| / L
+            // the wing's distance from the edge line) and w times the position a
+            // of the wing's foot on the edge, B + a (C - B)
+            const R c = (R)gld(T->hbar + e) * f * (R)L;
+            const R wA = c * rsqrt_r((R)fmadd(n1x, n1x, fmadd(n1y, n1y, n1z * n1z)));
+            const R wD = c * rsqrt_r((R)fmadd(n2x, n2x, fmadd(n2y, n2y, n2z * n2z)));
+            const R aA = (R)(-fmadd(ux, dx, fmadd(uy, dy, uz * dz)) / L2);
+            const R aD = (R)((L2 - fmadd(wx_, dx, fmadd(wy_, dy, wz_ * dz))) / L2);
+            q[0] = wA;
+            q[1] = wD;
+            q[2] = aA * wA;
+            q[3] = aD * wD;
         }
     }
     __syncthreads();
 
     const R cg = (R)(-T->kag * dSg / Sg);             // global area coefficient
     const R cv = (R)(-T->kv * (Vol - T->V0) / T->V0); // volume coefficient
-    const R kal = (R)T->kal;
-    const R third = R(1) / R(3);
+    const R cv3 = cv * (R(1) / R(3));
     const int nxb = B->nx, nyb = B->ny, nzb = B->nz;
     const S* __restrict__ pop = (const S*)B->f[parity];
     const float inv = B->st_inv;
@@ -457,71 +547,73 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     int blo[3] = {INT_MAX, INT_MAX, INT_MAX}, bhi[3] = {INT_MIN, INT_MIN, INT_MIN};
 
     // 3. nodes (in the patch launch the patch's nodes are the sub-template's
-    // first nn nodes, so xs, the incidence lists and fs take the same index)
+    // first nn nodes, so xs, the corners and fs take the same index).  The
+    // node's force from its corners (v, a, b) alone: each hands it the
+    // stretching of its edge (v, a), and, as every bending force runs along a
+    // triangle's normal, the triangle's normal times the sum of the magnitudes
+    // that act on v through it: its own wing (edge (a, b)), the shares of the
+    // hinges on (v, a) and (b, v), and the volume force.  (Gathering edges,
+    // hinges and triangles by three lists read 24 entries of 8 to 16 bytes and
+    // some 150 LDS words per node where the corners take 6 entries of 12 bytes,
+    // a wave's entries contiguous, and some 75 words.  With the shorter
+    // arithmetic of div_r and its kin: launch of 500 spheres of 642 nodes, FP32,
+    // 79.2 -> 72.4 us; FP64, 120 conservative ones 64.2 -> 55.8 us.)
+    typedef typename std::conditional<WIDE, RawCorner32, RawCorner16>::type Raw;
     for (int i = threadIdx.x; i < nn; i += blockDim.x) {
-        const int v = i;
-        const double px = xs[3 * v], py = xs[3 * v + 1], pz = xs[3 * v + 2];
+        const double px = xs[3 * i], py = xs[3 * i + 1], pz = xs[3 * i + 2];
         R Fx = 0, Fy = 0, Fz = 0;
-        const int4 o0 = gld(T->n_off + v), o1 = gld(T->n_off + v + 1);
-        if (do_s) {
-            // F_v += ks kappa (L - L0)/L0 (x_u - x_v)/L  ("Stretching force")
-#pragma unroll 2
-            for (int k = o0.x; k < o1.x; ++k) {
-                const int2 ie = gld(T->e_inc + k);
-                const R s = se[ie.y];
-                Fx += s * (R)(xs[3 * ie.x] - px);
-                Fy += s * (R)(xs[3 * ie.x + 1] - py);
-                Fz += s * (R)(xs[3 * ie.x + 2] - pz);
+        auto corner = [&](const Raw& raw) {
+#pragma clang fp contract(off)
+            if (!raw.valid()) return;
+            const Corner c = raw.get();
+            const double ax = px - xs[3 * c.a], ay = py - xs[3 * c.a + 1], az = pz - xs[3 * c.a + 2];
+            const double bx = px - xs[3 * c.b], by = py - xs[3 * c.b + 1], bz = pz - xs[3 * c.b + 2];
+            const R s = se[c.ea];
+            const R n0 = tn[4 * c.t], n1 = tn[4 * c.t + 1], n2 = tn[4 * c.t + 2], S = tn[4 * c.t + 3];
+            // bending: wings along their triangle's normal, edge ends minus
+            // half the sum ("Bending force"; conservative model: minus the wing
+            // forces split by the positions of the wings' feet)
+            R cn;
+            if (!cons) {
+                cn = fh[c.o] - R(0.5) * (fh[c.ea] + fh[c.eb]);
+            } else {
+                const R* qa = fh + 4 * c.ea;  // v is the edge's B where the triangle is its T1, else C
+                const R* qb = fh + 4 * c.eb;  // v is the edge's C where the triangle is its T1, else B
+                cn = fh[4 * c.o + ((c.fl & 4u) ? 1 : 0)];
+                cn -= (c.fl & 1u) ? qa[3] : qa[0] - qa[2];
+                cn -= (c.fl & 2u) ? qb[1] - qb[3] : qb[2];
             }
-        }
-        if (do_b) {
-            // wings along their triangle's normal, edge ends minus half the sum
-            // ("Bending force"; conservative model: minus the wing forces split
-            // by the positions of the wings' feet); the role picks the two
-            // coefficients of the normals n1, n2
-#pragma unroll 4
-            for (int k = o0.y; k < o1.y; ++k) {
-                const int4 r = gld(T->h_inc + k);
-                const int role = r.x & 3;
-                R a1, a2;
-                if (!cons) {
-                    const R f = fh[r.x >> 2];
-                    const R hf = R(-0.5) * f;
-                    a1 = role == 0 ? f : (role == 3 ? R(0) : hf);
-                    a2 = role == 3 ? f : (role == 0 ? R(0) : hf);
-                } else {
-                    const R* q = fh + 4 * (r.x >> 2);
-                    const R wA = q[0], wD = q[1], aA = q[2], aD = q[3];
-                    a1 = role == 0 ? wA : (role == 3 ? R(0) : -(role == 1 ? R(1) - aA : aA) * wA);
-                    a2 = role == 3 ? wD : (role == 0 ? R(0) : -(role == 1 ? R(1) - aD : aD) * wD);
-                }
-                Fx += a1 * tn[4 * r.y] + a2 * tn[4 * r.z];
-                Fy += a1 * tn[4 * r.y + 1] + a2 * tn[4 * r.z + 1];
-                Fz += a1 * tn[4 * r.y + 2] + a2 * tn[4 * r.z + 2];
-            }
-        }
-        // local area (-kal dS/S w), global area (-kag dSg/Sg w), volume
-        // (-kv dV/V0 S n_out / 3); w = centroid -> vertex over its length, or
-        // (conservative model) over the RMS length of the triangle's three
-#pragma unroll 2
-        for (int k = o0.z; k < o1.z; ++k) {
-            const int4 r = gld(T->t_inc + k);
-            const int t = r.x;
-            const double gx = (px + xs[3 * r.y] + xs[3 * r.z]) * (1.0 / 3.0);
-            const double gy = (py + xs[3 * r.y + 1] + xs[3 * r.z + 1]) * (1.0 / 3.0);
-            const double gz = (pz + xs[3 * r.y + 2] + xs[3 * r.z + 2]) * (1.0 / 3.0);
-            const R wx = (R)(px - gx), wy = (R)(py - gy), wz = (R)(pz - gz);
-            R n2 = wx * wx + wy * wy + wz * wz;
+            // volume: -kv dV/V0 S n_out / 3
+            cn = fmadd(-cv3, S, cn);
+            // local area (-kal dS/S w), global area (-kag dSg/Sg w); w = centroid
+            // -> vertex over its length (three times it: (v - a) + (v - b)), or
+            // (conservative model) over the RMS length of the triangle's three
+            const R wx = (R)(ax + bx), wy = (R)(ay + by), wz = (R)(az + bz);
+            R w2 = fmadd(wx, wx, fmadd(wy, wy, wz * wz));
             if (cons) {
-                const R bx = (R)(xs[3 * r.y] - gx), by = (R)(xs[3 * r.y + 1] - gy), bz = (R)(xs[3 * r.y + 2] - gz);
-                const R qx = (R)(xs[3 * r.z] - gx), qy = (R)(xs[3 * r.z + 1] - gy), qz = (R)(xs[3 * r.z + 2] - gz);
-                n2 = (n2 + bx * bx + by * by + bz * bz + qx * qx + qy * qy + qz * qz) * third;
+                const R cx_ = (R)(bx - ax - ax), cy_ = (R)(by - ay - ay), cz_ = (R)(bz - az - az);
+                const R dx = (R)(ax - bx - bx), dy = (R)(ay - by - by), dz = (R)(az - bz - bz);
+                w2 += fmadd(cx_, cx_, fmadd(cy_, cy_, cz_ * cz_)) + fmadd(dx, dx, fmadd(dy, dy, dz * dz));
+                w2 *= R(1) / R(3);
             }
-            const R ct = (-kal * tr[t] + cg) / sqrt(n2);
-            const R vf = cv * tn[4 * t + 3] * third;
-            Fx += ct * wx - vf * tn[4 * t];
-            Fy += ct * wy - vf * tn[4 * t + 1];
-            Fz += ct * wz - vf * tn[4 * t + 2];
+            const R ct = (tr[c.t] + cg) * rsqrt_r(w2);
+            // F_v += ks kappa (L - L0)/L0 (x_a - x_v)/L  ("Stretching force")
+            Fx = fmadd(ct, wx, fmadd(cn, n0, fmadd(-s, (R)ax, Fx)));
+            Fy = fmadd(ct, wy, fmadd(cn, n1, fmadd(-s, (R)ay, Fy)));
+            Fz = fmadd(ct, wz, fmadd(cn, n2, fmadd(-s, (R)az, Fz)));
+        };
+        // the first six corners' entries are all in flight before the first is
+        // used (most nodes have five to seven)
+        Raw raw[6];
+        const int n6 = min(6, T->rmax);
+#pragma unroll
+        for (int j = 0; j < 6; ++j) load_corner(T, min(j, n6 - 1), i, raw[j]);
+#pragma unroll
+        for (int j = 0; j < 6; ++j)
+            if (j < n6) corner(raw[j]);
+        for (int j = 6; j < T->rmax; ++j) {
+            load_corner(T, j, i, raw[0]);
+            corner(raw[0]);
         }
 
         fs[3 * i] = Fx;

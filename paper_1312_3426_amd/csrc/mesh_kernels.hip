@@ -10,8 +10,8 @@
 //   2. per edge: the stretching coefficient from the strain (L - L0)/L0 and
 //      the bending magnitude from theta - theta0, both formed in FP64 so the
 //      cancellation near the relaxed shape keeps its digits;
-//   3. per node: gather of its edge, hinge and triangle contributions in a
-//      fixed order (deterministic, no atomics), trilinear interpolation of the
+//   3. per node: gather of its corners' contributions in a fixed order
+//      (deterministic, no atomics), trilinear interpolation of the
 //      fluid velocity from the 8 surrounding nodes, drag, symplectic Euler
 //      update, and spreading of the reaction to the 8 nodes (int64 fixed-point
 //      atomics: one word per component in the FP32 forms, a 2^-30 / 2^-80

@@ -85,17 +85,25 @@ template <typename real>
 struct TmplDev {
     int nv, nt, ne;
     int linear;
-    const int* tri;        // [nt][3]
-    // Per-node incidence lists (CSR).  Each entry holds everything the node's
-    // gather needs besides LDS data, so the entries of a node are independent
-    // loads with no second indirection.
-    const int4* n_off;     // [nv + 1] (edge, hinge, triangle) list offsets
-    const int2* e_inc;     // (neighbour node, edge id)
-    const int4* h_inc;     // (hinge id << 2 | role, T1, T2, 0); role 0 = A, 1 = B, 2 = C, 3 = D
-    const int4* t_inc;     // (triangle, next vertex, vertex after that, 0) in the triangle's order
+    // Index lists, in 16 bits where the mesh runs in LDS (node, triangle and
+    // edge numbers fit then; null when they do not) and in 32 bits for meshes
+    // in the global scratch.
+    const ushort4* tri16;     // [nt] (a, b, c, 0), inward
+    const int4* tri32;
+    const ushort4* hinge16;   // [ne] (A, B, C, D): T1 = (A, B, C) runs B -> C, T2 has wing D
+    const int4* hinge32;
+    // Corners of each node: corner j of node v is entry j * rstride + v (so a
+    // wave reads 64 consecutive entries), j < rmax; a node with fewer corners
+    // has entries of all ones after them.  A corner is a triangle (v, a, b) in
+    // its order: a, b, the triangle t, and its edges ea = (v, a), eb = (b, v),
+    // o = (a, b), each with its top bit set where the triangle is the edge's T2.
+    const uint2* ring16;      // a | b << 16, t | ea << 16
+    const unsigned* ring16b;  // eb | o << 16
+    const int4* ring32;       // a, b, t, ea
+    const int2* ring32b;      // eb, o
+    int rstride, rmax;
     const double* L0;      // [ne] (FP64: L - L0 cancels near the relaxed shape)
-    const int4* hinge;     // (A, B, C, D): T1 = (A, B, C) runs B -> C, T2 has wing D
-    const double* theta0;  // [ne] relaxed inner dihedral angle
+    const double* kth;     // [ne] kb / theta0, theta0 the relaxed inner dihedral angle
     const double2* cs0;    // [ne] cos and sin of theta0 - pi (FP64)
     const double* S0;      // [nt] (FP64: S - S0 cancels near the relaxed shape)
     const double* hbar;    // [ne] mean relaxed wing height (conservative model)
@@ -109,8 +117,8 @@ struct TmplDev {
     // compact patch of the reference shape, of at most smax nodes, through its
     // sub-template subs[k]: the patch's nodes (numbered 0 .. slice_off[1] - 1
     // there) and the other nodes its triangles and hinges reach, those
-    // triangles and hinges, and the incidence lists of the patch's nodes, all
-    // in local numbering; its order maps local node numbers to the object's.
+    // triangles and hinges, and the corners of the patch's nodes, all in local
+    // numbering; its order maps local node numbers to the object's.
     // A sub-template keeps the template's nslice, smax, capacities and moduli.
     int nslice, smax;
     const int* order;      // [nv]

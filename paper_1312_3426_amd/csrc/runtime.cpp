@@ -91,9 +91,8 @@ struct Template {
     // nodes, triangles and hinges of each patch's sub-template (set when the
     // template is uploaded)
     std::vector<int> pnv, pnt, pne;
-    std::vector<int> e_off, h_off, t_off;
-    std::vector<std::array<int, 2>> e_inc;
-    std::vector<int> h_inc, t_inc;
+    std::vector<int> side;              // [nt][3] edge of side (v_s, v_s+1), complemented where the triangle is its T2
+    std::vector<std::vector<int>> corner;  // per node: (triangle << 2) | position, ascending
 };
 
 inline int tmpl_conservative(const Template& T) { return T.k.force_model == OIF_FORCES_CONSERVATIVE ? 1 : 0; }
@@ -311,25 +310,17 @@ int build_template(const double* nodes, int nv, const int32_t* tris, int nt, con
         T.smax = 0;
         for (int sl = 0; sl < K; ++sl) T.smax = std::max(T.smax, T.slice_off[sl + 1] - T.slice_off[sl]);
     }
-    // per-node incidence lists (CSR)
-    std::vector<std::vector<std::array<int, 2>>> ei(nv);
-    std::vector<std::vector<int>> hi(nv), ti(nv);
-    for (int e = 0; e < T.ne; ++e) {
-        ei[T.edge[e][0]].push_back({T.edge[e][1], e});
-        ei[T.edge[e][1]].push_back({T.edge[e][0], e});
-        for (int r = 0; r < 4; ++r) hi[T.hinge[e][r]].push_back((e << 2) | r);
-    }
+    // each triangle's edges and each node's corners
+    T.side.resize(3 * (size_t)nt);
+    for (int e = 0; e < T.ne; ++e)
+        for (int w = 0; w < 2; ++w) {
+            const int t = T.hinge_tri[e][w], from = T.edge[e][w];  // T1 runs B -> C, T2 C -> B
+            for (int s3 = 0; s3 < 3; ++s3)
+                if (T.tri[3 * t + s3] == from) T.side[3 * t + s3] = w ? ~e : e;
+        }
+    T.corner.resize(nv);
     for (int t = 0; t < nt; ++t)
-        for (int s3 = 0; s3 < 3; ++s3) ti[T.tri[3 * t + s3]].push_back((t << 2) | s3);
-    T.e_off.assign(1, 0); T.h_off.assign(1, 0); T.t_off.assign(1, 0);
-    for (int v = 0; v < nv; ++v) {
-        for (auto& p : ei[v]) T.e_inc.push_back(p);
-        for (int c : hi[v]) T.h_inc.push_back(c);
-        for (int c : ti[v]) T.t_inc.push_back(c);
-        T.e_off.push_back((int)T.e_inc.size());
-        T.h_off.push_back((int)T.h_inc.size());
-        T.t_off.push_back((int)T.t_inc.size());
-    }
+        for (int s3 = 0; s3 < 3; ++s3) T.corner[T.tri[3 * t + s3]].push_back((t << 2) | s3);
     return OIF_OK;
 }
 
@@ -640,140 +631,149 @@ int setup_repulsion(oif_ctx* c, size_t real_bytes) {
 }
 
 // Device-format arrays of a template, or of one patch's sub-template (split
-// membrane launches); hinge and incidence entries hold everything the gather
-// needs, so a node's entries are independent loads.
+// membrane launches).
 struct TArr {
     int nv = 0, nt = 0, ne = 0;
-    std::vector<int> tri;           // [nt][3]
-    std::vector<int4> noff;         // [nv + 1] (edge, hinge, triangle) list offsets
-    std::vector<int2> einc;         // (neighbour, edge)
-    std::vector<int4> hinc;         // (hinge << 2 | role, T1, T2, 0)
-    std::vector<int4> tinc;         // (triangle, next vertex, vertex after that, 0)
-    std::vector<double> L0;         // [ne]
+    std::vector<int4> tri;          // [nt] (a, b, c, 0)
     std::vector<int4> hv;           // [ne] (A, B, C, D)
-    std::vector<double> th, cs0;    // [ne], [ne][2]: theta0; cos, sin of theta0 - pi
+    std::vector<double> L0;         // [ne]
+    std::vector<double> kth, cs0;   // [ne], [ne][2]: kb / theta0; cos, sin of theta0 - pi
     std::vector<double> S0;         // [nt]
     std::vector<double> hbar;       // [ne]
+    // corners (TmplDev::ring32): [rmax][rstride]
+    int rstride = 0, rmax = 0;
+    std::vector<int4> ring;
+    std::vector<int2> ringb;
     std::vector<int> order, slice_off;
+    // the same lists in 16 bits (empty when some number does not fit)
+    std::vector<ushort4> tri16, hv16;
+    std::vector<uint2> ring16;
+    std::vector<unsigned> ring16b;
 };
+
+// Corner of triangle t at position s3 in device form; nl, tl, el map node,
+// triangle and edge numbers (null: as they are).
+void corner_entry(const Template& T, int code, const int* nl, const int* tl, const int* el, int4& p, int2& q) {
+    const int t = code >> 2, s3 = code & 3;
+    auto node = [&](int k) {
+        const int v = T.tri[3 * t + (s3 + k) % 3];
+        return nl ? nl[v] : v;
+    };
+    auto edge = [&](int k) {
+        const int s = T.side[3 * t + (s3 + k) % 3], e = s < 0 ? ~s : s;
+        return (int)((unsigned)(el ? el[e] : e) | (s < 0 ? 0x80000000u : 0u));
+    };
+    p = make_int4(node(1), node(2), tl ? tl[t] : t, edge(0));
+    q = make_int2(edge(2), edge(1));
+}
+
+// The 16-bit lists from the 32-bit ones.
+void narrow(TArr& A) {
+    auto h4 = [](const int4& v) { return make_ushort4((unsigned short)v.x, (unsigned short)v.y, (unsigned short)v.z, (unsigned short)v.w); };
+    if (A.nv > 0xffff) return;
+    for (const int4& v : A.tri) A.tri16.push_back(h4(v));
+    if (A.nt > 0xffff || A.ne > 0x7fff) return;
+    for (const int4& v : A.hv) A.hv16.push_back(h4(v));
+    auto e16 = [](int e) { return ((unsigned)e & 0x7fffu) | (e < 0 ? 0x8000u : 0u); };
+    for (size_t k = 0; k < A.ring.size(); ++k) {
+        const int4 p = A.ring[k];
+        const int2 q = A.ringb[k];
+        const bool none = p.x < 0;
+        A.ring16.push_back(none ? make_uint2(~0u, ~0u)
+                                : make_uint2((unsigned)p.x | (unsigned)p.y << 16, (unsigned)p.z | e16(p.w) << 16));
+        A.ring16b.push_back(none ? ~0u : e16(q.x) | e16(q.y) << 16);
+    }
+}
+
+// Corners of the nodes whose triangles `corner(i)` lists, in wave-sized columns.
+template <typename F, typename G>
+void fill_rings(TArr& A, int n, const F& corners, const G& entry) {
+    A.rstride = (n + 63) & ~63;
+    A.rmax = 1;
+    for (int i = 0; i < n; ++i) A.rmax = std::max(A.rmax, (int)corners(i).size());
+    A.ring.assign((size_t)A.rmax * A.rstride, make_int4(-1, -1, -1, -1));
+    A.ringb.assign(A.ring.size(), make_int2(-1, -1));
+    for (int i = 0; i < n; ++i) {
+        const std::vector<int>& c = corners(i);
+        for (size_t j = 0; j < c.size(); ++j) entry(c[j], A.ring[j * A.rstride + i], A.ringb[j * A.rstride + i]);
+    }
+}
 
 TArr template_arrays(const Template& T) {
     TArr A;
     A.nv = T.nv;
     A.nt = T.nt;
     A.ne = T.ne;
-    A.tri = T.tri;
+    for (int t = 0; t < T.nt; ++t) A.tri.push_back(make_int4(T.tri[3 * t], T.tri[3 * t + 1], T.tri[3 * t + 2], 0));
     A.L0 = T.L0;
-    A.th = T.theta0;
     A.S0 = T.S0;
     A.hbar = T.hbar;
+    A.kth.resize(T.ne);
     A.cs0.resize(2 * (size_t)T.ne);
+    A.hv.resize(T.ne);
     for (int e = 0; e < T.ne; ++e) {
+        A.kth[e] = T.k.kb / T.theta0[e];
         A.cs0[2 * e] = std::cos(T.theta0[e] - M_PI);
         A.cs0[2 * e + 1] = std::sin(T.theta0[e] - M_PI);
+        A.hv[e] = make_int4(T.hinge[e][0], T.hinge[e][1], T.hinge[e][2], T.hinge[e][3]);
     }
-    A.hv.resize(T.ne);
-    for (int e = 0; e < T.ne; ++e) A.hv[e] = make_int4(T.hinge[e][0], T.hinge[e][1], T.hinge[e][2], T.hinge[e][3]);
-    A.noff.resize((size_t)T.nv + 1);
-    for (int v = 0; v <= T.nv; ++v) A.noff[v] = make_int4(T.e_off[v], T.h_off[v], T.t_off[v], 0);
-    A.einc.resize(T.e_inc.size());
-    for (size_t k = 0; k < T.e_inc.size(); ++k) A.einc[k] = make_int2(T.e_inc[k][0], T.e_inc[k][1]);
-    A.hinc.resize(T.h_inc.size());
-    for (size_t k = 0; k < T.h_inc.size(); ++k) {
-        const int e = T.h_inc[k] >> 2;
-        A.hinc[k] = make_int4(T.h_inc[k], T.hinge_tri[e][0], T.hinge_tri[e][1], 0);
-    }
-    A.tinc.resize(T.t_inc.size());
-    for (size_t k = 0; k < T.t_inc.size(); ++k) {
-        const int t = T.t_inc[k] >> 2, s3 = T.t_inc[k] & 3;
-        A.tinc[k] = make_int4(t, T.tri[3 * t + (s3 + 1) % 3], T.tri[3 * t + (s3 + 2) % 3], 0);
-    }
+    fill_rings(A, T.nv, [&](int i) -> const std::vector<int>& { return T.corner[i]; },
+               [&](int code, int4& p, int2& q) { corner_entry(T, code, nullptr, nullptr, nullptr, p, q); });
     A.order = T.order;
     A.slice_off = T.slice_off;
+    narrow(A);
     return A;
 }
 
 // Sub-template of patch k: the patch's nodes first (in slice order), then the
 // other nodes its triangles and hinges reach; the triangles and hinges the
-// patch nodes' gathers read; incidence lists of the patch nodes only, entry
-// for entry those of the template, renumbered (so a node's forces are summed
-// in the same order as in the whole template).
+// patch nodes' gathers read (those of their corners); the corners of the patch
+// nodes only, entry for entry those of the template, renumbered (so a node's
+// forces are summed in the same order as in the whole template).
 TArr patch_arrays(const Template& T, const TArr& A, int k) {
     TArr P;
     std::vector<int> nl(T.nv, -1), tl(T.nt, -1), el(T.ne, -1), tris, edges;
-    auto addn = [&](int v) {
-        if (nl[v] < 0) {
-            nl[v] = (int)P.order.size();
-            P.order.push_back(v);
-        }
-    };
-    auto addt = [&](int t) {
-        if (tl[t] < 0) {
-            tl[t] = (int)tris.size();
-            tris.push_back(t);
-        }
-    };
-    auto adde = [&](int e) {
-        if (el[e] < 0) {
-            el[e] = (int)edges.size();
-            edges.push_back(e);
+    auto add = [](std::vector<int>& local, std::vector<int>& list, int v) {
+        if (local[v] < 0) {
+            local[v] = (int)list.size();
+            list.push_back(v);
         }
     };
     const int s0 = T.slice_off[k], s1 = T.slice_off[k + 1], np = s1 - s0;
-    for (int i = s0; i < s1; ++i) addn(T.order[i]);
-    for (int i = 0; i < np; ++i) {
-        const int v = P.order[i];
-        const int4 o0 = A.noff[v], o1 = A.noff[v + 1];
-        for (int q = o0.x; q < o1.x; ++q) adde(A.einc[q].y);
-        for (int q = o0.y; q < o1.y; ++q) {
-            adde(A.hinc[q].x >> 2);
-            addt(A.hinc[q].y);
-            addt(A.hinc[q].z);
+    for (int i = s0; i < s1; ++i) add(nl, P.order, T.order[i]);
+    for (int i = 0; i < np; ++i)
+        for (int code : T.corner[P.order[i]]) {
+            const int t = code >> 2;
+            add(tl, tris, t);
+            for (int s3 = 0; s3 < 3; ++s3) {
+                const int s = T.side[3 * t + s3];
+                add(el, edges, s < 0 ? ~s : s);
+            }
         }
-        for (int q = o0.z; q < o1.z; ++q) addt(A.tinc[q].x);
-    }
     for (int t : tris)
-        for (int a = 0; a < 3; ++a) addn(A.tri[3 * t + a]);
-    for (int e : edges) {
-        addn(A.hv[e].x);
-        addn(A.hv[e].y);
-        addn(A.hv[e].z);
-        addn(A.hv[e].w);
-    }
+        for (int v : {A.tri[t].x, A.tri[t].y, A.tri[t].z}) add(nl, P.order, v);
+    for (int e : edges)
+        for (int v : {A.hv[e].x, A.hv[e].y, A.hv[e].z, A.hv[e].w}) add(nl, P.order, v);
     P.nv = (int)P.order.size();
     P.nt = (int)tris.size();
     P.ne = (int)edges.size();
     for (int t : tris) {
-        for (int a = 0; a < 3; ++a) P.tri.push_back(nl[A.tri[3 * t + a]]);
+        P.tri.push_back(make_int4(nl[A.tri[t].x], nl[A.tri[t].y], nl[A.tri[t].z], 0));
         P.S0.push_back(A.S0[t]);
     }
     for (int e : edges) {
         const int4 h = A.hv[e];
         P.hv.push_back(make_int4(nl[h.x], nl[h.y], nl[h.z], nl[h.w]));
         P.L0.push_back(A.L0[e]);
-        P.th.push_back(A.th[e]);
+        P.kth.push_back(A.kth[e]);
         P.cs0.push_back(A.cs0[2 * e]);
         P.cs0.push_back(A.cs0[2 * e + 1]);
         P.hbar.push_back(A.hbar[e]);
     }
-    P.noff.resize((size_t)P.nv + 1);
-    for (int i = 0; i < P.nv; ++i) {
-        P.noff[i] = make_int4((int)P.einc.size(), (int)P.hinc.size(), (int)P.tinc.size(), 0);
-        if (i >= np) continue;
-        const int v = P.order[i];
-        const int4 o0 = A.noff[v], o1 = A.noff[v + 1];
-        for (int q = o0.x; q < o1.x; ++q) P.einc.push_back(make_int2(nl[A.einc[q].x], el[A.einc[q].y]));
-        for (int q = o0.y; q < o1.y; ++q) {
-            const int4 h = A.hinc[q];
-            P.hinc.push_back(make_int4((el[h.x >> 2] << 2) | (h.x & 3), tl[h.y], tl[h.z], 0));
-        }
-        for (int q = o0.z; q < o1.z; ++q) {
-            const int4 r = A.tinc[q];
-            P.tinc.push_back(make_int4(tl[r.x], nl[r.y], nl[r.z], 0));
-        }
-    }
-    P.noff[P.nv] = make_int4((int)P.einc.size(), (int)P.hinc.size(), (int)P.tinc.size(), 0);
+    fill_rings(P, np, [&](int i) -> const std::vector<int>& { return T.corner[P.order[i]]; },
+               [&](int code, int4& p, int2& q) { corner_entry(T, code, nl.data(), tl.data(), el.data(), p, q); });
     P.slice_off = {0, np};
+    narrow(P);
     return P;
 }
 
@@ -783,9 +783,9 @@ size_t vbytes(const std::vector<V>& v) {
 }
 
 size_t tarr_bytes(const TArr& A) {
-    return vbytes(A.tri) + vbytes(A.noff) + vbytes(A.einc) + vbytes(A.hinc) + vbytes(A.tinc) + vbytes(A.L0) +
-           vbytes(A.hv) + vbytes(A.th) + vbytes(A.cs0) + vbytes(A.S0) + vbytes(A.hbar) + vbytes(A.order) +
-           vbytes(A.slice_off);
+    return vbytes(A.tri) + vbytes(A.hv) + vbytes(A.ring) + vbytes(A.ringb) + vbytes(A.tri16) + vbytes(A.hv16) +
+           vbytes(A.ring16) + vbytes(A.ring16b) + vbytes(A.L0) + vbytes(A.kth) + vbytes(A.cs0) + vbytes(A.S0) +
+           vbytes(A.hbar) + vbytes(A.order) + vbytes(A.slice_off);
 }
 
 // Copies A's arrays to host[..] and points D's arrays at dev[..] (the same
@@ -802,14 +802,18 @@ void tarr_place(const TArr& A, unsigned char* host, unsigned char* dev, TmplDev<
     D.nv = A.nv;
     D.nt = A.nt;
     D.ne = A.ne;
-    D.tri = (const int*)put(A.tri);
-    D.n_off = (const int4*)put(A.noff);
-    D.e_inc = (const int2*)put(A.einc);
-    D.h_inc = (const int4*)put(A.hinc);
-    D.t_inc = (const int4*)put(A.tinc);
+    D.rstride = A.rstride;
+    D.rmax = A.rmax;
+    D.tri32 = (const int4*)put(A.tri);
+    D.hinge32 = (const int4*)put(A.hv);
+    D.ring32 = (const int4*)put(A.ring);
+    D.ring32b = (const int2*)put(A.ringb);
+    D.tri16 = (const ushort4*)put(A.tri16);
+    D.hinge16 = (const ushort4*)put(A.hv16);
+    D.ring16 = (const uint2*)put(A.ring16);
+    D.ring16b = (const unsigned*)put(A.ring16b);
     D.L0 = (const double*)put(A.L0);
-    D.hinge = (const int4*)put(A.hv);
-    D.theta0 = (const double*)put(A.th);
+    D.kth = (const double*)put(A.kth);
     D.cs0 = (const double2*)put(A.cs0);
     D.S0 = (const double*)put(A.S0);
     D.hbar = (const double*)put(A.hbar);
