@@ -4,6 +4,7 @@
 
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <math.h>
 #include <stdint.h>
 
@@ -189,6 +190,53 @@ __device__ inline double block_sum(double v, double* red) {
     for (int k = 0; k < nw; ++k) tot += red[k];
     __syncthreads();
     return tot;
+}
+
+// Cross-lane moves inside the vector ALU (no LDS round trip): each step takes
+// a lane's value from a lower lane, `old` where there is none.  The reductions
+// below combine 1, 2, 4, 8 lanes of a row of 16, then (row_bcast) the rows, so
+// that lane 63 holds the wave's result and lane 16 k + 15 its row's, in a fixed
+// order.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp(int old, int v) {
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
+}
+constexpr int DPP_SHR1 = 0x111, DPP_SHR2 = 0x112, DPP_SHR4 = 0x114, DPP_SHR8 = 0x118, DPP_BC15 = 0x142, DPP_BC31 = 0x143;
+__device__ __forceinline__ int row_min(int v) {
+    v = min(v, dpp<DPP_SHR1, 0xf>(INT_MAX, v));
+    v = min(v, dpp<DPP_SHR2, 0xf>(INT_MAX, v));
+    v = min(v, dpp<DPP_SHR4, 0xf>(INT_MAX, v));
+    return min(v, dpp<DPP_SHR8, 0xf>(INT_MAX, v));
+}
+__device__ __forceinline__ int wave_min(int v) {
+    v = row_min(v);
+    v = min(v, dpp<DPP_BC15, 0xa>(INT_MAX, v));
+    return min(v, dpp<DPP_BC31, 0xc>(INT_MAX, v));
+}
+// inclusive prefix sum over the wave's lanes
+__device__ __forceinline__ int wave_scan(int v) {
+    v += dpp<DPP_SHR1, 0xf>(0, v);
+    v += dpp<DPP_SHR2, 0xf>(0, v);
+    v += dpp<DPP_SHR4, 0xf>(0, v);
+    v += dpp<DPP_SHR8, 0xf>(0, v);
+    v += dpp<DPP_BC15, 0xa>(0, v);
+    return v + dpp<DPP_BC31, 0xc>(0, v);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = dpp<CTRL, ROWS>(0, (int)b), hi = dpp<CTRL, ROWS>(0, (int)(b >> 32));
+    return v + __builtin_bit_cast(double, (long long)((unsigned long long)(unsigned)hi << 32 | (unsigned)lo));
+}
+__device__ __forceinline__ double row_sum(double v) {
+    return dpp_add<DPP_SHR8, 0xf>(dpp_add<DPP_SHR4, 0xf>(dpp_add<DPP_SHR2, 0xf>(dpp_add<DPP_SHR1, 0xf>(v))));
+}
+__device__ __forceinline__ double wave_sum(double v) { return dpp_add<DPP_BC31, 0xc>(dpp_add<DPP_BC15, 0xa>(row_sum(v))); }
+// lane k's value, uniform
+__device__ __forceinline__ double lane_value(double v, int k) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)b, k), hi = __builtin_amdgcn_readlane((int)(b >> 32), k);
+    return __builtin_bit_cast(double, (long long)((unsigned long long)hi << 32 | lo));
 }
 
 // Merge per-lane integer bounds [lo, hi] (3 axes) into the block's bbox[6]

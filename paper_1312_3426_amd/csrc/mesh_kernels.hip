@@ -5,18 +5,22 @@
 // interpolation of the fluid velocity and distribution of the reaction).
 //
 // One workgroup per object.  Its node positions are staged in LDS (FP64), then
-//   1. per triangle: unit inward normal, area, (S - S0)/S; FP64 block sums of
+//   1. the lattice nodes its stencils touch: marked in the bits of a box,
+//      numbered, and their populations asked for;
+//   2. per triangle: unit inward normal, area, (S - S0)/S; FP64 block sums of
 //      the object's area and volume (divergence theorem, signed tetrahedra);
-//   2. per edge: the stretching coefficient from the strain (L - L0)/L0 and
+//   3. per edge: the stretching coefficient from the strain (L - L0)/L0 and
 //      the bending magnitude from theta - theta0, both formed in FP64 so the
-//      cancellation near the relaxed shape keeps its digits;
-//   3. per node: gather of its corners' contributions in a fixed order
-//      (deterministic, no atomics), trilinear interpolation of the
-//      fluid velocity from the 8 surrounding nodes, drag, symplectic Euler
-//      update, and spreading of the reaction to the 8 nodes (int64 fixed-point
-//      atomics: one word per component in the FP32 forms, a 2^-30 / 2^-80
-//      pair of words in the FP64 form; exact, so order-independent) with the
-//      nodes' mask bits set.
+//      cancellation near the relaxed shape keeps its digits; then the fluid
+//      velocity from the populations that have arrived;
+//   4. per node: gather of its corners' contributions in a fixed order
+//      (deterministic, no atomics);
+//   5. per node: trilinear interpolation of the fluid velocity from the 8
+//      surrounding nodes, drag, symplectic Euler update, and spreading of the
+//      reaction to the 8 nodes (int64 fixed-point sums in LDS, then atomics:
+//      one word per component in the FP32 forms, a 2^-30 / 2^-80 pair of words
+//      in the FP64 form; exact, so order-independent) with the nodes' mask
+//      bits set.
 // With velocity Verlet (the integrator of the paper's engine) the staged
 // positions are first advanced by the half-step velocity V + F_last/(2m), the
 // forces and the drag are taken there (drag at the half-step velocity), and
@@ -158,15 +162,17 @@ void dynlds_kernels(std::vector<const void*>& v) {
 
 }  // namespace
 
-size_t mesh_lds_bytes(int precision, int nv, int nt, int ne, int ucap, int ccap, int cons) {
-    return mesh_layout(precision == PREC_FP64 ? sizeof(double) : sizeof(float), nv, nt, ne, ucap, ccap, cons)
-        .total;
+static MeshLayout layout_of(int precision, int nv, int nt, int ne, int ucap, int ccap, int cons, bool lds) {
+    return mesh_layout(precision == PREC_FP64 ? sizeof(double) : sizeof(float), nv, nt, ne, ucap, ccap, cons, lds);
 }
-
+size_t mesh_lds_bytes(int precision, int nv, int nt, int ne, int ucap, int ccap, int cons) {
+    return layout_of(precision, nv, nt, ne, ucap, ccap, cons, true).total;
+}
 size_t mesh_cpl_lds_bytes(int precision, int nv, int nt, int ne, int ucap, int ccap, int cons) {
-    const MeshLayout L =
-        mesh_layout(precision == PREC_FP64 ? sizeof(double) : sizeof(float), nv, nt, ne, ucap, ccap, cons);
-    return align16(L.gacc + (size_t)ccap * (precision == PREC_FP64 ? 6 : 3) * 8) - L.need;
+    return layout_of(precision, nv, nt, ne, ucap, ccap, cons, false).coupling;
+}
+size_t mesh_scratch_bytes(int precision, int nv, int nt, int ne, int ucap, int ccap, int cons) {
+    return layout_of(precision, nv, nt, ne, ucap, ccap, cons, false).total;
 }
 
 hipError_t launch_mesh(const MeshLaunch& L) {

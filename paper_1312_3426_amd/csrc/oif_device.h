@@ -126,46 +126,59 @@ struct TmplDev {
     const TmplDev* subs;   // [nslice], null when nslice == 1
 };
 
-// Per-object LDS (or global scratch) layout of the membrane kernel, R = the
-// arithmetic type:
-//   fs  elastic force per node, R [nv][3]
-//   then a region used twice:
-//     forces phase:  xs  node positions, FP64 [nv][3]
-//                    tn  unit inward normal + area per triangle, R [nt][4]
-//                    tr  (S - S0)/S per triangle, R [nt]
-//                    se  stretching coefficient per edge, R [ne]
-//                    fh  bending coefficients per edge: R [ne] (the paper's
-//                        magnitude) or R [ne][4] (conservative model: wing
-//                        factors c/h_A, c/h_D and foot positions a_A, a_D)
-//     coupling phase: need  one bit per node of the object's stencil box
-//                     pre   exclusive popcount prefix per bit word
-//                     ug    fluid velocity at the touched nodes, R [ccap][3]
-//                     qn    their lattice indices, int [ccap]
-//                     gacc  summed reaction force, 8-byte accumulators [ccap][3]
-// (the coupling phase reads the node positions from HBM again, so the
-// positions need not outlive the forces phase)
+// Per-object layout of the membrane kernel, R = the arithmetic type:
+//   forces:   xs   node positions, FP64 [nv][3]
+//             tn   unit inward normal + area per triangle, R [nt][4]
+//             tr   -kal (S - S0)/S per triangle, R [nt]
+//             se   stretching coefficient per edge, R [ne]
+//             fh   bending coefficients per edge: R [ne] (the paper's
+//                  magnitude) or R [ne][4] (conservative model: wing
+//                  factors w = c/h_A, c/h_D and a_A w_A, a_D w_D, a the
+//                  feet's positions on the edge)
+//             fs   elastic force per node, R [nv][3]
+//   coupling: gacc summed reaction force at the touched lattice nodes, 8-byte
+//                  accumulators [ccap][3] (FP64 form [ccap][6])
+//             ug   fluid velocity there, R [ccap][3]
+//             need one bit per node of the object's stencil box
+//             pw   its words with their exclusive popcount prefix, uint2
+//             qn   lattice indices of the touched nodes, int [ccap]
+// In LDS the coupling's gacc and ug overlie the forces' arrays, which are dead
+// once every node has its force, and the bits, dead once counted, lie under
+// fs (the positions are read from HBM again after the gather).  A mesh in the
+// global scratch has both parts side by side, or the coupling part in LDS.
 struct MeshLayout {
-    size_t fs, xs, tn, tr, se, fh, need, nwords, ug, qn, gacc, total;
+    size_t xs, tn, tr, se, fh, fs, forces;        // offsets and size of the forces part
+    size_t gacc, ug, need, pw, qn, coupling;      // of the coupling part (in LDS mode from the same base)
+    size_t nwords, total;
 };
 __host__ __device__ inline size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
-__host__ __device__ inline MeshLayout mesh_layout(size_t r, int nv, int nt, int ne, int ucap, int ccap,
-                                                   int cons) {
+__host__ __device__ inline MeshLayout mesh_layout(size_t r, int nv, int nt, int ne, int ucap, int ccap, int cons,
+                                                  bool lds) {
     MeshLayout L;
-    L.fs = 0;
-    L.xs = align16((size_t)nv * 3 * r);
-    L.tn = align16(L.xs + (size_t)nv * 3 * sizeof(double));
+    L.nwords = ((size_t)ucap + 31) / 32;
+    L.xs = 0;
+    L.tn = align16((size_t)nv * 3 * sizeof(double));
     L.tr = L.tn + (size_t)nt * 4 * r;
     L.se = align16(L.tr + (size_t)nt * r);
     L.fh = align16(L.se + (size_t)ne * r);
-    const size_t end_forces = L.fh + (size_t)ne * r * (cons ? 4 : 1);
-    L.need = L.xs;
-    L.nwords = ((size_t)ucap + 31) / 32;
-    L.ug = align16(L.need + 2 * L.nwords * 4);
-    L.qn = L.ug + (size_t)ccap * 3 * r;
-    L.gacc = align16(L.qn + (size_t)ccap * 4);
-    // summed reaction force: 3 int64 words per node (FP32 forms), 6 (FP64)
-    const size_t end_coupling = L.gacc + (size_t)ccap * (r == 8 ? 6 : 3) * 8;
-    L.total = align16(end_forces > end_coupling ? end_forces : end_coupling);
+    const size_t end = align16(L.fh + (size_t)ne * r * (cons ? 4 : 1));
+    const size_t fsb = (size_t)nv * 3 * r, bits = L.nwords * 4;
+    L.gacc = 0;
+    L.ug = (size_t)ccap * (r == 8 ? 6 : 3) * 8;
+    const size_t uend = align16(L.ug + (size_t)ccap * 3 * r);
+    if (lds) {
+        L.fs = end > uend ? end : uend;
+        L.need = L.fs;
+        L.pw = align16(L.fs + (fsb > bits ? fsb : bits));
+    } else {
+        L.fs = end;
+        L.need = uend;
+        L.pw = align16(L.need + bits);
+    }
+    L.forces = align16(L.fs + fsb);
+    L.qn = L.pw + L.nwords * 8;
+    L.coupling = align16(L.qn + (size_t)ccap * 4);
+    L.total = lds ? L.coupling : L.forces + L.coupling;
     return L;
 }
 
@@ -174,9 +187,9 @@ __host__ __device__ inline MeshLayout mesh_layout(size_t r, int nv, int nt, int 
 enum { PH_ALL = 0, PH_SUMS = 1, PH_PATCH = 2 };
 // LDS of the split launches: the sums launch holds the object's positions
 // (FP64 [nv][3]); the patch launch the mesh layout of the patch's
-// sub-template.  The object's scratch: its mesh layout, then the area and
-// volume sums of each slice (double [nslice][2]).
-__host__ __device__ inline size_t split_part_offset(const MeshLayout& L) { return align16(L.total); }
+// sub-template.  The object's scratch: its mesh layout (both parts), then the
+// area and volume sums of each slice (double [nslice][2]).
+__host__ __device__ inline size_t split_part_offset(const MeshLayout& L) { return L.total; }
 
 template <typename real>
 struct ObjDev {
@@ -305,8 +318,9 @@ hipError_t launch_repulsion(const RepDev& h, const RepDev* d, const void* objs, 
 
 // Per-template LDS bytes of the mesh kernel.
 size_t mesh_lds_bytes(int precision, int nv, int nt, int ne, int ucap, int ccap, int cons);
-// Bytes of the coupling area alone (the part of the layout from `need` on).
+// Bytes of the coupling part alone, and of the whole layout in the global scratch.
 size_t mesh_cpl_lds_bytes(int precision, int nv, int nt, int ne, int ucap, int ccap, int cons);
+size_t mesh_scratch_bytes(int precision, int nv, int nt, int ne, int ucap, int ccap, int cons);
 // Allow the LDS-resident mesh kernels to use up to `bytes` of dynamic LDS.
 hipError_t mesh_set_max_lds(size_t bytes);
 

@@ -951,7 +951,8 @@ int upload_mesh_t(oif_ctx* c) {
     // scratch of an object outside LDS: the mesh layout, then the slices' sums
     auto scratch_bytes = [&](int i) {
         const Template& T = c->tmpl[c->obj[i].tid];
-        return (need(i) + 16 * (size_t)T.nslice + 16 + 255) & ~(size_t)255;
+        return (mesh_scratch_bytes(c->d.precision, T.nv, T.nt, T.ne, T.ucap, T.ccap, tmpl_conservative(T)) +
+                16 * (size_t)T.nslice + 16 + 255) & ~(size_t)255;
     };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         const int ga = group(a), gb = group(b);
