@@ -161,10 +161,25 @@ __device__ __forceinline__ double2 gld(const double2* p) {
     const v2 v = *(gptr<const v2>)p;
     return make_double2(v.x, v.y);
 }
-__device__ __forceinline__ uint2 gld(const uint2* p) {
-    typedef unsigned v2 __attribute__((ext_vector_type(2)));
-    const v2 v = *(gptr<const v2>)p;
-    return make_uint2(v.x, v.y);
+// element i of an array below 4 GiB (uniform base, 32-bit offset)
+template <typename T>
+__device__ __forceinline__ T gat(const T* base, int i) {
+    return gload(base, (unsigned)i * (unsigned)sizeof(T));
+}
+__device__ __forceinline__ int4 gat(const int4* base, int i) {
+    typedef int v4 __attribute__((ext_vector_type(4)));
+    const v4 v = gload((const v4*)base, (unsigned)i * 16u);
+    return make_int4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint4 gat(const uint4* base, int i) {
+    typedef unsigned v4 __attribute__((ext_vector_type(4)));
+    const v4 v = gload((const v4*)base, (unsigned)i * 16u);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ double2 gat(const double2* base, int i) {
+    typedef double v2 __attribute__((ext_vector_type(2)));
+    const v2 v = gload((const v2*)base, (unsigned)i * 16u);
+    return make_double2(v.x, v.y);
 }
 template <typename T>
 __device__ __forceinline__ T gatomic_add(T* p, T v) {

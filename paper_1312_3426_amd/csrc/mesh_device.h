@@ -188,50 +188,79 @@ __device__ __forceinline__ float angle_of(float y, float x) {
     return atan2f(y, x);
 }
 
-// One corner of a node (TmplDev::ring16 / ring32): the flags of ea, eb, o sit
-// in bits 0, 1, 2 of fl.
+// x > 0 (a stretch ratio): the square root by the refined reciprocal one
+__device__ __forceinline__ double sqrt_r(double x) { return sqrt(x); }
+__device__ __forceinline__ float sqrt_r(float x) { return x * rsqrt_r(x); }
+
+// Records of a triangle, an edge and a node's corner as loaded (TmplDev), in
+// 16- or 32-bit numbers.
+struct TriRec {
+    int a, b, c;
+    double S0;
+};
+struct EdgeRec {
+    int A, B, C, D;
+    double L0;
+};
 struct Corner {
     int a, b, t, ea, eb, o;
-    unsigned fl;
+    bool t2a, t2b, t2o, valid;  // the triangle is the edge's T2; false: a repeated corner
 };
-struct RawCorner16 {
-    uint2 p;
-    unsigned q;
-    __device__ __forceinline__ bool valid() const { return p.x != 0xffffffffu; }
-    __device__ __forceinline__ Corner get() const {
-        return Corner{(int)(p.x & 0xffffu), (int)(p.x >> 16), (int)(p.y & 0xffffu), (int)((p.y >> 16) & 0x7fffu),
-                      (int)(q & 0x7fffu), (int)((q >> 16) & 0x7fffu),
-                      (p.y >> 31) | ((q >> 14) & 2u) | ((q >> 29) & 4u)};
-    }
-};
-struct RawCorner32 {
-    int4 p;
-    int2 q;
-    __device__ __forceinline__ bool valid() const { return p.x >= 0; }
-    __device__ __forceinline__ Corner get() const {
-        return Corner{p.x, p.y, p.z, p.w & 0x7fffffff, q.x & 0x7fffffff, q.y & 0x7fffffff,
-                      ((unsigned)p.w >> 31) | (((unsigned)q.x >> 30) & 2u) | (((unsigned)q.y >> 29) & 4u)};
-    }
-};
-template <class TP>
-__device__ __forceinline__ void load_corner(TP T, int j, int v, RawCorner16& c) {
-    const int k = j * T->rstride + v;
-    c.p = gld(T->ring16 + k);
-    c.q = gld(T->ring16b + k);
+__device__ __forceinline__ double double_of(unsigned lo, unsigned hi) {
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
 }
-template <class TP>
-__device__ __forceinline__ void load_corner(TP T, int j, int v, RawCorner32& c) {
-    const int k = j * T->rstride + v;
-    c.p = gld(T->ring32 + k);
-    c.q = gld(T->ring32b + k);
-}
-// triangle (a, b, c, -) and hinge (A, B, C, D) of 16- or 32-bit lists
 template <bool WIDE>
-__device__ __forceinline__ int4 load_quad(const ushort4* q16, const int4* q32, int k) {
-    if (WIDE) return gld(q32 + k);
-    const uint2 q = gld((const uint2*)q16 + k);
-    return make_int4((int)(q.x & 0xffffu), (int)(q.x >> 16), (int)(q.y & 0xffffu), (int)(q.y >> 16));
-}
+struct Lists;
+template <>
+struct Lists<false> {
+    typedef uint4 Raw;
+    const uint4 *tri, *edge, *ring;
+    int rstride;
+    template <class TP>
+    __device__ __forceinline__ explicit Lists(TP T) : tri(T->tri16), edge(T->edge16), ring(T->ring16), rstride(T->rstride) {}
+    __device__ __forceinline__ TriRec triangle(int t) const {
+        const uint4 r = gat(tri, t);
+        return TriRec{(int)(r.x & 0xffffu), (int)(r.x >> 16), (int)r.y, double_of(r.z, r.w)};
+    }
+    __device__ __forceinline__ EdgeRec hinge(int e) const {
+        const uint4 r = gat(edge, e);
+        return EdgeRec{(int)(r.x & 0xffffu), (int)(r.x >> 16), (int)(r.y & 0xffffu), (int)(r.y >> 16), double_of(r.z, r.w)};
+    }
+    __device__ __forceinline__ Raw raw(int j, int v) const { return gat(ring, j * rstride + v); }
+    __device__ __forceinline__ static Corner corner(const Raw& r) {
+        return Corner{(int)(r.x & 0xffffu), (int)(r.x >> 16), (int)(r.y & 0xffffu), (int)((r.y >> 16) & 0x7fffu),
+                      (int)(r.z & 0x7fffu), (int)((r.z >> 16) & 0x7fffu),
+                      (r.y >> 31) != 0u, (r.z & 0x8000u) != 0u, (r.z >> 31) != 0u, r.w != 0u};
+    }
+};
+template <>
+struct Lists<true> {
+    struct Raw {
+        int4 p, q;
+    };
+    const int4 *tri, *edge, *ring;
+    const double *S0, *L0;
+    int rstride;
+    template <class TP>
+    __device__ __forceinline__ explicit Lists(TP T)
+        : tri(T->tri32), edge(T->hinge32), ring(T->ring32), S0(T->S0), L0(T->L0), rstride(T->rstride) {}
+    __device__ __forceinline__ TriRec triangle(int t) const {
+        const int4 r = gat(tri, t);
+        return TriRec{r.x, r.y, r.z, gat(S0, t)};
+    }
+    __device__ __forceinline__ EdgeRec hinge(int e) const {
+        const int4 r = gat(edge, e);
+        return EdgeRec{r.x, r.y, r.z, r.w, gat(L0, e)};
+    }
+    __device__ __forceinline__ Raw raw(int j, int v) const {
+        const int k = 2 * (j * rstride + v);
+        return Raw{gat(ring, k), gat(ring, k + 1)};
+    }
+    __device__ __forceinline__ static Corner corner(const Raw& r) {
+        return Corner{r.p.x, r.p.y, r.p.z, r.p.w & 0x7fffffff, r.q.x & 0x7fffffff, r.q.y & 0x7fffffff,
+                      r.p.w < 0, r.q.x < 0, r.q.y < 0, r.q.z != 0};
+    }
+};
 
 // Stencil marking of one object for split stepping: every lattice node inside
 // the 2x2x2 stencil of a finite node position gets its bit in `touch`.  The
@@ -404,7 +433,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     // same bits).
     const R half_im = R(0.5) * O.inv_mass;
     auto stage = [&](int k) -> double {
-        return O.F ? gld(O.X + k) + (double)fmadd(gld(O.F + k), half_im, gld(O.V + k)) : gld(O.X + k);
+        return O.F ? gat(O.X, k) + (double)fmadd(gat(O.F, k), half_im, gat(O.V, k)) : gat(O.X, k);
     };
     // The stencil box is found on the way: each wave's bounds are reduced in
     // its lanes and meet in LDS.
@@ -575,49 +604,147 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         y = (jy + R(0.5) * gy_) * ir;
         z = (jz + R(0.5) * gz_) * ir;
     };
-    S raw0[19];
-    int q0 = 0;
-    const bool mine = compact && tid < ncomp;
-    if (mine) {
-        q0 = qn[tid];
-        ask(q0, raw0);
-    }
+    // Triangles, edges and the touched nodes' velocities, side by side: the
+    // last waves of the workgroup (a quarter to a third of them) fetch
+    // populations, one touched node a lane and up to four rounds, while the
+    // others compute the elements, a wave of 64 triangles or edges at a time.
+    // Waves of their own because a wave's loads return in order: a fetching
+    // wave that also read element records would wait for its populations
+    // first.  (The populations of a 642-node sphere lie in some 2000 lines of
+    // 128 bytes; all objects of a launch fetch at once: 500 of them move 170 MB,
+    // half of the launch's time at the memory's rate.)  With one 16-byte record
+    // per triangle, edge and corner in place of two or three loads, and no
+    // branches between a node's corners: 500 spheres FP16 46.7 -> 43.4 us (FP32
+    // 58.0 -> 57.3, bound by the fetch), 120 conservative ones FP64 53.1 -> 48.0,
+    // 32 uneven boxes 86.6 -> 80.7.
+    constexpr int VROUNDS = 4, VDEPTH = sizeof(S) == 8 ? 1 : 2;
+    const int nvw = compact ? min((ncomp + 255) >> 8, nwave / 3) : 0;  // fetching waves
+    const int cw = nwave - nvw, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    R uv[VROUNDS][3];
+    const int vt = tid - 64 * cw, vn = 64 * nvw;  // this lane's first touched node, nodes a round
 
-    // 1. triangles
+    constexpr bool WIDE = !USE_LDS && PH == PH_ALL;  // mesh in the global scratch: 32-bit lists
+    const Lists<WIDE> lists_of(T);
+    const R kal = (R)T->kal, ks = (R)T->ks;
+    const bool do_s = T->ks != 0.0, do_b = T->kb != 0.0, linear = T->linear != 0;
     // (S - S0 is formed as (S^2 - S0^2)/(S + S0): the cancelling difference in
     // FP64 multiply-adds, the square root and division in the arithmetic type)
-    constexpr bool WIDE = !USE_LDS && PH == PH_ALL;  // mesh in the global scratch: 32-bit lists
-    const R kal = (R)T->kal;
     double sdarea = 0.0, svol = 0.0;
-    {
+    auto triangle = [&](int t, const TriRec& q, double r0x, double r0y, double r0z) {
+#pragma clang fp contract(off)
+        const double ax = xs[3 * q.a], ay = xs[3 * q.a + 1], az = xs[3 * q.a + 2];
+        const double abx = xs[3 * q.b] - ax, aby = xs[3 * q.b + 1] - ay, abz = xs[3 * q.b + 2] - az;
+        const double acx = xs[3 * q.c] - ax, acy = xs[3 * q.c + 1] - ay, acz = xs[3 * q.c + 2] - az;
+        const double nx_ = fmadd(aby, acz, -(abz * acy));
+        const double ny_ = fmadd(abz, acx, -(abx * acz));
+        const double nz_ = fmadd(abx, acy, -(aby * acx));
+        const double n2 = fmadd(nx_, nx_, fmadd(ny_, ny_, nz_ * nz_));  // 4 S^2
+        const R rl = rsqrt_r((R)n2);
+        const R S = R(0.5) * (R)n2 * rl;
+        const R dS = div_r((R)fmadd(0.25, n2, -(q.S0 * q.S0)), S + (R)q.S0);
+        if (PH != PH_SUMS) {  // the sums launch keeps the sums only
+            tn[4 * t + 0] = (R)nx_ * rl;
+            tn[4 * t + 1] = (R)ny_ * rl;
+            tn[4 * t + 2] = (R)nz_ * rl;
+            tn[4 * t + 3] = S;
+            tr[t] = -kal * (R(2) * dS * rl);
+        }
+        sdarea += (double)dS;
+        // signed tetrahedron (node 0, a, b, c): a . N = -6 V for inward N
+        svol = fmadd(ax - r0x, nx_, fmadd(ay - r0y, ny_, fmadd(az - r0z, nz_, svol)));
+    };
+    // stretching coefficient and bending magnitude of a hinge
+    auto edge = [&](int e, const EdgeRec& h, const double2& cs, double kth) {
+#pragma clang fp contract(off)
+        const double bx = xs[3 * h.B], by = xs[3 * h.B + 1], bz = xs[3 * h.B + 2];
+        const double cx_ = xs[3 * h.C], cy_ = xs[3 * h.C + 1], cz_ = xs[3 * h.C + 2];
+        const double dx = cx_ - bx, dy = cy_ - by, dz = cz_ - bz;
+        const double L2 = fmadd(dx, dx, fmadd(dy, dy, dz * dz));
+        double L;
+        R rL;
+        length_of(L2, L, rL);
+        R s = R(0);
+        if (do_s) {
+            // strain (L - L0)/L0 = (L^2 - L0^2) / (L0 (L + L0)); neo-Hookean
+            // kappa = (lam^1/2 + lam^-5/2) / (lam + lam^-3)
+            //       = lam^1/2 (1 + lam^3) / (1 + lam^4)
+            const R strain = div_r((R)fmadd(-h.L0, h.L0, L2), (R)(h.L0 * (L + h.L0)));
+            R kap = R(1);
+            if (!linear) {
+                const R lam = R(1) + strain, l3 = lam * lam * lam;
+                kap = div_r(sqrt_r(lam) * (R(1) + l3), fmadd(l3, lam, R(1)));
+            }
+            s = ks * kap * strain * rL;
+        }
+        se[e] = s;
+        R* q = fh + (cons ? 4 : 1) * e;
+        if (!do_b) {
+            for (int k = 0; k < (cons ? 4 : 1); ++k) q[k] = R(0);
+            return;
+        }
+        // normals of T1 = (A, B, C) and T2 = (D, C, B) (inward, unnormalised):
+        // N1 = (B - A) x (C - B), N2 = (C - B) x (C - D)
+        const double ux = bx - xs[3 * h.A], uy = by - xs[3 * h.A + 1], uz = bz - xs[3 * h.A + 2];
+        const double wx_ = cx_ - xs[3 * h.D], wy_ = cy_ - xs[3 * h.D + 1], wz_ = cz_ - xs[3 * h.D + 2];
+        const double n1x = fmadd(uy, dz, -(uz * dy)), n1y = fmadd(uz, dx, -(ux * dz)), n1z = fmadd(ux, dy, -(uy * dx));
+        const double n2x = fmadd(dy, wz_, -(dz * wy_)), n2y = fmadd(dz, wx_, -(dx * wz_)),
+                     n2z = fmadd(dx, wy_, -(dy * wx_));
+        // theta - pi = atan2((n1 x n2) . e, n1 . n2) for the unit vectors, where
+        // N1 x N2 = (C - B) ((B - A) . N2); the difference to theta0 - pi is the
+        // angle of the relative rotation, atan2(sin d, cos d), every term scaled
+        // by |N1| |N2| > 0
+        const double sn = L * fmadd(ux, n2x, fmadd(uy, n2y, uz * n2z));
+        const double cn = fmadd(n1x, n2x, fmadd(n1y, n2y, n1z * n2z));
+        const R dth = angle_of((R)fmadd(sn, cs.x, -(cn * cs.y)), (R)fmadd(cn, cs.x, sn * cs.y));
+        const R f = (R)kth * dth;
+        if (!cons) {
+            q[0] = f;
+        } else {
+            // gradient form: the wing factors w = c / h (c = hbar f, h = |N| / L
+            // the wing's distance from the edge line) and w times the position a
+            // of the wing's foot on the edge, B + a (C - B)
+            const R c = (R)gat(T->hbar, e) * f * (R)L;
+            const R wA = c * rsqrt_r((R)fmadd(n1x, n1x, fmadd(n1y, n1y, n1z * n1z)));
+            const R wD = c * rsqrt_r((R)fmadd(n2x, n2x, fmadd(n2y, n2y, n2z * n2z)));
+            const R aA = (R)(-fmadd(ux, dx, fmadd(uy, dy, uz * dz)) / L2);
+            const R aD = (R)((L2 - fmadd(wx_, dx, fmadd(wy_, dy, wz_ * dz))) / L2);
+            q[0] = wA;
+            q[1] = wD;
+            q[2] = aA * wA;
+            q[3] = aD * wD;
+        }
+    };
+    if (wave >= cw) {
+        S raw[VDEPTH][19];
+        int qv[VROUNDS];
+#pragma unroll
+        for (int k = 0; k < VROUNDS + VDEPTH - 1; ++k) {
+            if (k < VROUNDS && vt + k * vn < ncomp) {
+                qv[k] = qn[vt + k * vn];
+                ask(qv[k], raw[k % VDEPTH]);
+            }
+            const int d = k - (VDEPTH - 1);  // the round whose populations are taken now
+            if (d >= 0 && vt + d * vn < ncomp)
+                velocity(qv[d], raw[d % VDEPTH], uv[d][0], uv[d][1], uv[d][2]);
+        }
+    } else {
         // node 0 of the object: the apex of the signed tetrahedra in every launch
         const double r0x = PH == PH_PATCH ? stage(0) : xs[0], r0y = PH == PH_PATCH ? stage(1) : xs[1],
                      r0z = PH == PH_PATCH ? stage(2) : xs[2];
         const int t0 = PH == PH_SUMS ? (int)((long long)nt * slice / nsl) : 0;
         const int t1 = PH == PH_SUMS ? (int)((long long)nt * (slice + 1) / nsl) : nt;
-        for (int t = t0 + (int)threadIdx.x; t < t1; t += blockDim.x) {
-            const int4 q = load_quad<WIDE>(T->tri16, T->tri32, t);
-            const double S0 = gld(T->S0 + t);
-            const double ax = xs[3 * q.x], ay = xs[3 * q.x + 1], az = xs[3 * q.x + 2];
-            const double abx = xs[3 * q.y] - ax, aby = xs[3 * q.y + 1] - ay, abz = xs[3 * q.y + 2] - az;
-            const double acx = xs[3 * q.z] - ax, acy = xs[3 * q.z + 1] - ay, acz = xs[3 * q.z + 2] - az;
-            const double nx_ = fmadd(aby, acz, -(abz * acy));
-            const double ny_ = fmadd(abz, acx, -(abx * acz));
-            const double nz_ = fmadd(abx, acy, -(aby * acx));
-            const double n2 = fmadd(nx_, nx_, fmadd(ny_, ny_, nz_ * nz_));  // 4 S^2
-            const R rl = rsqrt_r((R)n2);
-            const R S = R(0.5) * (R)n2 * rl;
-            const R dS = div_r((R)fmadd(0.25, n2, -(S0 * S0)), S + (R)S0);
-            if (PH != PH_SUMS) {  // the sums launch keeps the sums only
-                tn[4 * t + 0] = (R)nx_ * rl;
-                tn[4 * t + 1] = (R)ny_ * rl;
-                tn[4 * t + 2] = (R)nz_ * rl;
-                tn[4 * t + 3] = S;
-                tr[t] = -kal * (R(2) * dS * rl);
+        const int ntc = (t1 - t0 + 63) >> 6;                            // waves of triangles,
+        const int nch = ntc + (PH == PH_SUMS ? 0 : (ne + 63) >> 6);     // and of edges after them
+        const double2* cs0 = T->cs0;
+        const double* kth = T->kth;
+        for (int ch = wave; ch < nch; ch += cw) {
+            if (ch < ntc) {
+                const int t = t0 + 64 * ch + lane;
+                if (t < t1) triangle(t, lists_of.triangle(t), r0x, r0y, r0z);
+            } else {
+                const int e = 64 * (ch - ntc) + lane;
+                if (e < ne) edge(e, lists_of.hinge(e), gat(cs0, e), gat(kth, e));
             }
-            sdarea += (double)dS;
-            // signed tetrahedron (node 0, a, b, c): a . N = -6 V for inward N
-            svol = fmadd(ax - r0x, nx_, fmadd(ay - r0y, ny_, fmadd(az - r0z, nz_, svol)));
         }
         svol *= -1.0 / 6.0;
     }
@@ -635,8 +762,8 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         dSg = lane_value(v, 15);
         Vol = lane_value(v, 31);
     };
+    __syncthreads();
     if (PH == PH_SUMS) {
-        __syncthreads();
         block_sums();
         if (tid == 0) {
             gst(part + 2 * slice, dSg);
@@ -644,74 +771,6 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         }
         return;  // the patch launch reads the slices' sums
     }
-
-    // 2. edges: stretching coefficient and bending magnitude of each hinge
-    const bool do_s = T->ks != 0.0, do_b = T->kb != 0.0;
-    for (int e = threadIdx.x; e < ne; e += blockDim.x) {
-        const int4 h = load_quad<WIDE>(T->hinge16, T->hinge32, e);  // (A, B, C, D): the edge is B -> C
-        const double L0 = gld(T->L0 + e);
-        const double bx = xs[3 * h.y], by = xs[3 * h.y + 1], bz = xs[3 * h.y + 2];
-        const double cx_ = xs[3 * h.z], cy_ = xs[3 * h.z + 1], cz_ = xs[3 * h.z + 2];
-        const double dx = cx_ - bx, dy = cy_ - by, dz = cz_ - bz;
-        const double L2 = fmadd(dx, dx, fmadd(dy, dy, dz * dz));
-        double L;
-        R rL;
-        length_of(L2, L, rL);
-        R s = R(0);
-        if (do_s) {
-            // strain (L - L0)/L0 = (L^2 - L0^2) / (L0 (L + L0)); neo-Hookean
-            // kappa = (lam^1/2 + lam^-5/2) / (lam + lam^-3)
-            //       = lam^1/2 (1 + lam^3) / (1 + lam^4)
-            const R strain = div_r((R)fmadd(-L0, L0, L2), (R)(L0 * (L + L0)));
-            R kap = R(1);
-            if (!T->linear) {
-                const R lam = R(1) + strain, l3 = lam * lam * lam;
-                kap = div_r(sqrt(lam) * (R(1) + l3), fmadd(l3, lam, R(1)));
-            }
-            s = (R)T->ks * kap * strain * rL;
-        }
-        se[e] = s;
-        R* q = fh + (cons ? 4 : 1) * e;
-        if (!do_b) {
-            for (int k = 0; k < (cons ? 4 : 1); ++k) q[k] = R(0);
-            continue;
-        }
-        // normals of T1 = (A, B, C) and T2 = (D, C, B) (inward, unnormalised):
-        // N1 = (B - A) x (C - B), N2 = (C - B) x (C - D)
-        const double ux = bx - xs[3 * h.x], uy = by - xs[3 * h.x + 1], uz = bz - xs[3 * h.x + 2];
-        const double wx_ = cx_ - xs[3 * h.w], wy_ = cy_ - xs[3 * h.w + 1], wz_ = cz_ - xs[3 * h.w + 2];
-        const double n1x = fmadd(uy, dz, -(uz * dy)), n1y = fmadd(uz, dx, -(ux * dz)), n1z = fmadd(ux, dy, -(uy * dx));
-        const double n2x = fmadd(dy, wz_, -(dz * wy_)), n2y = fmadd(dz, wx_, -(dx * wz_)),
-                     n2z = fmadd(dx, wy_, -(dy * wx_));
-        // theta - pi = atan2((n1 x n2) . e, n1 . n2) for the unit vectors, where
-        // N1 x N2 = (C - B) ((B - A) . N2); the difference to theta0 - pi is the
-        // angle of the relative rotation, atan2(sin d, cos d), every term scaled
-        // by |N1| |N2| > 0
-        const double sn = L * fmadd(ux, n2x, fmadd(uy, n2y, uz * n2z));
-        const double cn = fmadd(n1x, n2x, fmadd(n1y, n2y, n1z * n2z));
-        const double2 cs = gld(T->cs0 + e);  // cos, sin of theta0 - pi
-        const R dth = angle_of((R)fmadd(sn, cs.x, -(cn * cs.y)), (R)fmadd(cn, cs.x, sn * cs.y));
-        const R f = (R)gld(T->kth + e) * dth;
-        if (!cons) {
-            q[0] = f;
-        } else {
-            // gradient form: the wing factors w = c / h (c = hbar f, h = |N| / L
-            // the wing's distance from the edge line) and w times the position a
-            // of the wing's foot on the edge, B + a (C - B)
-            const R c = (R)gld(T->hbar + e) * f * (R)L;
-            const R wA = c * rsqrt_r((R)fmadd(n1x, n1x, fmadd(n1y, n1y, n1z * n1z)));
-            const R wD = c * rsqrt_r((R)fmadd(n2x, n2x, fmadd(n2y, n2y, n2z * n2z)));
-            const R aA = (R)(-fmadd(ux, dx, fmadd(uy, dy, uz * dz)) / L2);
-            const R aD = (R)((L2 - fmadd(wx_, dx, fmadd(wy_, dy, wz_ * dz))) / L2);
-            q[0] = wA;
-            q[1] = wD;
-            q[2] = aA * wA;
-            q[3] = aD * wD;
-        }
-    }
-    R u0x = 0, u0y = 0, u0z = 0;
-    if (mine) velocity(q0, raw0, u0x, u0y, u0z);
-    __syncthreads();
 
     if (PH == PH_ALL) {
         block_sums();
@@ -746,17 +805,17 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     // a wave's entries contiguous, and some 75 words.  With the shorter
     // arithmetic of div_r and its kin: launch of 500 spheres of 642 nodes, FP32,
     // 79.2 -> 72.4 us; FP64, 120 conservative ones 64.2 -> 55.8 us.)
-    typedef typename std::conditional<WIDE, RawCorner32, RawCorner16>::type Raw;
-    for (int i = threadIdx.x; i < nn; i += blockDim.x) {
+    typedef typename Lists<WIDE>::Raw Raw;
+    const int rmax = T->rmax;
+    for (int i = tid; i < nn; i += bd) {
         const double px = xs[3 * i], py = xs[3 * i + 1], pz = xs[3 * i + 2];
         R Fx = 0, Fy = 0, Fz = 0;
         auto corner = [&](const Raw& raw) {
 #pragma clang fp contract(off)
-            if (!raw.valid()) return;
-            const Corner c = raw.get();
+            const Corner c = Lists<WIDE>::corner(raw);
             const double ax = px - xs[3 * c.a], ay = py - xs[3 * c.a + 1], az = pz - xs[3 * c.a + 2];
             const double bx = px - xs[3 * c.b], by = py - xs[3 * c.b + 1], bz = pz - xs[3 * c.b + 2];
-            const R s = se[c.ea];
+            R s = se[c.ea];
             const R n0 = tn[4 * c.t], n1 = tn[4 * c.t + 1], n2 = tn[4 * c.t + 2], S = tn[4 * c.t + 3];
             // bending: wings along their triangle's normal, edge ends minus
             // half the sum ("Bending force"; conservative model: minus the wing
@@ -767,9 +826,9 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
             } else {
                 const R* qa = fh + 4 * c.ea;  // v is the edge's B where the triangle is its T1, else C
                 const R* qb = fh + 4 * c.eb;  // v is the edge's C where the triangle is its T1, else B
-                cn = fh[4 * c.o + ((c.fl & 4u) ? 1 : 0)];
-                cn -= (c.fl & 1u) ? qa[3] : qa[0] - qa[2];
-                cn -= (c.fl & 2u) ? qb[1] - qb[3] : qb[2];
+                cn = fh[4 * c.o + (c.t2o ? 1 : 0)];
+                cn -= c.t2a ? qa[3] : qa[0] - qa[2];
+                cn -= c.t2b ? qb[1] - qb[3] : qb[2];
             }
             // volume: -kv dV/V0 S n_out / 3
             cn = fmadd(-cv3, S, cn);
@@ -784,24 +843,37 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
                 w2 += fmadd(cx_, cx_, fmadd(cy_, cy_, cz_ * cz_)) + fmadd(dx, dx, fmadd(dy, dy, dz * dz));
                 w2 *= R(1) / R(3);
             }
-            const R ct = (tr[c.t] + cg) * rsqrt_r(w2);
+            R ct = (tr[c.t] + cg) * rsqrt_r(w2);
+            // a repeated corner adds nothing (selected, not skipped: without
+            // branches the corners' LDS reads overlap)
+            ct = c.valid ? ct : R(0);
+            cn = c.valid ? cn : R(0);
+            s = c.valid ? s : R(0);
             // F_v += ks kappa (L - L0)/L0 (x_a - x_v)/L  ("Stretching force")
             Fx = fmadd(ct, wx, fmadd(cn, n0, fmadd(-s, (R)ax, Fx)));
             Fy = fmadd(ct, wy, fmadd(cn, n1, fmadd(-s, (R)ay, Fy)));
             Fz = fmadd(ct, wz, fmadd(cn, n2, fmadd(-s, (R)az, Fz)));
         };
-        // the first six corners' entries are all in flight before the first is
-        // used (most nodes have five to seven)
-        Raw raw[6];
-        const int n6 = min(6, T->rmax);
+        if (CONS) {
+            // (with the conservative terms six corners side by side spill a
+            // hundred registers in the FP32 forms: one ahead instead)
+            Raw raw = lists_of.raw(0, i);
+#pragma unroll 1
+            for (int j = 0; j < rmax; ++j) {
+                const Raw cur = raw;
+                raw = lists_of.raw(min(j + 1, rmax - 1), i);
+                corner(cur);
+            }
+        } else {
+            // the first six corners' entries (most nodes have five to seven) are
+            // all in flight before the first is used, and the seventh's with them
+            Raw raw[7];
 #pragma unroll
-        for (int j = 0; j < 6; ++j) load_corner(T, min(j, n6 - 1), i, raw[j]);
+            for (int j = 0; j < 7; ++j) raw[j] = lists_of.raw(min(j, rmax - 1), i);
 #pragma unroll
-        for (int j = 0; j < 6; ++j)
-            if (j < n6) corner(raw[j]);
-        for (int j = 6; j < T->rmax; ++j) {
-            load_corner(T, j, i, raw[0]);
-            corner(raw[0]);
+            for (int j = 0; j < 6; ++j) corner(raw[j]);
+            if (rmax > 6) corner(raw[6]);
+            for (int j = 7; j < rmax; ++j) corner(lists_of.raw(j, i));
         }
 
         fs[3 * i] = Fx;
@@ -817,12 +889,12 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     R vx = 0, vy = 0, vz = 0;
     auto fetch = [&](int i) {
         const int v = node_of(i);
-        px = gld(O.X + 3 * v);
-        py = gld(O.X + 3 * v + 1);
-        pz = gld(O.X + 3 * v + 2);
-        vx = gld(O.V + 3 * v);
-        vy = gld(O.V + 3 * v + 1);
-        vz = gld(O.V + 3 * v + 2);
+        px = gat(O.X, 3 * v);
+        py = gat(O.X, 3 * v + 1);
+        pz = gat(O.X, 3 * v + 2);
+        vx = gat(O.V, 3 * v);
+        vy = gat(O.V, 3 * v + 1);
+        vz = gat(O.V, 3 * v + 2);
         if (O.F) {  // the half-step velocity, as staged
             vx = fmadd(gld(O.F + 3 * v), half_im, vx);
             vy = fmadd(gld(O.F + 3 * v + 1), half_im, vy);
@@ -836,12 +908,18 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     __syncthreads();
     if (compact) {
         for (int k = tid; k < AW * ncomp; k += bd) gacc[k] = A(0);
-        if (mine) {
-            ug[3 * tid] = u0x;
-            ug[3 * tid + 1] = u0y;
-            ug[3 * tid + 2] = u0z;
+        if (wave >= cw) {
+#pragma unroll
+            for (int k = 0; k < VROUNDS; ++k) {
+                const int c = vt + k * vn;
+                if (c < ncomp) {
+                    ug[3 * c] = uv[k][0];
+                    ug[3 * c + 1] = uv[k][1];
+                    ug[3 * c + 2] = uv[k][2];
+                }
+            }
         }
-        for (int c = tid + bd; c < ncomp; c += bd) {
+        for (int c = VROUNDS * vn + tid; c < ncomp; c += bd) {
             const int q = qn[c];
             S raw[19];
             ask(q, raw);

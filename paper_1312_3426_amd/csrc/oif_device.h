@@ -85,27 +85,26 @@ template <typename real>
 struct TmplDev {
     int nv, nt, ne;
     int linear;
-    // Index lists, in 16 bits where the mesh runs in LDS (node, triangle and
-    // edge numbers fit then; null when they do not) and in 32 bits for meshes
-    // in the global scratch.
-    const ushort4* tri16;     // [nt] (a, b, c, 0), inward
-    const int4* tri32;
-    const ushort4* hinge16;   // [ne] (A, B, C, D): T1 = (A, B, C) runs B -> C, T2 has wing D
-    const int4* hinge32;
+    // Records of the triangles, edges and corners, with node, triangle and
+    // edge numbers in 16 bits where the mesh runs in LDS (they fit then; null
+    // when they do not) and in 32 bits for meshes in the global scratch.
+    const uint4* tri16;       // [nt] a | b << 16, c, S0 (FP64: S - S0 cancels near the relaxed shape)
+    const int4* tri32;        // [nt] (a, b, c, 0), inward
+    const double* S0;         // [nt]
+    const uint4* edge16;      // [ne] A | B << 16, C | D << 16, L0 (FP64, as S0)
+    const int4* hinge32;      // [ne] (A, B, C, D): T1 = (A, B, C) runs B -> C, T2 has wing D
+    const double* L0;         // [ne]
     // Corners of each node: corner j of node v is entry j * rstride + v (so a
-    // wave reads 64 consecutive entries), j < rmax; a node with fewer corners
-    // has entries of all ones after them.  A corner is a triangle (v, a, b) in
-    // its order: a, b, the triangle t, and its edges ea = (v, a), eb = (b, v),
-    // o = (a, b), each with its top bit set where the triangle is the edge's T2.
-    const uint2* ring16;      // a | b << 16, t | ea << 16
-    const unsigned* ring16b;  // eb | o << 16
-    const int4* ring32;       // a, b, t, ea
-    const int2* ring32b;      // eb, o
+    // wave reads 64 consecutive entries), j < rmax (at least 6).  A corner is a
+    // triangle (v, a, b) in its order: a, b, the triangle t, and its edges
+    // ea = (v, a), eb = (b, v), o = (a, b), each with its top bit set where the
+    // triangle is the edge's T2.  A node with fewer corners repeats its first
+    // one with the validity word 0.
+    const uint4* ring16;      // a | b << 16, t | ea << 16, eb | o << 16, valid
+    const int4* ring32;       // [..][2]: (a, b, t, ea), (eb, o, valid, 0)
     int rstride, rmax;
-    const double* L0;      // [ne] (FP64: L - L0 cancels near the relaxed shape)
     const double* kth;     // [ne] kb / theta0, theta0 the relaxed inner dihedral angle
     const double2* cs0;    // [ne] cos and sin of theta0 - pi (FP64)
-    const double* S0;      // [nt] (FP64: S - S0 cancels near the relaxed shape)
     const double* hbar;    // [ne] mean relaxed wing height (conservative model)
     int conservative;      // force model: 0 = the paper's rules, 1 = conservative
     double Sg0, V0;

@@ -642,18 +642,15 @@ struct TArr {
     std::vector<double> hbar;       // [ne]
     // corners (TmplDev::ring32): [rmax][rstride]
     int rstride = 0, rmax = 0;
-    std::vector<int4> ring;
-    std::vector<int2> ringb;
+    std::vector<int4> ring;         // two per entry
     std::vector<int> order, slice_off;
-    // the same lists in 16 bits (empty when some number does not fit)
-    std::vector<ushort4> tri16, hv16;
-    std::vector<uint2> ring16;
-    std::vector<unsigned> ring16b;
+    // the same records in 16 bits (empty when some number does not fit)
+    std::vector<uint4> tri16, edge16, ring16;
 };
 
 // Corner of triangle t at position s3 in device form; nl, tl, el map node,
 // triangle and edge numbers (null: as they are).
-void corner_entry(const Template& T, int code, const int* nl, const int* tl, const int* el, int4& p, int2& q) {
+void corner_entry(const Template& T, int code, const int* nl, const int* tl, const int* el, int4* p) {
     const int t = code >> 2, s3 = code & 3;
     auto node = [&](int k) {
         const int v = T.tri[3 * t + (s3 + k) % 3];
@@ -663,39 +660,44 @@ void corner_entry(const Template& T, int code, const int* nl, const int* tl, con
         const int s = T.side[3 * t + (s3 + k) % 3], e = s < 0 ? ~s : s;
         return (int)((unsigned)(el ? el[e] : e) | (s < 0 ? 0x80000000u : 0u));
     };
-    p = make_int4(node(1), node(2), tl ? tl[t] : t, edge(0));
-    q = make_int2(edge(2), edge(1));
+    p[0] = make_int4(node(1), node(2), tl ? tl[t] : t, edge(0));
+    p[1] = make_int4(edge(2), edge(1), 1, 0);
 }
 
-// The 16-bit lists from the 32-bit ones.
+// The 16-bit records from the 32-bit ones.
 void narrow(TArr& A) {
-    auto h4 = [](const int4& v) { return make_ushort4((unsigned short)v.x, (unsigned short)v.y, (unsigned short)v.z, (unsigned short)v.w); };
+    auto two = [](int a, int b) { return (unsigned)a | (unsigned)b << 16; };
+    auto rec = [](unsigned a, unsigned b, double d) {
+        unsigned w[2];
+        std::memcpy(w, &d, 8);
+        return make_uint4(a, b, w[0], w[1]);
+    };
     if (A.nv > 0xffff) return;
-    for (const int4& v : A.tri) A.tri16.push_back(h4(v));
+    for (int t = 0; t < A.nt; ++t) A.tri16.push_back(rec(two(A.tri[t].x, A.tri[t].y), (unsigned)A.tri[t].z, A.S0[t]));
     if (A.nt > 0xffff || A.ne > 0x7fff) return;
-    for (const int4& v : A.hv) A.hv16.push_back(h4(v));
+    for (int e = 0; e < A.ne; ++e)
+        A.edge16.push_back(rec(two(A.hv[e].x, A.hv[e].y), two(A.hv[e].z, A.hv[e].w), A.L0[e]));
     auto e16 = [](int e) { return ((unsigned)e & 0x7fffu) | (e < 0 ? 0x8000u : 0u); };
-    for (size_t k = 0; k < A.ring.size(); ++k) {
-        const int4 p = A.ring[k];
-        const int2 q = A.ringb[k];
-        const bool none = p.x < 0;
-        A.ring16.push_back(none ? make_uint2(~0u, ~0u)
-                                : make_uint2((unsigned)p.x | (unsigned)p.y << 16, (unsigned)p.z | e16(p.w) << 16));
-        A.ring16b.push_back(none ? ~0u : e16(q.x) | e16(q.y) << 16);
+    for (size_t k = 0; k < A.ring.size(); k += 2) {
+        const int4 p = A.ring[k], q = A.ring[k + 1];
+        A.ring16.push_back(make_uint4(two(p.x, p.y), (unsigned)p.z | e16(p.w) << 16, e16(q.x) | e16(q.y) << 16, (unsigned)q.z));
     }
 }
 
-// Corners of the nodes whose triangles `corner(i)` lists, in wave-sized columns.
+// Corners of the nodes whose triangles `corners(i)` lists, in wave-sized columns.
 template <typename F, typename G>
 void fill_rings(TArr& A, int n, const F& corners, const G& entry) {
     A.rstride = (n + 63) & ~63;
-    A.rmax = 1;
+    A.rmax = 6;
     for (int i = 0; i < n; ++i) A.rmax = std::max(A.rmax, (int)corners(i).size());
-    A.ring.assign((size_t)A.rmax * A.rstride, make_int4(-1, -1, -1, -1));
-    A.ringb.assign(A.ring.size(), make_int2(-1, -1));
+    A.ring.assign(2 * (size_t)A.rmax * A.rstride, make_int4(0, 0, 0, 0));
     for (int i = 0; i < n; ++i) {
         const std::vector<int>& c = corners(i);
-        for (size_t j = 0; j < c.size(); ++j) entry(c[j], A.ring[j * A.rstride + i], A.ringb[j * A.rstride + i]);
+        for (int j = 0; j < A.rmax && !c.empty(); ++j) {
+            int4* p = &A.ring[2 * ((size_t)j * A.rstride + i)];
+            entry(c[j < (int)c.size() ? j : 0], p);
+            if (j >= (int)c.size()) p[1].z = 0;  // repeated, not valid
+        }
     }
 }
 
@@ -718,7 +720,7 @@ TArr template_arrays(const Template& T) {
         A.hv[e] = make_int4(T.hinge[e][0], T.hinge[e][1], T.hinge[e][2], T.hinge[e][3]);
     }
     fill_rings(A, T.nv, [&](int i) -> const std::vector<int>& { return T.corner[i]; },
-               [&](int code, int4& p, int2& q) { corner_entry(T, code, nullptr, nullptr, nullptr, p, q); });
+               [&](int code, int4* p) { corner_entry(T, code, nullptr, nullptr, nullptr, p); });
     A.order = T.order;
     A.slice_off = T.slice_off;
     narrow(A);
@@ -771,7 +773,7 @@ TArr patch_arrays(const Template& T, const TArr& A, int k) {
         P.hbar.push_back(A.hbar[e]);
     }
     fill_rings(P, np, [&](int i) -> const std::vector<int>& { return T.corner[P.order[i]]; },
-               [&](int code, int4& p, int2& q) { corner_entry(T, code, nl.data(), tl.data(), el.data(), p, q); });
+               [&](int code, int4* p) { corner_entry(T, code, nl.data(), tl.data(), el.data(), p); });
     P.slice_off = {0, np};
     narrow(P);
     return P;
@@ -783,9 +785,9 @@ size_t vbytes(const std::vector<V>& v) {
 }
 
 size_t tarr_bytes(const TArr& A) {
-    return vbytes(A.tri) + vbytes(A.hv) + vbytes(A.ring) + vbytes(A.ringb) + vbytes(A.tri16) + vbytes(A.hv16) +
-           vbytes(A.ring16) + vbytes(A.ring16b) + vbytes(A.L0) + vbytes(A.kth) + vbytes(A.cs0) + vbytes(A.S0) +
-           vbytes(A.hbar) + vbytes(A.order) + vbytes(A.slice_off);
+    return vbytes(A.tri) + vbytes(A.hv) + vbytes(A.ring) + vbytes(A.tri16) + vbytes(A.edge16) + vbytes(A.ring16) +
+           vbytes(A.L0) + vbytes(A.kth) + vbytes(A.cs0) + vbytes(A.S0) + vbytes(A.hbar) + vbytes(A.order) +
+           vbytes(A.slice_off);
 }
 
 // Copies A's arrays to host[..] and points D's arrays at dev[..] (the same
@@ -807,11 +809,9 @@ void tarr_place(const TArr& A, unsigned char* host, unsigned char* dev, TmplDev<
     D.tri32 = (const int4*)put(A.tri);
     D.hinge32 = (const int4*)put(A.hv);
     D.ring32 = (const int4*)put(A.ring);
-    D.ring32b = (const int2*)put(A.ringb);
-    D.tri16 = (const ushort4*)put(A.tri16);
-    D.hinge16 = (const ushort4*)put(A.hv16);
-    D.ring16 = (const uint2*)put(A.ring16);
-    D.ring16b = (const unsigned*)put(A.ring16b);
+    D.tri16 = (const uint4*)put(A.tri16);
+    D.edge16 = (const uint4*)put(A.edge16);
+    D.ring16 = (const uint4*)put(A.ring16);
     D.L0 = (const double*)put(A.L0);
     D.kth = (const double*)put(A.kth);
     D.cs0 = (const double2*)put(A.cs0);
