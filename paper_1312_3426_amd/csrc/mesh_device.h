@@ -262,6 +262,12 @@ struct Lists<true> {
     }
 };
 
+// Whether a stencil box of these extents has at most cap nodes (a runaway
+// mesh's extents reach 2e7, whose product leaves 64 bits).
+__device__ __forceinline__ bool box_fits(long long ex, long long ey, long long ez, int cap) {
+    return ex <= cap && ey <= cap && ez <= cap && ex * ey * ez <= cap;  // cap <= 10^6
+}
+
 // Stencil marking of one object for split stepping: every lattice node inside
 // the 2x2x2 stencil of a finite node position gets its bit in `touch`.  The
 // object's stencil box is marked in the bitmask `bits` ((ucap + 31)/32 words)
@@ -293,7 +299,7 @@ __device__ void mark_object(const double* pos, const int* order, int nv, const i
     if (bbox[3] < bbox[0]) return;  // no finite node (block-uniform)
     const long long exl = (long long)bbox[3] - ox + 2, eyl = (long long)bbox[4] - oy + 2,
                     ezl = (long long)bbox[5] - oz + 2;
-    if (exl * eyl * ezl <= (long long)ucap) {
+    if (box_fits(exl, eyl, ezl, ucap)) {
         const int ex = (int)exl, exy = (int)(exl * eyl), vol = (int)(exl * eyl * ezl);
         for (int k = threadIdx.x; k < (vol + 31) / 32; k += blockDim.x) bits[k] = 0u;
         __syncthreads();
@@ -495,11 +501,13 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
                   hz = ~__builtin_amdgcn_readlane(v1, 31);
         if (hx >= ox) {  // some finite node
             const long long exl = (long long)hx - ox + 2, eyl = (long long)hy - oy + 2, ezl = (long long)hz - oz + 2;
-            grid = exl * eyl * ezl <= (long long)ucap;
-            ex = (int)exl;
-            ey = (int)eyl;
-            ez = (int)ezl;
-            exy = (int)(exl * eyl);
+            grid = box_fits(exl, eyl, ezl, ucap);
+            if (grid) {
+                ex = (int)exl;
+                ey = (int)eyl;
+                ez = (int)ezl;
+                exy = ex * ey;
+            }
         }
     }
     if (grid) {

@@ -65,3 +65,35 @@ def test_odd_meshes_vs_oracle(mesh, prec, model):
         say(f"   {block} threads: {fmt(res)}")
         assert all(v[3] for v in res.values()), fmt(res)
     ctx.close()
+
+
+@pytest.mark.parametrize("overlap", [False, True])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_runaway_mesh_takes_the_corner_path(prec, overlap):
+    """A mesh spread over 2.4e6 lattice units per axis: the node count of its
+    stencil box leaves 63 bits, and it must not pass for a small box.  Without
+    moduli and friction the nodes fly straight and leave the fluid alone, so
+    positions are exact and the fluid equals a box without cells."""
+    from paper_1312_3426_amd import oif
+
+    say(f"[membrane edges] runaway mesh {prec} overlap={overlap}")
+    nodes, tris = synth.tetrahedron(5.0)
+    box = synth.Box(24, 20, 22, templates=[synth.Template(nodes, tris)], friction=0.0,
+                    objects=[synth.ObjectSpec(0, np.array([11.0, 9.0, 10.0]))])
+    ctx = oif.Context.from_box(box, precision=prec)
+    ctx.set_overlap(overlap)
+    X0, _ = ctx.read_mesh()
+    V = 1.2e6 * np.sign(nodes)  # extents of 2.4e6 after one step, 1.4e19 box nodes
+    assert 2 ** 63 < int(2.4e6) ** 3 < 2 ** 64
+    ctx.write_mesh(-1, X0, V)
+    ctx.step(1)
+    ctx.step(1)
+    X, V1 = ctx.read_mesh()
+    u = ctx.read_velocity()
+    ctx.close()
+    box.objects = []
+    plain = oif.Context.from_box(box, precision=prec)
+    plain.step(2)
+    assert np.array_equal(V1, V) and np.array_equal(X, (X0 + V) + V)
+    assert np.array_equal(u, plain.read_velocity())
+    plain.close()
