@@ -387,7 +387,8 @@ int oif_set_overlap(oif_ctx* ctx, int on);
  * 64 in [64, 1024] (one workgroup per object: block sizes that let two objects
  * share a compute unit matter more than powers of two); xcd_remap 0/1 maps
  * consecutive lattice blocks to the same XCD.  Values < 0 keep the current
- * setting. */
+ * setting; before mesh_block is set, each membrane launch takes its size from
+ * its meshes and their number.  The results do not depend on any of them. */
 int oif_set_launch(oif_ctx* ctx, int lb_block, int mesh_block, int xcd_remap);
 
 /* Cache policy of the lattice kernel's population reads (the stored

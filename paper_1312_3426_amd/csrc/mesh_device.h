@@ -379,6 +379,8 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     R* tr = (R*)(base + lay.tr);
     R* se = (R*)(base + lay.se);
     R* fh = (R*)(base + lay.fh);
+    // area and volume sums of each 64 triangles
+    double* sums = PH == PH_SUMS ? (double*)(smem + align16((size_t)nv * 3 * sizeof(double))) : (double*)(base + lay.sums);
     // coupling part: over the forces phase's arrays, alone in LDS (CPL), or
     // beside them in the scratch
     unsigned char* cbase = USE_LDS || CPL ? smem : O.scratch + lay.forces;
@@ -428,7 +430,6 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     A* gacc = (A*)(cbase + lay.gacc);
     __shared__ int bbox[6];             // of mark_object
     __shared__ int wbox[6][16];         // stencil bounds per wave: low corners, complements of the high ones
-    __shared__ double red[2][16];       // area and volume sums per wave
     const int tid = threadIdx.x, bd = blockDim.x, lane = tid & 63, nwave = (bd + 63) >> 6;
     unsigned flags = 0;
 
@@ -637,8 +638,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     const bool do_s = T->ks != 0.0, do_b = T->kb != 0.0, linear = T->linear != 0;
     // (S - S0 is formed as (S^2 - S0^2)/(S + S0): the cancelling difference in
     // FP64 multiply-adds, the square root and division in the arithmetic type)
-    double sdarea = 0.0, svol = 0.0;
-    auto triangle = [&](int t, const TriRec& q, double r0x, double r0y, double r0z) {
+    auto triangle = [&](int t, const TriRec& q, double r0x, double r0y, double r0z, double& sdarea, double& svol) {
 #pragma clang fp contract(off)
         const double ax = xs[3 * q.a], ay = xs[3 * q.a + 1], az = xs[3 * q.a + 2];
         const double abx = xs[3 * q.b] - ax, aby = xs[3 * q.b + 1] - ay, abz = xs[3 * q.b + 2] - az;
@@ -657,9 +657,9 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
             tn[4 * t + 3] = S;
             tr[t] = -kal * (R(2) * dS * rl);
         }
-        sdarea += (double)dS;
+        sdarea = (double)dS;
         // signed tetrahedron (node 0, a, b, c): a . N = -6 V for inward N
-        svol = fmadd(ax - r0x, nx_, fmadd(ay - r0y, ny_, fmadd(az - r0z, nz_, svol)));
+        svol = fmadd(ax - r0x, nx_, fmadd(ay - r0y, ny_, (az - r0z) * nz_));
     };
     // stretching coefficient and bending magnitude of a hinge
     auto edge = [&](int e, const EdgeRec& h, const double2& cs, double kth) {
@@ -748,31 +748,38 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         for (int ch = wave; ch < nch; ch += cw) {
             if (ch < ntc) {
                 const int t = t0 + 64 * ch + lane;
-                if (t < t1) triangle(t, lists_of.triangle(t), r0x, r0y, r0z);
+                double sdarea = 0.0, svol = 0.0;
+                if (t < t1) triangle(t, lists_of.triangle(t), r0x, r0y, r0z, sdarea, svol);
+                if (PH != PH_PATCH) {
+                    sdarea = wave_sum(sdarea);
+                    svol = wave_sum(svol);
+                    if (lane == 63) {
+                        sums[2 * ch] = sdarea;
+                        sums[2 * ch + 1] = svol;
+                    }
+                }
             } else {
                 const int e = 64 * (ch - ntc) + lane;
                 if (e < ne) edge(e, lists_of.hinge(e), gat(cs0, e), gat(kth, e));
             }
         }
-        svol *= -1.0 / 6.0;
     }
-    // the waves' area and volume sums; added after the next barrier
-    if (PH != PH_PATCH) {
-        const double s0 = wave_sum(sdarea), s1 = wave_sum(svol);
-        if (lane == 63) {
-            red[0][tid >> 6] = s0;
-            red[1][tid >> 6] = s1;
-        }
-    }
+    // The object's area and volume: each 64 triangles' sums are taken in the
+    // lanes of the wave that computed them and added here in an order of their
+    // own, so that the bits do not depend on the number of threads.
     double dSg, Vol;  // Sg - Sg0, volume
-    auto block_sums = [&]() {
-        const double v = row_sum(lane < 32 && (lane & 15) < nwave ? red[(lane >> 4) & 1][lane & 15] : 0.0);
-        dSg = lane_value(v, 15);
-        Vol = lane_value(v, 31);
+    auto block_sums = [&](int n) {
+        double s0 = 0.0, s1 = 0.0;
+        for (int k = lane; k < n; k += 64) {
+            s0 += sums[2 * k];
+            s1 += sums[2 * k + 1];
+        }
+        dSg = lane_value(wave_sum(s0), 63);
+        Vol = lane_value(wave_sum(s1), 63) * (-1.0 / 6.0);
     };
     __syncthreads();
     if (PH == PH_SUMS) {
-        block_sums();
+        block_sums(((int)((long long)nt * (slice + 1) / nsl) - (int)((long long)nt * slice / nsl) + 63) >> 6);
         if (tid == 0) {
             gst(part + 2 * slice, dSg);
             gst(part + 2 * slice + 1, Vol);
@@ -781,7 +788,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     }
 
     if (PH == PH_ALL) {
-        block_sums();
+        block_sums((nt + 63) >> 6);
     } else {
         // the slices' sums, added in slice order (the same bits in every
         // workgroup of the object)

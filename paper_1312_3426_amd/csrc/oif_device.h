@@ -135,6 +135,7 @@ struct TmplDev {
 //                  factors w = c/h_A, c/h_D and a_A w_A, a_D w_D, a the
 //                  feet's positions on the edge)
 //             fs   elastic force per node, R [nv][3]
+//             sums area and volume sums of each 64 triangles, FP64 [..][2]
 //   coupling: gacc summed reaction force at the touched lattice nodes, 8-byte
 //                  accumulators [ccap][3] (FP64 form [ccap][6])
 //             ug   fluid velocity there, R [ccap][3]
@@ -146,7 +147,7 @@ struct TmplDev {
 // fs (the positions are read from HBM again after the gather).  A mesh in the
 // global scratch has both parts side by side, or the coupling part in LDS.
 struct MeshLayout {
-    size_t xs, tn, tr, se, fh, fs, forces;        // offsets and size of the forces part
+    size_t xs, tn, tr, se, fh, fs, sums, forces;  // offsets and size of the forces part
     size_t gacc, ug, need, pw, qn, coupling;      // of the coupling part (in LDS mode from the same base)
     size_t nwords, total;
 };
@@ -161,31 +162,38 @@ __host__ __device__ inline MeshLayout mesh_layout(size_t r, int nv, int nt, int 
     L.se = align16(L.tr + (size_t)nt * r);
     L.fh = align16(L.se + (size_t)ne * r);
     const size_t end = align16(L.fh + (size_t)ne * r * (cons ? 4 : 1));
-    const size_t fsb = (size_t)nv * 3 * r, bits = L.nwords * 4;
+    const size_t fsb = (size_t)nv * 3 * r, bits = L.nwords * 4, sumb = (((size_t)nt + 63) / 64) * 16;
     L.gacc = 0;
     L.ug = (size_t)ccap * (r == 8 ? 6 : 3) * 8;
     const size_t uend = align16(L.ug + (size_t)ccap * 3 * r);
     if (lds) {
         L.fs = end > uend ? end : uend;
         L.need = L.fs;
-        L.pw = align16(L.fs + (fsb > bits ? fsb : bits));
+        L.sums = align16(L.fs + (fsb > bits ? fsb : bits));
+        L.pw = L.sums + sumb;
     } else {
         L.fs = end;
+        L.sums = align16(L.fs + fsb);
         L.need = uend;
         L.pw = align16(L.need + bits);
     }
-    L.forces = align16(L.fs + fsb);
+    L.forces = L.sums + sumb;
     L.qn = L.pw + L.nwords * 8;
     L.coupling = align16(L.qn + (size_t)ccap * 4);
     L.total = lds ? L.coupling : L.forces + L.coupling;
     return L;
 }
 
+// LDS of the sums launch of a split mesh.
+__host__ __device__ inline size_t sums_lds_bytes(int nv, int nt) {
+    return align16((size_t)nv * 3 * sizeof(double)) + (((size_t)nt + 63) / 64) * 16;
+}
+
 // Split launches (meshes too large for LDS whose positions fit there): the
 // phase a membrane launch runs (all of it, or one of the two split launches)
 enum { PH_ALL = 0, PH_SUMS = 1, PH_PATCH = 2 };
 // LDS of the split launches: the sums launch holds the object's positions
-// (FP64 [nv][3]); the patch launch the mesh layout of the patch's
+// (FP64 [nv][3]) and the sums of each 64 triangles of its slice; the patch launch the mesh layout of the patch's
 // sub-template.  The object's scratch: its mesh layout (both parts), then the
 // area and volume sums of each slice (double [nslice][2]).
 __host__ __device__ inline size_t split_part_offset(const MeshLayout& L) { return L.total; }

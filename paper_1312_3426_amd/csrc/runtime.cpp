@@ -415,7 +415,9 @@ struct oif_ctx {
     int any_conservative = 0;   // some template uses the conservative force model
 
     // launch configuration
-    int lb_block = 256, mesh_block = 256, remap = 1;
+    int lb_block = 256, remap = 1;
+    int mesh_block = 0;  // threads of a membrane workgroup; 0: by the rule of membrane_block per launch
+    int n_cu = 256;
     int lb_nt = 0;  // population reads of the lattice kernel non-temporal
     int graph_steps = 0;
     hipGraphExec_t gexec = nullptr;
@@ -466,7 +468,7 @@ struct oif_batch {
     size_t lds_need = 0;
     size_t cpl_need = 0;
     int any_conservative = 0;
-    int lb_block = 256, mesh_block = 256, remap = 1;
+    int lb_block = 256, mesh_block = 0, remap = 1;
     int lb_nt = 0;
     int graph_steps = 0;
     hipGraphExec_t gexec = nullptr;
@@ -843,7 +845,7 @@ void tmpl_scalars(const Template& T, TmplDev<real>& D) {
 // template has a single slice.
 size_t split_need_bytes(int precision, const Template& T) {
     if (T.nslice <= 1 || T.pnv.empty()) return SIZE_MAX;
-    size_t need = align16((size_t)T.nv * 3 * sizeof(double));
+    size_t need = sums_lds_bytes(T.nv, T.nt / T.nslice + 1);
     for (int k = 0; k < T.nslice; ++k)
         need = std::max(need, mesh_lds_bytes(precision, T.pnv[k], T.pnt[k], T.pne[k], T.ucap, T.ccap,
                                              tmpl_conservative(T)));
@@ -1077,13 +1079,40 @@ inline void rec(hipEvent_t e, hipStream_t s) {
     if (e) (void)hipEventRecord(e, s);
 }
 
+// Threads of a membrane workgroup when none are set: the waves a compute unit
+// holds of this kernel (24 with its 80 registers, 16 in the FP64 form) shared
+// among the workgroups it gets, between 512 and 1024 threads.  It gets as many
+// as its LDS holds, or fewer when the launch has fewer.  Measured (us, FP32
+// unless said): 1 sphere of 642 nodes 1024 threads 23.3, 768 24.0, 256 36.2; 200
+// of them 28.2, 29.3, 42.4; 2000 (two to a unit) 768 183.5, 512 197.8, 1024
+// 225.6, 256 236.8; 2000 cells of 393 (three) 512 129.1, 768 138.7, 256 151.9;
+// FP64 500 spheres of 642 (one) 1024 76.5, 512 88.6; 500 cells of 393 (two) 512
+// 47.4, 768 56.4.  Below 512 the phases of a small mesh get longer than the
+// extra workgroups gain (2000 spheres of 162 nodes: 256 123.8, 512 127.4; FP64
+// 213, 190).
+int membrane_block(int set, int precision, size_t lds_bytes, int nwg, int n_cu) {
+    if (set > 0) return set;
+    const int waves = precision == OIF_PREC_FP64 ? 16 : 24;
+    const int fit = lds_bytes ? std::max(1, (int)(163840 / (lds_bytes + 1024))) : waves;
+    const int per_cu = std::max(1, std::min(fit, (nwg + n_cu - 1) / n_cu));
+    return 64 * std::min(16, std::max(8, waves / per_cu));
+}
+
+// The membrane workgroup size of the context's first launch group.
+int first_membrane_block(const oif_ctx* c) {
+    if (c->n_lds_obj || (!c->n_split_obj && !c->n_cpl_obj))
+        return membrane_block(c->mesh_block, c->d.precision, c->lds_need, c->n_lds_obj, c->n_cu);
+    return c->n_split_obj ? membrane_block(c->mesh_block, c->d.precision, c->split_need, c->n_split_work, c->n_cu)
+                          : membrane_block(c->mesh_block, c->d.precision, c->cpl_need, c->n_cpl_obj, c->n_cu);
+}
+
 int enqueue_mesh(oif_ctx* c, int par, hipStream_t s, int mark_next) {
     const size_t osz = objdev_size(c->d.precision);
     if (c->rep_on)
         HIPCALL(c, launch_repulsion(c->rep_h, (const RepDev*)c->rep_desc.p, c->obj_dev.p, (int)c->obj.size(),
                                     c->d.precision, s));
     MeshLaunch ml{};
-    ml.block = c->mesh_block;
+    auto block = [&](size_t lds, int nwg) { return membrane_block(c->mesh_block, c->d.precision, lds, nwg, c->n_cu); };
     ml.parity = par;
     ml.mark_next = mark_next;
     ml.conservative = c->any_conservative;
@@ -1094,6 +1123,7 @@ int enqueue_mesh(oif_ctx* c, int par, hipStream_t s, int mark_next) {
         ml.objs = c->obj_dev.p;
         ml.nobj = c->n_lds_obj;
         ml.lds_bytes = c->lds_need;
+        ml.block = block(ml.lds_bytes, ml.nobj);
         HIPCALL(c, launch_mesh(ml));
     }
     if (c->n_split_obj > 0) {
@@ -1104,6 +1134,7 @@ int enqueue_mesh(oif_ctx* c, int par, hipStream_t s, int mark_next) {
         sl.work = (const int2*)c->split_work.p;
         sl.nwork = c->n_split_work;
         sl.split_lds = c->split_need;
+        sl.block = block(sl.split_lds, sl.nwork);
         HIPCALL(c, launch_mesh(sl));
     }
     if (c->n_cpl_obj > 0) {
@@ -1111,6 +1142,7 @@ int enqueue_mesh(oif_ctx* c, int par, hipStream_t s, int mark_next) {
         ml.nobj = c->n_cpl_obj;
         ml.lds_bytes = 0;
         ml.cpl_lds_bytes = c->cpl_need;
+        ml.block = block(ml.cpl_lds_bytes, ml.nobj);
         HIPCALL(c, launch_mesh(ml));
     }
     const int done = c->n_lds_obj + c->n_split_obj + c->n_cpl_obj;
@@ -1119,6 +1151,7 @@ int enqueue_mesh(oif_ctx* c, int par, hipStream_t s, int mark_next) {
         ml.nobj = (int)c->obj.size() - done;
         ml.lds_bytes = 0;
         ml.cpl_lds_bytes = 0;
+        ml.block = block(0, ml.nobj);
         HIPCALL(c, launch_mesh(ml));
     }
     return OIF_OK;
@@ -1332,7 +1365,8 @@ int oif_create(const oif_lattice_desc* desc, oif_ctx** out) {
     // non-temporal population reads pay while the two buffers are not much
     // larger than the last-level cache (the autotuner measures both)
     c->lb_nt = 2 * pop_bytes(c.get()) <= ((size_t)1 << 30) ? 1 : 0;
-    int lds = 0;
+    int lds = 0, ncu = 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, d.device) == hipSuccess && ncu > 0) c->n_cu = ncu;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, d.device) == hipSuccess && lds > 0)
         c->max_lds = (size_t)lds;
     // dynamic LDS budget of the membrane kernel: the device's per-workgroup
@@ -2182,7 +2216,7 @@ int oif_info(oif_ctx* c, oif_info_t* info) {
         bytes += (long long)b->n;
     info->device_bytes = bytes;
     info->lb_block = c->lb_block;
-    info->mesh_block = c->mesh_block;
+    info->mesh_block = first_membrane_block(c);
     info->xcd_remap = c->remap;
     info->graph_steps = c->graph_steps;
     info->max_lds = (long long)c->max_lds;
@@ -2427,7 +2461,7 @@ extern "C" int oif_autotune(oif_ctx* c, const char* cache_path) {
     c->overlap = 0;  // time each kernel alone
     const int reps = 6;  // even: parity is unchanged after each trial
     double best_lb = 1e300, best_mesh = 1e300;
-    best[0] = c->lb_block; best[1] = c->mesh_block; best[2] = c->remap; best[3] = c->lb_nt;
+    best[0] = c->lb_block; best[1] = first_membrane_block(c); best[2] = c->remap; best[3] = c->lb_nt;
     best[4] = c->box.g_by_mesh;
     for (int nt : {0, 1})
         for (int lb : {128, 256, 512, 1024})
@@ -2494,6 +2528,9 @@ void bdrop_graph(oif_batch* b) {
     b->gexec = nullptr;
     b->g_len = 0;
 }
+
+// threads of the persistent form's workgroups (membrane and lattice tasks)
+int persistent_block(const oif_batch* b) { return b->mesh_block > 0 ? b->mesh_block : 256; }
 
 int batch_build(oif_batch* b) {
     for (oif_ctx* c : b->ctx) {
@@ -2624,7 +2661,7 @@ int batch_build(oif_batch* b) {
         std::stable_sort(bo.begin(), bo.end(), [&](int a, int c) {
             return bmax[a] != bmax[c] ? bmax[a] < bmax[c] : bn[a] < bn[c];
         });
-        const int block = b->mesh_block;
+        const int block = persistent_block(b);
         b->p_lds = std::max(b->n_lds_obj ? b->lds_need : 0, b->p_cpl_need);
         int per_cu = 0, dev = 0, ncu = 0;
         BHIP(b, hipGetDevice(&dev));
@@ -2692,7 +2729,7 @@ int batch_enqueue(oif_batch* b, int n, int parity0, hipStream_t s, std::vector<h
                 BHIP(b, launch_repulsion(c->rep_h, (const RepDev*)c->rep_desc.p, c->obj_dev.p,
                                          (int)c->obj.size(), c->d.precision, s));
         if (b->persistent) {  // the membranes and the lattice of every box in one launch
-            BatchLaunch bl{(const BatchSched*)b->sched_dev.p, b->p_grid, b->mesh_block, b->p_lds, par,
+            BatchLaunch bl{(const BatchSched*)b->sched_dev.p, b->p_grid, persistent_block(b), b->p_lds, par,
                            b->precision, b->lb_nt, s};
             BHIP(b, launch_batch(bl));
             if (ev) {
@@ -2703,7 +2740,8 @@ int batch_enqueue(oif_batch* b, int n, int parity0, hipStream_t s, std::vector<h
             continue;
         }
         MeshLaunch ml{};
-        ml.block = b->mesh_block;
+        const int n_cu = b->ctx[0]->n_cu;
+        auto block = [&](size_t lds, int nwg) { return membrane_block(b->mesh_block, b->precision, lds, nwg, n_cu); };
         ml.parity = par;
         ml.precision = b->precision;
         ml.conservative = b->any_conservative;
@@ -2713,6 +2751,7 @@ int batch_enqueue(oif_batch* b, int n, int parity0, hipStream_t s, std::vector<h
             ml.objs = b->obj_dev.p;
             ml.nobj = b->n_lds_obj;
             ml.lds_bytes = b->lds_need;
+            ml.block = block(ml.lds_bytes, ml.nobj);
             BHIP(b, launch_mesh(ml));
         }
         if (b->n_split_obj > 0) {
@@ -2723,6 +2762,7 @@ int batch_enqueue(oif_batch* b, int n, int parity0, hipStream_t s, std::vector<h
             sl.work = (const int2*)b->split_work.p;
             sl.nwork = b->n_split_work;
             sl.split_lds = b->split_need;
+            sl.block = block(sl.split_lds, sl.nwork);
             BHIP(b, launch_mesh(sl));
         }
         if (b->n_cpl_obj > 0) {
@@ -2730,6 +2770,7 @@ int batch_enqueue(oif_batch* b, int n, int parity0, hipStream_t s, std::vector<h
             ml.nobj = b->n_cpl_obj;
             ml.lds_bytes = 0;
             ml.cpl_lds_bytes = b->cpl_need;
+            ml.block = block(ml.cpl_lds_bytes, ml.nobj);
             BHIP(b, launch_mesh(ml));
         }
         const int done = b->n_lds_obj + b->n_split_obj + b->n_cpl_obj;
@@ -2738,6 +2779,7 @@ int batch_enqueue(oif_batch* b, int n, int parity0, hipStream_t s, std::vector<h
             ml.nobj = b->nobj - done;
             ml.lds_bytes = 0;
             ml.cpl_lds_bytes = 0;
+            ml.block = block(0, ml.nobj);
             BHIP(b, launch_mesh(ml));
         }
         if (ev) (void)hipEventRecord((*ev)[3 * k + 1], s);
@@ -2940,7 +2982,7 @@ int oif_batch_autotune(oif_batch* b, const char* cache_path) {
         M += c->M;
     }
     const std::string key = tune_key(b->precision, dims, nobj, M);
-    int best[5] = {b->lb_block, b->mesh_block, b->remap, b->lb_nt, 0};
+    int best[5] = {b->lb_block, b->mesh_block > 0 ? b->mesh_block : 768, b->remap, b->lb_nt, 0};
     if (cache_lookup(cache_path, key, best)) {
         const int rc = oif_batch_set_launch(b, best[0], best[1], best[2]);
         return rc ? rc : oif_batch_set_lb_loads(b, best[3]);

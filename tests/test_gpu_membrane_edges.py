@@ -97,3 +97,28 @@ def test_runaway_mesh_takes_the_corner_path(prec, overlap):
     assert np.array_equal(V1, V) and np.array_equal(X, (X0 + V) + V)
     assert np.array_equal(u, plain.read_velocity())
     plain.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16"])
+def test_membrane_block_does_not_change_the_bits(prec):
+    """The default workgroup size and set ones from one wave on (one, two and
+    more waves fetch populations, or none), meshes in LDS and split ones: the
+    same bits after five steps."""
+    from paper_1312_3426_amd import oif
+
+    say(f"[membrane edges] block sizes {prec}")
+    box = synth.config_batch()[1]
+    assert {o.tid for o in box.objects} == {0, 1, 2}
+    got = []
+    for block in (None, 64, 128, 192, 448, 768, 1024):
+        c = oif.Context.from_box(box, precision=prec)
+        rng = np.random.default_rng(3)
+        X, _ = c.read_mesh()
+        c.write_mesh(-1, X + 0.01 * rng.standard_normal(X.shape), 1e-3 * rng.standard_normal(X.shape))
+        if block:
+            c.set_launch(-1, block, -1)
+        c.step(5)
+        got.append((*c.read_mesh(), c.read_velocity()))
+        c.close()
+    for g in got[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(g, got[0]))
