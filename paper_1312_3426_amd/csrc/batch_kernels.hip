@@ -50,7 +50,7 @@ __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirs
 // space; a new field of ObjDev must be added here as well).
 template <typename R>
 __device__ __forceinline__ ObjDev<R> load_obj(cptr<ObjDev<R>> p) {
-    static_assert(sizeof(ObjDev<R>) == (sizeof(R) == 8 ? 128 : 112), "ObjDev changed: update load_obj");
+    static_assert(sizeof(ObjDev<R>) == (sizeof(R) == 8 ? 136 : 120), "ObjDev changed: update load_obj");
     ObjDev<R> o;
     o.t = p->t;
     o.box = p->box;
@@ -65,14 +65,16 @@ __device__ __forceinline__ ObjDev<R> load_obj(cptr<ObjDev<R>> p) {
     for (int k = 0; k < 3; ++k) o.fext[k] = p->fext[k];
     o.mass = p->mass;
     o.scratch = p->scratch;
+    o.fel = p->fel;
     o.qsave = p->qsave;
     return o;
 }
 
 template <int P, bool USE_LDS, bool CPL>
-__device__ __noinline__ void mesh_task(const ObjDev<typename Prec<P>::R>* O, unsigned char* smem, int parity) {
+__device__ __noinline__ void mesh_task(const ObjDev<typename Prec<P>::R>* O, unsigned char* smem, MeshShared* sh,
+                                       int parity) {
     const ObjDev<typename Prec<P>::R> o = load_obj(uniform(O));
-    mesh_object<P, USE_LDS, true, CPL>(o, smem, uniform(parity), 0);
+    mesh_object<P, USE_LDS, true, CPL>(o, smem, *sh, uniform(parity), 0);
 }
 template <int P, bool NT>
 __device__ __noinline__ void lb_task(const BoxDev* B, int blk, int nblk, int parity) {
@@ -90,6 +92,7 @@ batch_kernel(const BatchSched* __restrict__ S, int parity) {
     typedef typename Prec<P>::R R;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int ticket;
+    __shared__ MeshShared sh;  // one for the three task bodies
     const int nbox = S->nbox, nmesh = S->nmesh, ntasks = S->ntasks;
     // this step's counters: next ticket, workgroups done, wait-limit flag,
     // then finished membrane tasks per box (one set per step parity; the set
@@ -122,9 +125,9 @@ batch_kernel(const BatchSched* __restrict__ S, int parity) {
         if (t < nmesh) {
             const ObjDev<R>* O = (const ObjDev<R>*)S->objs + t;
             const int g = __builtin_amdgcn_readfirstlane(S->group[t]);
-            if (g == 0) mesh_task<P, true, false>(O, smem, parity);
-            else if (g == 1) mesh_task<P, false, true>(O, smem, parity);
-            else mesh_task<P, false, false>(O, smem, parity);
+            if (g == 0) mesh_task<P, true, false>(O, smem, &sh, parity);
+            else if (g == 1) mesh_task<P, false, true>(O, smem, &sh, parity);
+            else mesh_task<P, false, false>(O, smem, &sh, parity);
             __syncthreads();  // all threads' spreading is done before thread 0 counts the task
             done_box = __builtin_amdgcn_readfirstlane(S->obj_box[t]);
         } else {

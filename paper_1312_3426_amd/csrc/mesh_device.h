@@ -337,6 +337,12 @@ __device__ void mark_object(const double* pos, const int* order, int nv, const i
     }
 }
 
+// The workgroup's fixed LDS besides its dynamic one.
+struct MeshShared {
+    int bbox[6];      // of mark_object
+    int wbox[6][16];  // stencil bounds per wave: low corners, complements of the high ones
+};
+
 // CONS: some object of the launch may use the conservative force model (each
 // object's template says whether it does); without it that code is left out.
 // CPL (meshes too large for LDS only): the coupling area alone sits in LDS, so
@@ -356,8 +362,8 @@ __device__ void mark_object(const double* pos, const int* order, int nv, const i
 // The membrane forces, coupling and update of object O by the whole
 // workgroup; smem is the workgroup's dynamic LDS.
 template <int P, bool USE_LDS, bool CONS, bool CPL, int PH = PH_ALL, bool LISTS = true>
-__device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O, unsigned char* smem, int parity,
-                                            int mark_next, int slice = 0) {
+__device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O, unsigned char* smem, MeshShared& sh,
+                                            int parity, int mark_next, int slice = 0) {
 #pragma clang fp contract(off)
     constexpr bool SPLIT = PH != PH_ALL;
     static_assert(PH != PH_SUMS || (!USE_LDS && CPL), "sums launch: positions alone in LDS");
@@ -374,7 +380,6 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     unsigned char* base = USE_LDS ? smem : O.scratch;
     // node positions (forces phase); the sums launch keeps them alone in LDS
     double* xs = PH == PH_SUMS ? (double*)smem : (double*)(base + lay.xs);
-    R* fs = (R*)(base + lay.fs);
     R* tn = (R*)(base + lay.tn);
     R* tr = (R*)(base + lay.tr);
     R* se = (R*)(base + lay.se);
@@ -428,8 +433,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     typedef typename Acc<P>::T A;
     constexpr int AW = 3 * Acc<P>::WC;  // accumulator words per node
     A* gacc = (A*)(cbase + lay.gacc);
-    __shared__ int bbox[6];             // of mark_object
-    __shared__ int wbox[6][16];         // stencil bounds per wave: low corners, complements of the high ones
+    int(&wbox)[6][16] = sh.wbox;
     const int tid = threadIdx.x, bd = blockDim.x, lane = tid & 63, nwave = (bd + 63) >> 6;
     unsigned flags = 0;
 
@@ -809,7 +813,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     const R cv3 = cv * (R(1) / R(3));
 
     // 3. nodes (in the patch launch the patch's nodes are the sub-template's
-    // first nn nodes, so xs, the corners and fs take the same index).  The
+    // first nn nodes, so xs and the corners take the same index).  The
     // node's force from its corners (v, a, b) alone: each hands it the
     // stretching of its edge (v, a), and, as every bending force runs along a
     // triangle's normal, the triangle's normal times the sum of the magnitudes
@@ -822,6 +826,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     // 79.2 -> 72.4 us; FP64, 120 conservative ones 64.2 -> 55.8 us.)
     typedef typename Lists<WIDE>::Raw Raw;
     const int rmax = T->rmax;
+    R F0x = 0, F0y = 0, F0z = 0;
     for (int i = tid; i < nn; i += bd) {
         const double px = xs[3 * i], py = xs[3 * i + 1], pz = xs[3 * i + 2];
         R Fx = 0, Fy = 0, Fz = 0;
@@ -891,9 +896,17 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
             for (int j = 7; j < rmax; ++j) corner(lists_of.raw(j, i));
         }
 
-        fs[3 * i] = Fx;
-        fs[3 * i + 1] = Fy;
-        fs[3 * i + 2] = Fz;
+        // the first node's force stays with its thread
+        if (i == tid) {
+            F0x = Fx;
+            F0y = Fy;
+            F0z = Fz;
+        } else {
+            R* f = O.fel + 3 * node_of(i);
+            gst(f, Fx);
+            gst(f + 1, Fy);
+            gst(f + 2, Fz);
+        }
     }
 
     // Coupling, second part: the reaction forces of all mesh nodes are summed
@@ -945,8 +958,13 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
 
     // per mesh node: interpolate, drag, integrate, spread
     for (int i = tid; i < nn; i += bd) {
-        if (i >= bd) fetch(i);
         const int v = node_of(i);
+        if (i >= bd) {
+            fetch(i);
+            F0x = gat(O.fel, 3 * v);
+            F0y = gat(O.fel, 3 * v + 1);
+            F0z = gat(O.fel, 3 * v + 2);
+        }
         R dgx = 0, dgy = 0, dgz = 0;
         int sb[3];
         if (stencil_corner(px, py, pz, O.anchor, sb)) {
@@ -1043,9 +1061,9 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
             ry = gld(O.frep + 3 * v + 1);
             rz = gld(O.frep + 3 * v + 2);
         }
-        const R ftx = fs[3 * i] - dgx + O.fext[0] + rx;
-        const R fty = fs[3 * i + 1] - dgy + O.fext[1] + ry;
-        const R ftz = fs[3 * i + 2] - dgz + O.fext[2] + rz;
+        const R ftx = F0x - dgx + O.fext[0] + rx;
+        const R fty = F0y - dgy + O.fext[1] + ry;
+        const R ftz = F0z - dgz + O.fext[2] + rz;
         if (O.F) {
             vx += ftx * half_im;
             vy += fty * half_im;
@@ -1105,7 +1123,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     }
     // split stepping: the stencils of the new positions, for the next step
     if (mark_next)  // (mark_object begins with a barrier: every new position is written)
-        mark_object(O.X, SPLIT ? T->order + n0 : nullptr, nn, O.anchor, B, ucap, need, bbox,
+        mark_object(O.X, SPLIT ? T->order + n0 : nullptr, nn, O.anchor, B, ucap, need, sh.bbox,
                     B->touch[parity ^ 1]);
     if (flags) gatomic_or(B->status, flags);
 }

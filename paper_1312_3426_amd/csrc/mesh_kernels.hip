@@ -49,8 +49,9 @@ template <int P, bool USE_LDS, bool CONS, bool CPL, bool LISTS>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(P == PREC_FP64 ? 1 : 6)))
 mesh_kernel(const ObjDev<typename Prec<P>::R>* __restrict__ objs, int parity, int mark_next) {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ MeshShared sh;
     const int bid = blockIdx.x;
-    mesh_object<P, USE_LDS, CONS, CPL, PH_ALL, LISTS>(objs[bid], smem, parity, mark_next);
+    mesh_object<P, USE_LDS, CONS, CPL, PH_ALL, LISTS>(objs[bid], smem, sh, parity, mark_next);
 }
 
 // Meshes too large for LDS whose patches fit there, split over several
@@ -61,8 +62,9 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(P == 
 mesh_split_kernel(const ObjDev<typename Prec<P>::R>* __restrict__ objs, const int2* __restrict__ work, int parity,
                   int mark_next) {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ MeshShared sh;
     const int2 w = work[blockIdx.x];
-    mesh_object<P, PH == PH_PATCH, CONS, PH != PH_PATCH, PH, LISTS>(objs[w.x], smem, parity, mark_next, w.y);
+    mesh_object<P, PH == PH_PATCH, CONS, PH != PH_PATCH, PH, LISTS>(objs[w.x], smem, sh, parity, mark_next, w.y);
 }
 
 // Touch bits of a step of parity `parity` from the current positions (split

@@ -134,7 +134,6 @@ struct TmplDev {
 //                  magnitude) or R [ne][4] (conservative model: wing
 //                  factors w = c/h_A, c/h_D and a_A w_A, a_D w_D, a the
 //                  feet's positions on the edge)
-//             fs   elastic force per node, R [nv][3]
 //             sums area and volume sums of each 64 triangles, FP64 [..][2]
 //   coupling: gacc summed reaction force at the touched lattice nodes, 8-byte
 //                  accumulators [ccap][3] (FP64 form [ccap][6])
@@ -144,10 +143,10 @@ struct TmplDev {
 //             qn   lattice indices of the touched nodes, int [ccap]
 // In LDS the coupling's gacc and ug overlie the forces' arrays, which are dead
 // once every node has its force, and the bits, dead once counted, lie under
-// fs (the positions are read from HBM again after the gather).  A mesh in the
+// tn (the positions are read from HBM again after the gather).  A mesh in the
 // global scratch has both parts side by side, or the coupling part in LDS.
 struct MeshLayout {
-    size_t xs, tn, tr, se, fh, fs, sums, forces;  // offsets and size of the forces part
+    size_t xs, tn, tr, se, fh, sums, forces;      // offsets and size of the forces part
     size_t gacc, ug, need, pw, qn, coupling;      // of the coupling part (in LDS mode from the same base)
     size_t nwords, total;
 };
@@ -162,18 +161,17 @@ __host__ __device__ inline MeshLayout mesh_layout(size_t r, int nv, int nt, int 
     L.se = align16(L.tr + (size_t)nt * r);
     L.fh = align16(L.se + (size_t)ne * r);
     const size_t end = align16(L.fh + (size_t)ne * r * (cons ? 4 : 1));
-    const size_t fsb = (size_t)nv * 3 * r, bits = L.nwords * 4, sumb = (((size_t)nt + 63) / 64) * 16;
+    const size_t bits = L.nwords * 4, sumb = (((size_t)nt + 63) / 64) * 16;
     L.gacc = 0;
     L.ug = (size_t)ccap * (r == 8 ? 6 : 3) * 8;
-    const size_t uend = align16(L.ug + (size_t)ccap * 3 * r);
+    const size_t uend = align16(L.ug + (size_t)ccap * 3 * r), bend = align16(L.tn + bits);
     if (lds) {
-        L.fs = end > uend ? end : uend;
-        L.need = L.fs;
-        L.sums = align16(L.fs + (fsb > bits ? fsb : bits));
+        L.need = L.tn;
+        L.sums = end > uend ? end : uend;
+        if (L.sums < bend) L.sums = bend;
         L.pw = L.sums + sumb;
     } else {
-        L.fs = end;
-        L.sums = align16(L.fs + fsb);
+        L.sums = end;
         L.need = uend;
         L.pw = align16(L.need + bits);
     }
@@ -217,6 +215,7 @@ struct ObjDev {
     real fext[3];
     double mass;
     unsigned char* scratch; // global stand-in for LDS when the mesh does not fit
+    real* fel;        // [nv][3]: elastic forces of the nodes a thread takes after its first
     // slots of G this object's workgroups added to, per step parity and slice:
     // [2][nslice][1 + ccap] ints (a count, then lattice node indices)
     int* qsave;

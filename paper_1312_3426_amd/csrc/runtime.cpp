@@ -401,7 +401,7 @@ struct oif_ctx {
 
     // device mesh
     std::vector<DevBuf> tbufs;  // per-template arrays
-    DevBuf tmpl_dev, obj_dev, X_dev, V_dev, F_dev, geo_dev, scratch_dev;
+    DevBuf tmpl_dev, obj_dev, X_dev, V_dev, F_dev, geo_dev, scratch_dev, fel_dev;
     DevBuf qsave_dev;           // per object: the G slots its workgroups added to (ObjDev::qsave)
     std::vector<unsigned char> obj_host; // ObjDev<real> array as uploaded (sorted)
     int n_lds_obj = 0;          // objects [0, n_lds_obj) use LDS, the rest global scratch
@@ -918,6 +918,7 @@ int upload_mesh_t(oif_ctx* c) {
             }
     if ((rc = dev_alloc(c, c->X_dev, n * sizeof(double)))) return rc;
     if ((rc = dev_alloc(c, c->V_dev, n * sizeof(real)))) return rc;
+    if ((rc = dev_alloc(c, c->fel_dev, n * sizeof(real)))) return rc;
     const bool verlet = c->integrator == OIF_INTEGRATOR_VERLET;
     c->F_dev.release();
     if (verlet) {
@@ -1037,6 +1038,7 @@ int upload_mesh_t(oif_ctx* c) {
         D.inv_mass = (real)(1.0 / o.mass);
         D.mass = o.mass;
         D.scratch = nullptr;
+        D.fel = (real*)c->fel_dev.p + 3 * o.off;
         D.qsave = (int*)c->qsave_dev.p + qoff;
         {
             const Template& T = c->tmpl[o.tid];
@@ -1460,7 +1462,7 @@ int oif_destroy(oif_ctx* c) {
         if (p) (void)hipFree(p);
     for (auto& b : c->tbufs) b.release();
     for (DevBuf* b : {&c->tmpl_dev, &c->obj_dev, &c->X_dev, &c->V_dev, &c->F_dev, &c->geo_dev,
-                      &c->scratch_dev, &c->split_work, &c->qsave_dev, &c->part_dev, &c->diag_out, &c->rep_desc,
+                      &c->scratch_dev, &c->fel_dev, &c->split_work, &c->qsave_dev, &c->part_dev, &c->diag_out, &c->rep_desc,
                       &c->rep_pos,
                       &c->rep_cell,
                       &c->rep_cnt, &c->rep_cursor, &c->rep_bsum, &c->rep_list, &c->rep_spos, &c->rep_stype,
@@ -2210,7 +2212,7 @@ int oif_info(oif_ctx* c, oif_info_t* info) {
     long long bytes = 2 * (long long)pop_bytes(c) + (long long)c->G_bytes + 8LL * ((c->N + 63) / 64);
     for (auto& b : c->tbufs) bytes += (long long)b.n;
     for (const DevBuf* b : {&c->tmpl_dev, &c->obj_dev, &c->X_dev, &c->V_dev, &c->F_dev, &c->geo_dev,
-                            &c->scratch_dev, &c->qsave_dev, &c->rep_pos, &c->rep_cell, &c->rep_cnt, &c->rep_cursor,
+                            &c->scratch_dev, &c->fel_dev, &c->qsave_dev, &c->rep_pos, &c->rep_cell, &c->rep_cnt, &c->rep_cursor,
                             &c->rep_bsum,
                             &c->rep_list, &c->rep_spos, &c->rep_stype, &c->rep_frep, &c->rep_type, &c->rep_shape})
         bytes += (long long)b->n;
