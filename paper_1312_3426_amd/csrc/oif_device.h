@@ -235,15 +235,23 @@ struct ShapeDev {
     double n[3], dist;          // half-space
 };
 constexpr int REP_TYPES = 16;   // part types 0 .. 15
-// Cell lists of one box: the mesh nodes sorted by cell (cells of at least the
-// largest pair range, a regular grid over the box, x fastest), inside a cell
-// by node id; positions and types copied into that order, so that a node's
-// partners are read from contiguous runs.
+// A mesh node as the walk along the lists reads it: its position rounded to
+// FP32, enough to pass over nodes beyond the range, and the next node of its
+// cell's list (-1: the last).
+struct alignas(16) RepNode {
+    float x, y, z;
+    int next;
+};
+// Cell lists of one box: a regular grid over the box (cells of at least the
+// largest pair range, x fastest), each cell the head of a linked list of its
+// nodes.  Two sets of heads, by step parity: a step of parity k fills head[k]
+// and empties the cells of the step before it in head[k ^ 1], so no pass runs
+// over all cells.
 struct RepDev {
     int M;
     int ncell;
     int nc[3];
-    double hc[3];               // cell edge per axis (>= the pair range)
+    double hc[3], rhc[3];       // cell edge per axis (>= the pair range), its reciprocal
     double L[3];
     double range2;              // square of the largest pair range
     int walls_z, pairs;         // pairs: some pair interaction is set
@@ -252,14 +260,10 @@ struct RepDev {
     int n_shape;
     const ShapeDev* shape;
     const unsigned char* type;  // [M] part type per node
-    double* pos;                // [M][3] positions the forces are taken at
-    int* cell;                  // [M] cell of each node
-    int* cnt;                   // [ncell + 1] nodes per cell, then cell starts
-    int* cursor;                // [ncell]
-    int* bsum;                  // block sums of the scan
-    int* list;                  // [M] node ids in cell order
-    double* spos;               // [M][3] positions in cell order
-    unsigned char* stype;       // [M] types in cell order
+    RepNode* node;              // [M]
+    double* pos;                // [M][3] positions, wrapped into the box along periodic axes
+    int* cell;                  // [M] cell of each node in the last step (-1: none yet)
+    int* head[2];               // [ncell] first node of each cell, -1: empty
     void* frep;                 // [M][3] force, arithmetic type
     unsigned* status;           // the box's watchdog word (ST_OVERFLOW: a force out of range)
 };
@@ -318,9 +322,10 @@ struct MeshLaunch {
 hipError_t launch_mesh(const MeshLaunch& L);
 
 // Soft-sphere forces of one box into rep->frep (host copy `h` of the device
-// descriptor `d` gives the sizes): bin, scan, scatter, order, force.
-hipError_t launch_repulsion(const RepDev& h, const RepDev* d, const void* objs, int nobj, int precision,
-                            hipStream_t s);
+// descriptor `d` gives the sizes; objects of at most max_nv nodes), in a step
+// of the given parity.
+hipError_t launch_repulsion(const RepDev& h, const RepDev* d, const void* objs, int nobj, int max_nv, int parity,
+                            int precision, hipStream_t s);
 
 // Per-template LDS bytes of the mesh kernel.
 size_t mesh_lds_bytes(int precision, int nv, int nt, int ne, int ucap, int ccap, int cons);

@@ -394,8 +394,8 @@ struct oif_ctx {
     std::vector<ShapeDev> shapes;
     bool rep_on = false;
     RepDev rep_h{};
-    DevBuf rep_desc, rep_pos, rep_cell, rep_cnt, rep_cursor, rep_bsum, rep_list, rep_spos, rep_stype, rep_frep,
-        rep_type, rep_shape;
+    DevBuf rep_desc, rep_node, rep_pos, rep_cell, rep_head, rep_frep, rep_type, rep_shape;
+    int rep_max_nv = 0;         // nodes of the largest object
     bool host_stale = false;
     bool mesh_dirty = true;     // device mesh arrays must be rebuilt
 
@@ -572,8 +572,8 @@ int setup_repulsion(oif_ctx* c, size_t real_bytes) {
             }
     }
     c->rep_on = (pairs || walls) && c->M > 0;
-    for (DevBuf* b : {&c->rep_desc, &c->rep_pos, &c->rep_cell, &c->rep_cnt, &c->rep_cursor, &c->rep_bsum,
-                      &c->rep_list, &c->rep_spos, &c->rep_stype, &c->rep_frep, &c->rep_type, &c->rep_shape})
+    for (DevBuf* b : {&c->rep_desc, &c->rep_node, &c->rep_pos, &c->rep_cell, &c->rep_head, &c->rep_frep, &c->rep_type,
+                      &c->rep_shape})
         b->release();
     if (!c->rep_on) return OIF_OK;
     RepDev& R = c->rep_h;
@@ -595,19 +595,25 @@ int setup_repulsion(oif_ctx* c, size_t real_bytes) {
         R.nc[big] = std::max(1, R.nc[big] - std::max(1, R.nc[big] / 8));
     }
     R.ncell = R.nc[0] * R.nc[1] * R.nc[2];
-    for (int a = 0; a < 3; ++a) R.hc[a] = R.L[a] / R.nc[a];
+    for (int a = 0; a < 3; ++a) {
+        R.hc[a] = R.L[a] / R.nc[a];
+        R.rhc[a] = R.nc[a] / R.L[a];
+    }
     std::memcpy(R.pair, c->rep_pair, sizeof(R.pair));
     std::memcpy(R.wall, c->rep_wall, sizeof(R.wall));
     const size_t M = c->M, NC = (size_t)R.ncell;
     int rc_ = 0;
-    if ((rc_ = dev_alloc(c, c->rep_pos, 3 * M * sizeof(double))) || (rc_ = dev_alloc(c, c->rep_cell, M * 4)) ||
-        (rc_ = dev_alloc(c, c->rep_cnt, (NC + 1) * 4)) || (rc_ = dev_alloc(c, c->rep_cursor, NC * 4)) ||
-        (rc_ = dev_alloc(c, c->rep_bsum, (NC / 1024 + 1) * 4)) || (rc_ = dev_alloc(c, c->rep_list, M * 4)) ||
-        (rc_ = dev_alloc(c, c->rep_spos, 3 * M * sizeof(double))) || (rc_ = dev_alloc(c, c->rep_stype, M)) ||
-        (rc_ = dev_alloc(c, c->rep_frep, 3 * M * real_bytes)) || (rc_ = dev_alloc(c, c->rep_type, M)) ||
+    if ((rc_ = dev_alloc(c, c->rep_node, M * sizeof(RepNode))) || (rc_ = dev_alloc(c, c->rep_pos, 3 * M * 8)) || (rc_ = dev_alloc(c, c->rep_cell, M * 4)) ||
+        (rc_ = dev_alloc(c, c->rep_head, 2 * NC * 4)) || (rc_ = dev_alloc(c, c->rep_frep, 3 * M * real_bytes)) ||
+        (rc_ = dev_alloc(c, c->rep_type, M)) ||
         (rc_ = dev_alloc(c, c->rep_shape, (c->shapes.size() + 1) * sizeof(ShapeDev))) ||
         (rc_ = dev_alloc(c, c->rep_desc, sizeof(RepDev))))
         return rc_;
+    // empty lists, no node in any
+    HIPCALL(c, hipMemset(c->rep_head.p, 0xff, 2 * NC * 4));
+    HIPCALL(c, hipMemset(c->rep_cell.p, 0xff, M * 4));
+    c->rep_max_nv = 0;
+    for (const Object& o : c->obj) c->rep_max_nv = std::max(c->rep_max_nv, o.nv);
     std::vector<unsigned char> types(M);
     for (const Object& o : c->obj)
         for (int v = 0; v < o.nv; ++v) types[(size_t)o.off + v] = (unsigned char)o.ptype;
@@ -618,14 +624,11 @@ int setup_repulsion(oif_ctx* c, size_t real_bytes) {
     R.n_shape = (int)c->shapes.size();
     R.shape = (const ShapeDev*)c->rep_shape.p;
     R.type = (const unsigned char*)c->rep_type.p;
+    R.node = (RepNode*)c->rep_node.p;
     R.pos = (double*)c->rep_pos.p;
     R.cell = (int*)c->rep_cell.p;
-    R.cnt = (int*)c->rep_cnt.p;
-    R.cursor = (int*)c->rep_cursor.p;
-    R.bsum = (int*)c->rep_bsum.p;
-    R.list = (int*)c->rep_list.p;
-    R.spos = (double*)c->rep_spos.p;
-    R.stype = (unsigned char*)c->rep_stype.p;
+    R.head[0] = (int*)c->rep_head.p;
+    R.head[1] = (int*)c->rep_head.p + NC;
     R.frep = c->rep_frep.p;
     R.status = c->status;
     HIPCALL(c, hipMemcpy(c->rep_desc.p, &R, sizeof(RepDev), hipMemcpyHostToDevice));
@@ -1112,7 +1115,7 @@ int enqueue_mesh(oif_ctx* c, int par, hipStream_t s, int mark_next) {
     const size_t osz = objdev_size(c->d.precision);
     if (c->rep_on)
         HIPCALL(c, launch_repulsion(c->rep_h, (const RepDev*)c->rep_desc.p, c->obj_dev.p, (int)c->obj.size(),
-                                    c->d.precision, s));
+                                    c->rep_max_nv, par, c->d.precision, s));
     MeshLaunch ml{};
     auto block = [&](size_t lds, int nwg) { return membrane_block(c->mesh_block, c->d.precision, lds, nwg, c->n_cu); };
     ml.parity = par;
@@ -1463,10 +1466,7 @@ int oif_destroy(oif_ctx* c) {
     for (auto& b : c->tbufs) b.release();
     for (DevBuf* b : {&c->tmpl_dev, &c->obj_dev, &c->X_dev, &c->V_dev, &c->F_dev, &c->geo_dev,
                       &c->scratch_dev, &c->fel_dev, &c->split_work, &c->qsave_dev, &c->part_dev, &c->diag_out, &c->rep_desc,
-                      &c->rep_pos,
-                      &c->rep_cell,
-                      &c->rep_cnt, &c->rep_cursor, &c->rep_bsum, &c->rep_list, &c->rep_spos, &c->rep_stype,
-                      &c->rep_frep, &c->rep_type, &c->rep_shape})
+                      &c->rep_node, &c->rep_pos, &c->rep_cell, &c->rep_head, &c->rep_frep, &c->rep_type, &c->rep_shape})
         b->release();
     if (c->own) (void)hipStreamDestroy(c->own);
     if (c->side) (void)hipStreamDestroy(c->side);
@@ -2212,9 +2212,8 @@ int oif_info(oif_ctx* c, oif_info_t* info) {
     long long bytes = 2 * (long long)pop_bytes(c) + (long long)c->G_bytes + 8LL * ((c->N + 63) / 64);
     for (auto& b : c->tbufs) bytes += (long long)b.n;
     for (const DevBuf* b : {&c->tmpl_dev, &c->obj_dev, &c->X_dev, &c->V_dev, &c->F_dev, &c->geo_dev,
-                            &c->scratch_dev, &c->fel_dev, &c->qsave_dev, &c->rep_pos, &c->rep_cell, &c->rep_cnt, &c->rep_cursor,
-                            &c->rep_bsum,
-                            &c->rep_list, &c->rep_spos, &c->rep_stype, &c->rep_frep, &c->rep_type, &c->rep_shape})
+                            &c->scratch_dev, &c->fel_dev, &c->qsave_dev, &c->rep_node, &c->rep_pos, &c->rep_cell, &c->rep_head,
+                            &c->rep_frep, &c->rep_type, &c->rep_shape})
         bytes += (long long)b->n;
     info->device_bytes = bytes;
     info->lb_block = c->lb_block;
@@ -2729,7 +2728,7 @@ int batch_enqueue(oif_batch* b, int n, int parity0, hipStream_t s, std::vector<h
         for (oif_ctx* c : b->ctx)
             if (c->rep_on)
                 BHIP(b, launch_repulsion(c->rep_h, (const RepDev*)c->rep_desc.p, c->obj_dev.p,
-                                         (int)c->obj.size(), c->d.precision, s));
+                                         (int)c->obj.size(), c->rep_max_nv, par, c->d.precision, s));
         if (b->persistent) {  // the membranes and the lattice of every box in one launch
             BatchLaunch bl{(const BatchSched*)b->sched_dev.p, b->p_grid, persistent_block(b), b->p_lds, par,
                            b->precision, b->lb_nt, s};
