@@ -190,23 +190,6 @@ __device__ __forceinline__ T gatomic_or(T* p, T v) {
     return __hip_atomic_fetch_or((gptr<T>)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Block-wide FP64 sum with a fixed combination order: a butterfly inside each
-// 64-lane wave (every lane ends with the same value), then the per-wave sums
-// added in wave order.  Deterministic for a given block size.  `red` must hold
-// one double per wave; all threads of the block must call it.
-__device__ inline double block_sum(double v, double* red) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    double tot = 0.0;
-    const int nw = (blockDim.x + 63) >> 6;
-    for (int k = 0; k < nw; ++k) tot += red[k];
-    __syncthreads();
-    return tot;
-}
-
 // Cross-lane moves inside the vector ALU (no LDS round trip): each step takes
 // a lane's value from a lower lane, `old` where there is none.  The reductions
 // below combine 1, 2, 4, 8 lanes of a row of 16, then (row_bcast) the rows, so

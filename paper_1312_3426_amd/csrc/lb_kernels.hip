@@ -11,8 +11,8 @@
 //               and writes 19 stored values once, 2 x 19 x sizeof(storage)
 //               bytes per node; the force read adds 24 bytes only at nodes
 //               touched by the spreading.
-//   diag_*      FP64 sums of mass and momentum and a non-finite watchdog,
-//               two passes with a fixed summation order (deterministic).
+//   diag_kernel FP64 sums of mass and momentum (lattice and membranes) and a
+//               non-finite watchdog, with a fixed summation order (deterministic).
 //   *_to_*      conversions between the storage form and canonical FP64 fields.
 #include "lb_device.h"
 
@@ -43,63 +43,105 @@ lb_kernel(const BoxDev* __restrict__ boxes, const int2* __restrict__ work, int n
     lb_node<P, OBST, ALL, MRT, NT>(boxes + box, blk * (int)blockDim.x + (int)threadIdx.x, parity, mode);
 }
 
+// The sums of a state in one launch: blocks below `nlat` take lattice nodes,
+// each of the others one object, and the last block to end adds the partials
+// up and writes the ten totals and the status word to host memory.  Every sum
+// has a fixed order (a thread's nodes in turn, a tree over the wave, the waves
+// in turn; the partials likewise), so which block comes last does not show in
+// the bits.  A chain of latencies on all but the largest boxes, which is why
+// it is one launch: a call takes 23 us at half a million nodes (12 of them the
+// kernel), as three kernels and two copies 50.  1024 threads per block: sixteen
+// waves per compute unit keep enough population loads in flight over the
+// grid-stride loop.
 template <int P>
 __global__ void __launch_bounds__(1024)
-diag_lattice_kernel(const BoxDev* __restrict__ B, int parity, double* __restrict__ part) {
+diag_kernel(const BoxDev* __restrict__ B, const ObjDev<typename Prec<P>::R>* __restrict__ objs, int nlat, int nobj,
+            int parity, double* part, double* out) {
     typedef typename Prec<P>::S S;
-    __shared__ double red[16];
-    const S* __restrict__ src = (const S*)B->f[parity];
-    const int N = B->N;
-    const float inv = B->st_inv;
-    double dm = 0, jx = 0, jy = 0, jz = 0, bad = 0;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < N; p += gridDim.x * blockDim.x) {
-        double d[19];
+    __shared__ double red[5][16];
+    __shared__ bool last;
+    const int t = threadIdx.x, wave = t >> 6, blk = blockIdx.x;
+    double s[5] = {0, 0, 0, 0, 0};
+    double scale = 1.0;
+    if (blk < nlat) {
+        const S* __restrict__ src = (const S*)B->f[parity];
+        const int N = B->N;
+        const float inv = B->st_inv;
+        for (int p = blk * 1024 + t; p < N; p += nlat * 1024) {
+            double d[19];
 #pragma unroll
-        for (int i = 0; i < 19; ++i) {
-            d[i] = (double)dec<P>(pop_load(src, i, p), inv);
-            if (!isfinite(d[i])) bad = 1.0;
-        }
+            for (int i = 0; i < 19; ++i) {
+                d[i] = (double)dec<P>(pop_load(src, i, p), inv);
+                if (!isfinite(d[i])) s[4] = 1.0;
+            }
 #pragma unroll
-        for (int i = 0; i < 19; ++i) {
-            dm += d[i];
-            jx += cx(i) * d[i];
-            jy += cy(i) * d[i];
-            jz += cz(i) * d[i];
+            for (int i = 0; i < 19; ++i) {
+                s[0] += d[i];
+                s[1] += cx(i) * d[i];
+                s[2] += cy(i) * d[i];
+                s[3] += cz(i) * d[i];
+            }
         }
+    } else {
+        const ObjDev<typename Prec<P>::R>& O = objs[blk - nlat];
+        const int nv = O.t->nv;
+        for (int v = t; v < nv; v += 1024) {
+            const double a = O.V[3 * v], b = O.V[3 * v + 1], c = O.V[3 * v + 2];
+            s[1] += a;
+            s[2] += b;
+            s[3] += c;
+            if (!isfinite(a + b + c) || !isfinite(O.X[3 * v] + O.X[3 * v + 1] + O.X[3 * v + 2])) s[4] = 1.0;
+        }
+        scale = O.mass;
     }
-    const double s0 = block_sum(dm, red), s1 = block_sum(jx, red), s2 = block_sum(jy, red),
-                 s3 = block_sum(jz, red), s4 = block_sum(bad, red);
-    if (threadIdx.x == 0) {
-        double* o = part + 5 * blockIdx.x;
-        o[0] = s0; o[1] = s1; o[2] = s2; o[3] = s3; o[4] = s4;
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+        const double w = wave_sum(s[c]);
+        if ((t & 63) == 63) red[c][wave] = w;
     }
-}
-
-// The five sums of the lattice blocks' partials and of the objects' partials
-// in a fixed order (thread t adds partials t, t + 256, ... in turn, then a fixed
-// tree over the 256 threads): the same bits on every run.
-__global__ void __launch_bounds__(256) diag_final_kernel(const double* __restrict__ part, int nlat, int nmesh,
-                                                         double* __restrict__ out) {
-    __shared__ double red[5][256];
-    const int t = threadIdx.x;
-    for (int g = 0; g < 2; ++g) {
-        const double* p = part + (g ? 5 * (size_t)nlat : 0);
-        const int n = g ? nmesh : nlat;
-        double s[5] = {0, 0, 0, 0, 0};
-        for (int k = t; k < n; k += 256)
+    __syncthreads();
+    if (t < 5) {
+        double tot = 0.0;
+        for (int k = 0; k < 16; ++k) tot += red[t][k];
+        if (t > 0 && t < 4) tot *= scale;
+        // an exchange whose old value has come back is in device memory, so no
+        // fence is needed before the count (a release here writes each XCD's L2
+        // back, and with it what the step left there: 84 us instead of 12 at half a
+        // million nodes)
+        const double old = __hip_atomic_exchange(part + 5 * (size_t)blk + t, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("" ::"v"(old));
+    }
+    __syncthreads();
+    unsigned* ctr = B->status + STATUS_DIAG_CTR;
+    if (t == 0) {
+        last = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        if (last) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+    }
+    __syncthreads();
+    if (!last) return;
+    // the lower half of the block adds the lattice's partials, the upper half the objects'
+    const int g = t >> 9, n = g ? nobj : nlat;
+    const double* p = part + (g ? 5 * (size_t)nlat : 0);
+    double q[5] = {0, 0, 0, 0, 0};
+    for (int k = t & 511; k < n; k += 512)
 #pragma unroll
-            for (int c = 0; c < 5; ++c) s[c] += p[5 * (size_t)k + c];
+        for (int c = 0; c < 5; ++c)
+            q[c] += __hip_atomic_load(p + 5 * (size_t)k + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int c = 0; c < 5; ++c) red[c][t] = s[c];
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (t < w)
-#pragma unroll
-                for (int c = 0; c < 5; ++c) red[c][t] += red[c][t + w];
-            __syncthreads();
-        }
-        if (t < 5) out[5 * g + t] = red[t][0];
-        __syncthreads();
+    for (int c = 0; c < 5; ++c) {
+        const double w = wave_sum(q[c]);
+        if ((t & 63) == 63) red[c][wave] = w;
+    }
+    __syncthreads();
+    double* word = out + t;
+    if (t < 10) {
+        const int c = t % 5, w0 = t / 5 * 8;
+        double tot = 0.0;
+        for (int k = 0; k < 8; ++k) tot += red[c][w0 + k];
+        __hip_atomic_store(word, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else if (t == 10) {
+        const unsigned st = __hip_atomic_load(B->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(word, (double)st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -229,16 +271,22 @@ hipError_t launch_lb(const LbLaunch& L) {
     return hipGetLastError();
 }
 
-hipError_t launch_diag_lattice(const BoxDev* box_dev, int precision, int parity, double* partials,
-                               int nblocks, hipStream_t s) {
-    // 1024 threads per block: sixteen waves per compute unit keep enough
-    // population loads in flight over the grid-stride loop
-    OIF_DISPATCH_P(precision, diag_lattice_kernel, dim3(nblocks), dim3(1024), s, box_dev, parity, partials);
-    return hipGetLastError();
-}
-
-hipError_t launch_diag_final(const double* partials, int nlat, int nmesh, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(256), 0, s, partials, nlat, nmesh, out);
+hipError_t launch_diag(const BoxDev* box_dev, int N, const void* objs, int nobj, int precision, int parity,
+                       double* partials, double* out, hipStream_t s) {
+    const int nlat = diag_lattice_blocks(N);
+#define OIF_DIAG(P)                                                                                               \
+    case P:                                                                                                       \
+        hipLaunchKernelGGL(diag_kernel<P>, dim3(nlat + nobj), dim3(1024), 0, s, box_dev,                          \
+                           (const ObjDev<typename Prec<P>::R>*)objs, nlat, nobj, parity, partials, out);          \
+        break
+    switch (precision) {
+        OIF_DIAG(PREC_FP64);
+        OIF_DIAG(PREC_FP32);
+        OIF_DIAG(PREC_FP16);
+        OIF_DIAG(PREC_BF16);
+        default: return hipErrorInvalidValue;
+    }
+#undef OIF_DIAG
     return hipGetLastError();
 }
 

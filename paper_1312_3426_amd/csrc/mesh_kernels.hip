@@ -79,27 +79,6 @@ __global__ void __launch_bounds__(256) mark_kernel(const ObjDev<R>* __restrict__
     mark_object(O.X, nullptr, O.t->nv, O.anchor, B, min(O.t->ucap, cap), bits, bbox, B->touch[parity]);
 }
 
-template <typename R>
-__global__ void __launch_bounds__(256)
-diag_mesh_kernel(const ObjDev<R>* __restrict__ objs, double* __restrict__ part) {
-    __shared__ double red[16];
-    const ObjDev<R>& O = objs[blockIdx.x];
-    const int nv = O.t->nv;
-    double vx = 0, vy = 0, vz = 0, bad = 0;
-    for (int v = threadIdx.x; v < nv; v += blockDim.x) {
-        const double a = O.V[3 * v], b = O.V[3 * v + 1], c = O.V[3 * v + 2];
-        vx += a; vy += b; vz += c;
-        if (!isfinite(a + b + c) || !isfinite(O.X[3 * v] + O.X[3 * v + 1] + O.X[3 * v + 2])) bad = 1.0;
-    }
-    const double m = O.mass;
-    const double s0 = block_sum(vx, red), s1 = block_sum(vy, red), s2 = block_sum(vz, red),
-                 s3 = block_sum(bad, red);
-    if (threadIdx.x == 0) {
-        double* o = part + 5 * blockIdx.x;
-        o[0] = 0.0; o[1] = m * s0; o[2] = m * s1; o[3] = m * s2; o[4] = s3;
-    }
-}
-
 template <int P, bool LISTS>
 hipError_t launch_mesh_pl(const MeshLaunch& L) {
     typedef typename Prec<P>::R R;
@@ -217,17 +196,6 @@ hipError_t launch_mark(const void* objs, int nobj, int precision, size_t lds_byt
     else
         hipLaunchKernelGGL(mark_kernel<float>, dim3(nobj), dim3(256), lds_bytes, s, (const ObjDev<float>*)objs,
                            parity, cap);
-    return hipGetLastError();
-}
-
-hipError_t launch_diag_mesh(const void* objs, int nobj, int precision, double* partials, hipStream_t s) {
-    if (nobj <= 0) return hipSuccess;
-    if (precision == PREC_FP64)
-        hipLaunchKernelGGL(diag_mesh_kernel<double>, dim3(nobj), dim3(256), 0, s, (const ObjDev<double>*)objs,
-                           partials);
-    else
-        hipLaunchKernelGGL(diag_mesh_kernel<float>, dim3(nobj), dim3(256), 0, s, (const ObjDev<float>*)objs,
-                           partials);
     return hipGetLastError();
 }
 

@@ -29,6 +29,8 @@
 namespace oif {
 
 enum : int { PREC_FP64 = 0, PREC_FP32 = 1, PREC_FP16 = 2, PREC_BF16 = 3 };
+// word of the status allocation that counts the diagnostics blocks that have ended
+constexpr int STATUS_DIAG_CTR = 16;
 enum : unsigned { ST_NONFINITE = 1u, ST_CLAMPED = 2u, ST_OVERFLOW = 4u };
 
 struct BoxDev {
@@ -337,12 +339,12 @@ hipError_t mesh_set_max_lds(size_t bytes);
 
 // FP64 diagnostics.  Lattice partials: per block [sum dev, jx, jy, jz, nonfinite];
 // mesh partials: per object [0, m vx, m vy, m vz, nonfinite], stored after the
-// lattice partials; final: out[0..4] lattice sums, out[5..9] mesh sums.
-hipError_t launch_diag_lattice(const BoxDev* box_dev, int precision, int parity, double* partials,
-                               int nblocks, hipStream_t s);
-hipError_t launch_diag_mesh(const void* objs, int nobj, int precision, double* partials,
-                            hipStream_t s);
-hipError_t launch_diag_final(const double* partials, int nlat, int nmesh, double* out, hipStream_t s);
+// lattice partials; out (memory that the host can read) [0..4] lattice sums,
+// [5..9] mesh sums, [10] the status word.
+constexpr int DIAG_BLOCKS = 256;  // most lattice blocks (of 1024 nodes at a time) it takes
+inline int diag_lattice_blocks(int N) { return N > 1024 * DIAG_BLOCKS ? DIAG_BLOCKS : (N + 1023) / 1024; }
+hipError_t launch_diag(const BoxDev* box_dev, int N, const void* objs, int nobj, int precision, int parity,
+                       double* partials, double* out, hipStream_t s);
 
 // plain device-to-device copy kernel of `bytes` (a multiple of 16)
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s);

@@ -32,7 +32,7 @@ using namespace oif;
 
 // Fixed device memory of the allocation-free diagnostics call
 // (oif_diagnostics_noalloc): the FP64 partial sums of the lattice blocks and
-// of the objects, then the ten final sums.  Every device the library runs on
+// of the objects.  Every device the library runs on
 // holds one such array until the process ends, shared by all contexts there.
 // On the host `scratch` names the symbol only, not device memory: host code
 // uses the address looked up once per device (scratch_address), never the
@@ -424,8 +424,9 @@ struct oif_ctx {
     int g_len = 0;
 
     // diagnostics
-    DevBuf part_dev, diag_out;
-    int diag_blocks = 256;
+    DevBuf part_dev;
+    double* diag_host = nullptr;  // pinned: the sums and status word of the last diagnostics launch
+    double* diag_out = nullptr;   // the same memory by its device address
     void* scratch_addr = nullptr;  // device address of this device's `scratch` array
 };
 
@@ -1056,7 +1057,7 @@ int upload_mesh_t(oif_ctx* c) {
     if ((rc = dev_alloc(c, c->obj_dev, od.size() * sizeof(ObjDev<real>)))) return rc;
     HIPCALL(c, hipMemcpy(c->obj_dev.p, od.data(), od.size() * sizeof(ObjDev<real>), hipMemcpyHostToDevice));
     // diagnostics partials: lattice blocks + objects
-    if ((rc = dev_alloc(c, c->part_dev, 5 * sizeof(double) * (c->diag_blocks + c->obj.size() + 1)))) return rc;
+    if ((rc = dev_alloc(c, c->part_dev, 5 * sizeof(double) * (DIAG_BLOCKS + c->obj.size() + 1)))) return rc;
     return OIF_OK;
 }
 
@@ -1240,23 +1241,27 @@ int enqueue_steps(oif_ctx* c, int n, int parity0, hipStream_t s) {
     return OIF_OK;
 }
 
-// FP64 sums of the current state: per-block and per-object partials in
-// `part` (5 doubles each), the ten totals in `fin`, copied to out[10].
-int run_diag_in(oif_ctx* c, double* part, double* fin, double out[10], unsigned* status) {
-    HIPCALL(c, launch_diag_lattice(c->box_dev, c->d.precision, c->parity, part, c->diag_blocks, c->stream));
-    HIPCALL(c, launch_diag_mesh(c->obj_dev.p, (int)c->obj.size(), c->d.precision, part + 5 * c->diag_blocks, c->stream));
-    HIPCALL(c, launch_diag_final(part, c->diag_blocks, (int)c->obj.size(), fin, c->stream));
-    HIPCALL(c, hipMemcpyAsync(out, fin, 10 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIPCALL(c, hipMemcpyAsync(status, c->status, sizeof(unsigned), hipMemcpyDeviceToHost, c->stream));
+// FP64 sums of the current state, enqueued on `s`: per-block and per-object
+// partials in `part` (5 doubles each), the ten totals and the status word in
+// the context's pinned words, to be read once `s` has been waited for.
+int enqueue_diag(oif_ctx* c, double* part, hipStream_t s) {
+    HIPCALL(c, launch_diag(c->box_dev, c->N, c->obj_dev.p, (int)c->obj.size(), c->d.precision, c->parity, part,
+                           c->diag_out, s));
+    return OIF_OK;
+}
+
+int run_diag(oif_ctx* c, double* part) {
+    int rc = enqueue_diag(c, part, c->stream);
+    if (rc) return rc;
     HIPCALL(c, hipStreamSynchronize(c->stream));
     return OIF_OK;
 }
 
-int run_diag(oif_ctx* c, double out[10], unsigned* status) {
-    return run_diag_in(c, (double*)c->part_dev.p, (double*)c->diag_out.p, out, status);
-}
+unsigned diag_status(const oif_ctx* c) { return (unsigned)c->diag_host[10]; }
 
-void fill_diag(const oif_ctx* c, const double out[10], unsigned st, oif_diag* d) {
+void fill_diag(const oif_ctx* c, oif_diag* d) {
+    const double* out = c->diag_host;
+    const unsigned st = diag_status(c);
     d->mass = (double)c->N * c->d.rho0 + out[0];
     for (int k = 0; k < 3; ++k) {
         d->momentum_fluid[k] = out[1 + k];
@@ -1267,15 +1272,19 @@ void fill_diag(const oif_ctx* c, const double out[10], unsigned st, oif_diag* d)
     d->overflow = (st & ST_OVERFLOW) ? 1 : 0;
 }
 
-int watchdog(oif_ctx* c) {
-    double out[10];
-    unsigned st = 0;
-    int rc = run_diag(c, out, &st);
-    if (rc) return rc;
+// What the watchdog says of the last diagnostics launch (already waited for).
+int watchdog_verdict(oif_ctx* c) {
+    const double* out = c->diag_host;
+    const unsigned st = diag_status(c);
     if (out[4] != 0 || out[9] != 0 || (st & ST_NONFINITE))
         return fail(c, OIF_E_NONFINITE, "watchdog: non-finite populations or mesh state");
     if (st & ST_OVERFLOW) return fail(c, OIF_E_OVERFLOW, "watchdog: coupling force out of fixed-point range");
     return OIF_OK;
+}
+
+int watchdog(oif_ctx* c) {
+    int rc = run_diag(c, (double*)c->part_dev.p);
+    return rc ? rc : watchdog_verdict(c);
 }
 
 int check_obj(oif_ctx* c, int oid) {
@@ -1442,8 +1451,9 @@ int oif_create(const oif_lattice_desc* desc, oif_ctx** out) {
     b.fp_scale = std::ldexp(1.0, d.fixed_point_exp);
     b.fp_inv = std::ldexp(1.0, -d.fixed_point_exp);
     if (hipMemcpyAsync(c->box_dev, &b, sizeof(BoxDev), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-        dev_alloc(cp, c->diag_out, 16 * sizeof(double)) != OIF_OK ||
-        dev_alloc(cp, c->part_dev, 5 * sizeof(double) * (c->diag_blocks + 1)) != OIF_OK ||
+        hipHostMalloc((void**)&c->diag_host, 16 * sizeof(double), hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer((void**)&c->diag_out, c->diag_host, 0) != hipSuccess ||
+        dev_alloc(cp, c->part_dev, 5 * sizeof(double) * (DIAG_BLOCKS + 1)) != OIF_OK ||
         hipStreamSynchronize(c->stream) != hipSuccess) {
         oif_destroy(c.release());
         return OIF_E_HIP;
@@ -1465,9 +1475,10 @@ int oif_destroy(oif_ctx* c) {
         if (p) (void)hipFree(p);
     for (auto& b : c->tbufs) b.release();
     for (DevBuf* b : {&c->tmpl_dev, &c->obj_dev, &c->X_dev, &c->V_dev, &c->F_dev, &c->geo_dev,
-                      &c->scratch_dev, &c->fel_dev, &c->split_work, &c->qsave_dev, &c->part_dev, &c->diag_out, &c->rep_desc,
+                      &c->scratch_dev, &c->fel_dev, &c->split_work, &c->qsave_dev, &c->part_dev, &c->rep_desc,
                       &c->rep_node, &c->rep_pos, &c->rep_cell, &c->rep_head, &c->rep_frep, &c->rep_type, &c->rep_shape})
         b->release();
+    if (c->diag_host) (void)hipHostFree(c->diag_host);
     if (c->own) (void)hipStreamDestroy(c->own);
     if (c->side) (void)hipStreamDestroy(c->side);
     if (c->ev_mark) (void)hipEventDestroy(c->ev_mark);
@@ -2238,10 +2249,8 @@ int oif_diagnostics(oif_ctx* c, oif_diag* d) {
     if (!c || !d) return OIF_E_ARG;
     int rc = sync_mesh(c);
     if (rc) return rc;
-    double out[10];
-    unsigned st = 0;
-    if ((rc = run_diag(c, out, &st))) return rc;
-    fill_diag(c, out, st, d);
+    if ((rc = run_diag(c, (double*)c->part_dev.p))) return rc;
+    fill_diag(c, d);
     return OIF_OK;
 }
 
@@ -2251,21 +2260,16 @@ int oif_diagnostics_noalloc(oif_ctx* c, oif_diag* d) {
         return fail(c, OIF_E_STATE,
                     "oif_diagnostics_noalloc: the objects changed since the last step and their device arrays "
                     "are not in place; call oif_step (or oif_diagnostics) first");
-    // partials of the lattice blocks and objects, then the totals on a
-    // 256-byte boundary
+    // room for the partials of the most lattice blocks and of the objects
     const long long nobj = (long long)c->obj.size();
-    const long long max_obj = (SCRATCH_DOUBLES - 16) / 32 * 32 / 5 - c->diag_blocks;
+    const long long max_obj = (SCRATCH_DOUBLES - 16) / 32 * 32 / 5 - DIAG_BLOCKS;
     if (nobj > max_obj)
         return fail(c, OIF_E_ARG,
                     "oif_diagnostics_noalloc: " + std::to_string(nobj) + " objects exceed its fixed scratch (at most " +
                         std::to_string(max_obj) + ")");
-    const long long fin_off = (5LL * (c->diag_blocks + nobj) + 31) / 32 * 32;
-    double* part = (double*)c->scratch_addr;
-    double out[10];
-    unsigned st = 0;
-    int rc = run_diag_in(c, part, part + fin_off, out, &st);
+    int rc = run_diag(c, (double*)c->scratch_addr);
     if (rc) return rc;
-    fill_diag(c, out, st, d);
+    fill_diag(c, d);
     return OIF_OK;
 }
 
@@ -2827,8 +2831,16 @@ int batch_finish(oif_batch* b, int n) {
         c->touch_valid = false;  // batched steps do not mark stencils
         if (c->M) c->host_stale = true;
     }
+    // the boxes' sums one launch after another behind the step, one wait for all
+    // (a wait for each took 1.6 ms of a batch of 32 boxes of 64^3)
+    hipStream_t s = b->ctx[0]->stream;
     for (oif_ctx* c : b->ctx) {
-        int rc = watchdog(c);
+        int rc = enqueue_diag(c, (double*)c->part_dev.p, s);
+        if (rc) return bfail(b, rc, c->err);
+    }
+    BHIP(b, hipStreamSynchronize(s));
+    for (oif_ctx* c : b->ctx) {
+        int rc = watchdog_verdict(c);
         if (rc) return bfail(b, rc, c->err);
     }
     return OIF_OK;
