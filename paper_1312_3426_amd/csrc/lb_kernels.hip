@@ -14,6 +14,8 @@
 //   diag_kernel FP64 sums of mass and momentum (lattice and membranes) and a
 //               non-finite watchdog, with a fixed summation order (deterministic).
 //   *_to_*      conversions between the storage form and canonical FP64 fields.
+#include <algorithm>
+
 #include "lb_device.h"
 
 namespace oif {
@@ -175,19 +177,19 @@ __global__ void f64_to_pops_kernel(const BoxDev* __restrict__ B, int parity, con
 }
 
 template <int P>
-__global__ void moments_kernel(const BoxDev* __restrict__ B, int parity, double* __restrict__ rho,
-                               double* __restrict__ u) {
+__global__ void moments_kernel(const BoxDev* __restrict__ B, int first, int count, int parity,
+                               double* __restrict__ rho, double* __restrict__ u) {
     typedef typename Prec<P>::S S;
-    const int N = B->N;
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= N) return;
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= count) return;
+    const int p = first + k;
     if (B->btype && B->btype[p]) {  // obstacle node: rho0 and the wall velocity
         const double* uw = B->wall_u + 3 * B->btype[p];
-        if (rho) rho[p] = B->rho0;
+        if (rho) rho[k] = B->rho0;
         if (u) {
-            u[p] = uw[0];
-            u[N + p] = uw[1];
-            u[2 * N + p] = uw[2];
+            u[k] = uw[0];
+            u[count + k] = uw[1];
+            u[2 * count + k] = uw[2];
         }
         return;
     }
@@ -204,11 +206,22 @@ __global__ void moments_kernel(const BoxDev* __restrict__ B, int parity, double*
         jz += cz(i) * d[i];
     }
     const double r = B->rho0 + dr;
-    if (rho) rho[p] = r;
+    if (rho) rho[k] = r;
     if (u) {
-        u[p] = (jx + 0.5 * B->g[0]) / r;
-        u[N + p] = (jy + 0.5 * B->g[1]) / r;
-        u[2 * N + p] = (jz + 0.5 * B->g[2]) / r;
+        u[k] = (jx + 0.5 * B->g[0]) / r;
+        u[count + k] = (jy + 0.5 * B->g[1]) / r;
+        u[2 * count + k] = (jz + 0.5 * B->g[2]) / r;
+    }
+}
+
+// device arrays into a slot of host memory in one launch
+__global__ void __launch_bounds__(256) gather_kernel(GatherSrc src, unsigned* __restrict__ dst) {
+    unsigned base = 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const unsigned* __restrict__ q = (const unsigned*)src.p[a];
+        for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < src.n[a]; i += gridDim.x * 256) dst[base + i] = q[i];
+        base += src.n[a];
     }
 }
 
@@ -306,10 +319,16 @@ hipError_t launch_f64_to_pops(const BoxDev* box_dev, int N, int precision, int p
     return hipGetLastError();
 }
 
-hipError_t launch_moments(const BoxDev* box_dev, int N, int precision, int parity, double* rho,
+hipError_t launch_moments(const BoxDev* box_dev, int first, int count, int precision, int parity, double* rho,
                           double* u, hipStream_t s) {
-    OIF_DISPATCH_P(precision, moments_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), s, box_dev,
-                   parity, rho, u);
+    OIF_DISPATCH_P(precision, moments_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), s, box_dev, first,
+                   count, parity, rho, u);
+    return hipGetLastError();
+}
+
+hipError_t launch_gather(const GatherSrc& src, void* dst, hipStream_t s) {
+    const unsigned n = std::max(src.n[0], std::max(src.n[1], src.n[2]));
+    hipLaunchKernelGGL(gather_kernel, dim3(std::min(256u, (n + 255) / 256)), dim3(256), 0, s, src, (unsigned*)dst);
     return hipGetLastError();
 }
 

@@ -356,7 +356,14 @@ hipError_t launch_pops_to_f64(const BoxDev* box_dev, int N, int precision, int p
                               int deviations, hipStream_t s);
 hipError_t launch_f64_to_pops(const BoxDev* box_dev, int N, int precision, int parity,
                               const double* in, int deviations, hipStream_t s);
-hipError_t launch_moments(const BoxDev* box_dev, int N, int precision, int parity, double* rho,
+// density, or velocity in three runs of `count`, of the nodes first ... first + count - 1
+hipError_t launch_moments(const BoxDev* box_dev, int first, int count, int precision, int parity, double* rho,
                           double* u, hipStream_t s);
+// up to three arrays of 4-byte words, one after the other, into dst
+struct GatherSrc {
+    const void* p[3];
+    unsigned n[3];
+};
+hipError_t launch_gather(const GatherSrc& src, void* dst, hipStream_t s);
 
 }  // namespace oif

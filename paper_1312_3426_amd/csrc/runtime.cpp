@@ -19,6 +19,8 @@
 #include <memory>
 #include <sstream>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -425,6 +427,7 @@ struct oif_ctx {
 
     // diagnostics
     DevBuf part_dev;
+    bool stage_user = false;      // counted among the users of the read-back stages
     double* diag_host = nullptr;  // pinned: the sums and status word of the last diagnostics launch
     double* diag_out = nullptr;   // the same memory by its device address
     void* scratch_addr = nullptr;  // device address of this device's `scratch` array
@@ -521,36 +524,156 @@ void drop_graph(oif_ctx* c) {
     c->g_len = 0;
 }
 
-// Pull the device mesh state into Xh/Vh (absolute coordinates).
-int pull_mesh(oif_ctx* c) {
+// Results go to the host through slots of pinned memory: kernels write a slot
+// while the one before it is taken out (converted, placed) into memory that the
+// host owns: no pageable copy, no allocation per call, one pass on the host.  The
+// velocities of a million lattice nodes took 9.9 ms, 3.9 so.  From 32 MiB on four
+// threads share the work, as one core fills new pages at a few GB/s: 1.28
+// million mesh nodes took 56 ms, 16 with one thread, 6 with four.  Below that
+// one thread: a program's own threads, which often still spin when a read
+// begins, made shared reads slower (32 boxes of 64^3, stepped and read: 37.7 ms
+// with one thread, 47.3 with two).
+// A stage is 4 MiB, allocated on first use; as many exist as reads ran at once
+// (one per device is kept between reads), and they are given back with the last
+// context.
+constexpr size_t STAGE_SLOT = 512u << 10, STAGE_SPLIT = 32u << 20;
+constexpr int STAGE_WORKERS = 4;
+struct Stage {
+    unsigned char *host = nullptr, *dev = nullptr;
+    hipEvent_t ev[2 * STAGE_WORKERS] = {};
+    ~Stage() {
+        for (hipEvent_t e : ev)
+            if (e) (void)hipEventDestroy(e);
+        if (host) (void)hipHostFree(host);
+    }
+};
+std::mutex g_stage_mu;
+int g_stage_users = 0;                                 // contexts
+std::map<int, std::unique_ptr<Stage>> g_stage_kept;    // by device
+
+hipError_t stage_get(int device, std::unique_ptr<Stage>& out) {
+    {
+        std::lock_guard<std::mutex> lock(g_stage_mu);
+        auto it = g_stage_kept.find(device);
+        if (it != g_stage_kept.end()) {
+            out = std::move(it->second);
+            g_stage_kept.erase(it);
+            return hipSuccess;
+        }
+    }
+    std::unique_ptr<Stage> s(new Stage());
+    hipError_t e = hipHostMalloc((void**)&s->host, 2 * STAGE_WORKERS * STAGE_SLOT, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&s->dev, s->host, 0);
+    for (int k = 0; k < 2 * STAGE_WORKERS && e == hipSuccess; ++k)
+        e = hipEventCreateWithFlags(&s->ev[k], hipEventDisableTiming);
+    if (e == hipSuccess) out = std::move(s);
+    return e;
+}
+
+void stage_put(int device, std::unique_ptr<Stage>& s) {
+    std::lock_guard<std::mutex> lock(g_stage_mu);
+    if (!g_stage_kept.count(device)) g_stage_kept[device] = std::move(s);
+}
+
+void stage_users(int d) {
+    std::lock_guard<std::mutex> lock(g_stage_mu);
+    g_stage_users += d;
+    if (!g_stage_users) g_stage_kept.clear();
+}
+
+// `items` results of `item_bytes` each: put(slot, first, n) enqueues on the
+// context's stream what writes n of them to the slot's device address,
+// take(slot, first, n) reads them from its host address; take runs on several
+// threads at once and must not throw.
+template <typename Put, typename Take>
+hipError_t stage_out(oif_ctx* c, size_t items, size_t item_bytes, Put put, Take take) {
+    if (!items) return hipSuccess;
+    std::unique_ptr<Stage> st;
+    hipError_t e = stage_get(c->d.device, st);
+    if (e != hipSuccess) return e;
+    const size_t per = STAGE_SLOT / item_bytes;
+    const int nw = items * item_bytes >= STAGE_SPLIT ? STAGE_WORKERS : 1;
+    hipError_t err[STAGE_WORKERS] = {};
+    auto range = [&](int w) {
+        const size_t lo = items * w / nw, hi = items * (w + 1) / nw;
+        const size_t chunks = (hi - lo + per - 1) / per;
+        hipError_t e = hipSuccess;
+        for (size_t k = 0; k <= chunks && e == hipSuccess; ++k) {
+            if (k < chunks) {  // start chunk k
+                const int slot = 2 * w + (int)(k & 1);
+                const size_t f = lo + k * per;
+                e = put(st->dev + slot * STAGE_SLOT, f, std::min(per, hi - f));
+                if (e == hipSuccess) e = hipEventRecord(st->ev[slot], c->stream);
+            }
+            if (k > 0 && e == hipSuccess) {  // take chunk k - 1
+                const int slot = 2 * w + (int)((k - 1) & 1);
+                const size_t f = lo + (k - 1) * per;
+                e = hipEventSynchronize(st->ev[slot]);
+                if (e == hipSuccess) take(st->host + slot * STAGE_SLOT, f, std::min(per, hi - f));
+            }
+        }
+        err[w] = e;
+    };
+    std::thread th[STAGE_WORKERS];
+    bool own[STAGE_WORKERS] = {};
+    for (int w = 1; w < nw; ++w) {
+        try {
+            th[w] = std::thread([&range, &err, c, w] {
+                err[w] = hipSetDevice(c->d.device);
+                if (err[w] == hipSuccess) range(w);
+            });
+        } catch (const std::system_error&) {
+            own[w] = true;  // no thread to be had: this one does it
+        }
+    }
+    range(0);
+    for (int w = 1; w < nw; ++w) {
+        if (own[w]) range(w);
+        else th[w].join();
+    }
+    for (hipError_t x : err)
+        if (e == hipSuccess) e = x;
+    if (e != hipSuccess) (void)hipStreamSynchronize(c->stream);  // no kernel may write to the slots any more
+    stage_put(c->d.device, st);
+    return e;
+}
+
+// Pull the device mesh state into Xh/Vh (absolute coordinates), and, when it
+// comes from the device, into Xu/Vu where given (all nodes); *done says so.
+int pull_mesh(oif_ctx* c, double* Xu = nullptr, double* Vu = nullptr, bool* done = nullptr) {
     if (!c->host_stale || c->M == 0 || !c->X_dev.p) {
         c->host_stale = false;
         return OIF_OK;
     }
-    const size_t n = 3 * (size_t)c->M;
     const bool verlet = c->integrator == OIF_INTEGRATOR_VERLET && c->F_dev.p;
-    std::vector<double> xl(n), vl(n), fl(verlet ? n : 0);
-    HIPCALL(c, hipMemcpyAsync(xl.data(), c->X_dev.p, n * 8, hipMemcpyDeviceToHost, c->stream));
-    if (is_fp64(c)) {
-        HIPCALL(c, hipMemcpyAsync(vl.data(), c->V_dev.p, n * 8, hipMemcpyDeviceToHost, c->stream));
-        if (verlet) HIPCALL(c, hipMemcpyAsync(fl.data(), c->F_dev.p, n * 8, hipMemcpyDeviceToHost, c->stream));
-        HIPCALL(c, hipStreamSynchronize(c->stream));
-    } else {
-        std::vector<float> vf(n), ff(verlet ? n : 0);
-        HIPCALL(c, hipMemcpyAsync(vf.data(), c->V_dev.p, n * 4, hipMemcpyDeviceToHost, c->stream));
-        if (verlet) HIPCALL(c, hipMemcpyAsync(ff.data(), c->F_dev.p, n * 4, hipMemcpyDeviceToHost, c->stream));
-        HIPCALL(c, hipStreamSynchronize(c->stream));
-        for (size_t i = 0; i < n; ++i) vl[i] = vf[i];
-        for (size_t i = 0; i < ff.size(); ++i) fl[i] = ff[i];
-    }
-    if (verlet) c->Fh = fl;
-    for (const Object& o : c->obj)
-        for (int v = 0; v < o.nv; ++v)
-            for (int k = 0; k < 3; ++k) {
-                const size_t i = 3 * ((size_t)o.off + v) + k;
-                c->Xh[i] = xl[i] + o.anchor[k];
-                c->Vh[i] = vl[i];
-            }
+    const size_t rs = real_size(c->d.precision), node = 24 + (verlet ? 6 : 3) * rs;
+    auto put = [&](unsigned char* slot, size_t first, size_t n) {
+        const GatherSrc g = {{(const char*)c->X_dev.p + 24 * first, (const char*)c->V_dev.p + 3 * rs * first,
+                              verlet ? (const char*)c->F_dev.p + 3 * rs * first : nullptr},
+                             {(unsigned)(6 * n), (unsigned)(3 * rs / 4 * n), verlet ? (unsigned)(3 * rs / 4 * n) : 0u}};
+        return launch_gather(g, slot, c->stream);
+    };
+    auto take = [&](const unsigned char* slot, size_t first, size_t n) {
+        const double* x = (const double*)slot;
+        const unsigned char *v = slot + 24 * n, *f = v + 3 * rs * n;
+        auto widen = [&](const unsigned char* src, double* dst) {
+            if (rs == 8) std::memcpy(dst, src, 24 * n);
+            else
+                for (size_t i = 0; i < 3 * n; ++i) dst[i] = ((const float*)src)[i];
+        };
+        for (const Object& o : c->obj) {
+            const size_t lo = std::max(first, (size_t)o.off), hi = std::min(first + n, (size_t)o.off + o.nv);
+            const double a[3] = {(double)o.anchor[0], (double)o.anchor[1], (double)o.anchor[2]};
+            for (size_t j = lo; j < hi; ++j)
+                for (int k = 0; k < 3; ++k) c->Xh[3 * j + k] = x[3 * (j - first) + k] + a[k];
+        }
+        widen(v, &c->Vh[3 * first]);
+        if (verlet) widen(f, &c->Fh[3 * first]);
+        if (Xu) std::memcpy(Xu + 3 * first, &c->Xh[3 * first], 24 * n);
+        if (Vu) std::memcpy(Vu + 3 * first, &c->Vh[3 * first], 24 * n);
+    };
+    HIPCALL(c, stage_out(c, (size_t)c->M, node, put, take));
+    if (done) *done = true;
     c->host_stale = false;
     return OIF_OK;
 }
@@ -1458,6 +1581,8 @@ int oif_create(const oif_lattice_desc* desc, oif_ctx** out) {
         oif_destroy(c.release());
         return OIF_E_HIP;
     }
+    stage_users(1);
+    cp->stage_user = true;
     *out = c.release();
     return OIF_OK;
 }
@@ -1479,6 +1604,7 @@ int oif_destroy(oif_ctx* c) {
                       &c->rep_node, &c->rep_pos, &c->rep_cell, &c->rep_head, &c->rep_frep, &c->rep_type, &c->rep_shape})
         b->release();
     if (c->diag_host) (void)hipHostFree(c->diag_host);
+    if (c->stage_user) stage_users(-1);
     if (c->own) (void)hipStreamDestroy(c->own);
     if (c->side) (void)hipStreamDestroy(c->side);
     if (c->ev_mark) (void)hipEventDestroy(c->ev_mark);
@@ -1857,8 +1983,9 @@ int oif_read_mesh(oif_ctx* c, int oid, double* X, double* V) {
         int rc = check_obj(c, oid);
         if (rc) return rc;
     }
-    int rc = pull_mesh(c);
-    if (rc) return rc;
+    bool done = false;
+    int rc = oid < 0 ? pull_mesh(c, X, V, &done) : pull_mesh(c);
+    if (rc || done) return rc;
     const size_t off = oid < 0 ? 0 : 3 * (size_t)c->obj[oid].off;
     const size_t n = oid < 0 ? 3 * (size_t)c->M : 3 * (size_t)c->obj[oid].nv;
     if (X && n) std::memcpy(X, &c->Xh[off], n * sizeof(double));
@@ -2151,15 +2278,15 @@ int oif_read_deviations(oif_ctx* c, double* out) { return read_pops(c, out, 1); 
 int oif_write_deviations(oif_ctx* c, const double* in) { return write_pops(c, in, 1); }
 
 static int read_moments(oif_ctx* c, double* rho, double* u) {
-    double* tmp = nullptr;
-    const size_t n = (size_t)c->N * (rho ? 1 : 3);
-    HIPCALL(c, hipMalloc(&tmp, n * 8));
-    hipError_t e = launch_moments(c->box_dev, c->N, c->d.precision, c->parity, rho ? tmp : nullptr,
-                                  rho ? nullptr : tmp, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(rho ? rho : u, tmp, n * 8, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(tmp);
-    HIPCALL(c, e);
+    const size_t N = (size_t)c->N;
+    auto put = [&](unsigned char* slot, size_t first, size_t n) {
+        return launch_moments(c->box_dev, (int)first, (int)n, c->d.precision, c->parity, rho ? (double*)slot : nullptr,
+                              rho ? nullptr : (double*)slot, c->stream);
+    };
+    auto take = [&](const unsigned char* slot, size_t first, size_t n) {
+        for (int k = 0; k < (rho ? 1 : 3); ++k) std::memcpy((rho ? rho : u + k * N) + first, slot + 8 * n * k, 8 * n);
+    };
+    HIPCALL(c, stage_out(c, N, rho ? 8 : 24, put, take));
     return OIF_OK;
 }
 
