@@ -527,8 +527,8 @@ void drop_graph(oif_ctx* c) {
 // Results go to the host through slots of pinned memory: kernels write a slot
 // while the one before it is taken out (converted, placed) into memory that the
 // host owns: no pageable copy, no allocation per call, one pass on the host.  The
-// velocities of a million lattice nodes took 9.9 ms, 3.9 so.  From 32 MiB on four
-// threads share the work, as one core fills new pages at a few GB/s: 1.28
+// velocities of 4.2 million lattice nodes took 9.9 ms, 3.9 so.  From 32 MiB on four
+// threads share the work, as one core fills new pages at a few GB/s: 3.21
 // million mesh nodes took 56 ms, 16 with one thread, 6 with four.  Below that
 // one thread: a program's own threads, which often still spin when a read
 // begins, made shared reads slower (32 boxes of 64^3, stepped and read: 37.7 ms
