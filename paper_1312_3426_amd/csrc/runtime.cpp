@@ -548,8 +548,10 @@ struct Stage {
     }
 };
 std::mutex g_stage_mu;
-int g_stage_users = 0;                                 // contexts
-std::map<int, std::unique_ptr<Stage>> g_stage_kept;    // by device
+int g_stage_users = 0;  // contexts
+// by device; never destroyed itself: when a process ends with contexts left, the
+// GPU runtime may be gone before this library's objects are
+std::map<int, std::unique_ptr<Stage>>& g_stage_kept = *new std::map<int, std::unique_ptr<Stage>>();
 
 hipError_t stage_get(int device, std::unique_ptr<Stage>& out) {
     {
