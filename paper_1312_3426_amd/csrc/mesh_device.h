@@ -147,50 +147,51 @@ __device__ __forceinline__ bool stencil_corner(double px, double py, double pz, 
 }
 
 // Arithmetic of the element forces.  FP64 form: the library's square root and
-// division.  FP32 forms: the hardware's reciprocal and reciprocal square root,
-// refined once (errors below one unit in the last place), without the scaling
-// for denormal and overflowing operands that the correctly rounded sequences
-// carry (10 to 15 instructions each; lengths and areas here are of order one).
-__device__ __forceinline__ double div_r(double a, double b) { return a / b; }
-__device__ __forceinline__ float div_r(float a, float b) {
-    const float r = __builtin_amdgcn_rcpf(b);
-    const float q = a * r;
-    return fmadd(fmadd(-b, q, a), r, q);
+// division.  FP32 forms: FP64 as well (additions, products and their sums run at
+// the FP32 rate of unpacked instructions), rounded to FP32 once where a value is
+// stored.  The hardware's reciprocal and reciprocal square root (good to some
+// 2^-23) are refined once, far below that rounding.  Root mean square error of
+// the FP32 form's force over the nodes, all moduli: 0.49 units of 2^-24 of the
+// force, where correctly rounded FP32 operations give 1.9 and FP32 estimates refined
+// once 2.3; pass of 500 spheres 92.2 ms, with those 92.8 (FP16 storage 59.6, 58.5).
+__device__ __forceinline__ double recip(double x) {
+    const double r = __builtin_amdgcn_rcp(x);
+    return fmadd(r, fmadd(-x, r, 1.0), r);
 }
-__device__ __forceinline__ double rsqrt_r(double x) { return 1.0 / sqrt(x); }
-__device__ __forceinline__ float rsqrt_r(float x) {
-    const float r = __builtin_amdgcn_rsqf(x), h = 0.5f * x * r;
-    return fmadd(r, fmadd(-h, r, 0.5f), r);
+template <typename R>
+__device__ __forceinline__ double rsqrt_of(double x) {
+    if (sizeof(R) == 8) return 1.0 / sqrt(x);
+    const double r = __builtin_amdgcn_rsq(x);
+    return fmadd(r, fmadd(-0.5 * x * r, r, 0.5), r);
 }
-// length L and 1 / L from L^2; L in FP64 in every form (its differences to the
-// relaxed length cancel): two refinements of the FP64 reciprocal square root
+// length L and 1 / L from L^2, both to FP64 in every form (the length's
+// difference to the relaxed one cancels): the estimate refined twice
+template <typename R>
 __device__ __forceinline__ void length_of(double L2, double& L, double& rL) {
-    L = sqrt(L2);
-    rL = 1.0 / L;
-}
-__device__ __forceinline__ void length_of(double L2, double& L, float& rL) {
+    if (sizeof(R) == 8) {
+        L = sqrt(L2);
+        rL = 1.0 / L;
+        return;
+    }
     double r = __builtin_amdgcn_rsq(L2);
-    double h = 0.5 * L2;
+    const double h = 0.5 * L2;
     r = fmadd(r, fmadd(-h * r, r, 0.5), r);
     r = fmadd(r, fmadd(-h * r, r, 0.5), r);
     L = L2 * r;
     L = fmadd(fmadd(-L, L, L2), 0.5 * r, L);
-    rL = (float)r;
+    rL = r;
 }
 // angle of (x, y).  FP32 forms: near the relaxed shape the Taylor series of
 // atan (terms to t^7 leave 7e-9 of t at |t| = 1/8), the library's atan2 beyond
-__device__ __forceinline__ double angle_of(double y, double x) { return atan2(y, x); }
-__device__ __forceinline__ float angle_of(float y, float x) {
-    if (fabsf(y) <= 0.125f * x) {
-        const float t = div_r(y, x), t2 = t * t;
+template <typename R>
+__device__ __forceinline__ R angle_of(double y, double x) {
+    if (sizeof(R) == 8) return atan2(y, x);
+    if (fabs(y) < 0.125 * x) {
+        const float t = (float)(y * recip(x)), t2 = t * t;
         return fmadd(t * t2, fmadd(t2, fmadd(t2, -1.0f / 7.0f, 0.2f), -1.0f / 3.0f), t);
     }
-    return atan2f(y, x);
+    return atan2f((float)y, (float)x);
 }
-
-// x > 0 (a stretch ratio): the square root by the refined reciprocal one
-__device__ __forceinline__ double sqrt_r(double x) { return sqrt(x); }
-__device__ __forceinline__ float sqrt_r(float x) { return x * rsqrt_r(x); }
 
 // Records of a triangle, an edge and a node's corner as loaded (TmplDev), in
 // 16- or 32-bit numbers.
@@ -638,10 +639,8 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
 
     constexpr bool WIDE = !USE_LDS && PH == PH_ALL;  // mesh in the global scratch: 32-bit lists
     const Lists<WIDE> lists_of(T);
-    const R kal = (R)T->kal, ks = (R)T->ks;
+    const double kal = T->kal, ks = T->ks;
     const bool do_s = T->ks != 0.0, do_b = T->kb != 0.0, linear = T->linear != 0;
-    // (S - S0 is formed as (S^2 - S0^2)/(S + S0): the cancelling difference in
-    // FP64 multiply-adds, the square root and division in the arithmetic type)
     auto triangle = [&](int t, const TriRec& q, double r0x, double r0y, double r0z, double& sdarea, double& svol) {
 #pragma clang fp contract(off)
         const double ax = xs[3 * q.a], ay = xs[3 * q.a + 1], az = xs[3 * q.a + 2];
@@ -651,17 +650,18 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         const double ny_ = fmadd(abz, acx, -(abx * acz));
         const double nz_ = fmadd(abx, acy, -(aby * acx));
         const double n2 = fmadd(nx_, nx_, fmadd(ny_, ny_, nz_ * nz_));  // 4 S^2
-        const R rl = rsqrt_r((R)n2);
-        const R S = R(0.5) * (R)n2 * rl;
-        const R dS = div_r((R)fmadd(0.25, n2, -(q.S0 * q.S0)), S + (R)q.S0);
+        double len, rl;
+        length_of<R>(n2, len, rl);
+        const double S = 0.5 * len;
+        const double dS = sizeof(R) == 8 ? fmadd(0.25, n2, -(q.S0 * q.S0)) / (S + q.S0) : S - q.S0;
         if (PH != PH_SUMS) {  // the sums launch keeps the sums only
-            tn[4 * t + 0] = (R)nx_ * rl;
-            tn[4 * t + 1] = (R)ny_ * rl;
-            tn[4 * t + 2] = (R)nz_ * rl;
-            tn[4 * t + 3] = S;
-            tr[t] = -kal * (R(2) * dS * rl);
+            tn[4 * t + 0] = (R)(nx_ * rl);
+            tn[4 * t + 1] = (R)(ny_ * rl);
+            tn[4 * t + 2] = (R)(nz_ * rl);
+            tn[4 * t + 3] = (R)S;
+            tr[t] = (R)(-kal * (2.0 * dS * rl));
         }
-        sdarea = (double)dS;
+        sdarea = dS;
         // signed tetrahedron (node 0, a, b, c): a . N = -6 V for inward N
         svol = fmadd(ax - r0x, nx_, fmadd(ay - r0y, ny_, (az - r0z) * nz_));
     };
@@ -672,21 +672,28 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         const double cx_ = xs[3 * h.C], cy_ = xs[3 * h.C + 1], cz_ = xs[3 * h.C + 2];
         const double dx = cx_ - bx, dy = cy_ - by, dz = cz_ - bz;
         const double L2 = fmadd(dx, dx, fmadd(dy, dy, dz * dz));
-        double L;
-        R rL;
-        length_of(L2, L, rL);
+        double L, rL;
+        length_of<R>(L2, L, rL);
         R s = R(0);
         if (do_s) {
-            // strain (L - L0)/L0 = (L^2 - L0^2) / (L0 (L + L0)); neo-Hookean
-            // kappa = (lam^1/2 + lam^-5/2) / (lam + lam^-3)
-            //       = lam^1/2 (1 + lam^3) / (1 + lam^4)
-            const R strain = div_r((R)fmadd(-h.L0, h.L0, L2), (R)(h.L0 * (L + h.L0)));
-            R kap = R(1);
-            if (!linear) {
-                const R lam = R(1) + strain, l3 = lam * lam * lam;
-                kap = div_r(sqrt_r(lam) * (R(1) + l3), fmadd(l3, lam, R(1)));
+            // neo-Hookean kappa = (lam^1/2 + lam^-5/2) / (lam + lam^-3)
+            //                   = lam^1/2 (1 + lam^3) / (1 + lam^4)
+            double strain, kap = 1.0;
+            if (sizeof(R) == 8) {
+                // (L - L0)/L0 = (L^2 - L0^2) / (L0 (L + L0))
+                strain = fmadd(-h.L0, h.L0, L2) / (h.L0 * (L + h.L0));
+                if (!linear) {
+                    const double lam = 1.0 + strain, l3 = lam * lam * lam;
+                    kap = sqrt(lam) * (1.0 + l3) / fmadd(l3, lam, 1.0);
+                }
+            } else {
+                strain = (L - h.L0) * recip(h.L0);
+                if (!linear) {
+                    const double lam = 1.0 + strain, l3 = lam * lam * lam;
+                    kap = lam * rsqrt_of<R>(lam) * (1.0 + l3) * recip(fmadd(l3, lam, 1.0));
+                }
             }
-            s = ks * kap * strain * rL;
+            s = (R)(ks * kap * strain * rL);
         }
         se[e] = s;
         R* q = fh + (cons ? 4 : 1) * e;
@@ -707,23 +714,19 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         // by |N1| |N2| > 0
         const double sn = L * fmadd(ux, n2x, fmadd(uy, n2y, uz * n2z));
         const double cn = fmadd(n1x, n2x, fmadd(n1y, n2y, n1z * n2z));
-        const R dth = angle_of((R)fmadd(sn, cs.x, -(cn * cs.y)), (R)fmadd(cn, cs.x, sn * cs.y));
+        const R dth = angle_of<R>(fmadd(sn, cs.x, -(cn * cs.y)), fmadd(cn, cs.x, sn * cs.y));
         const R f = (R)kth * dth;
         if (!cons) {
             q[0] = f;
         } else {
             // gradient form: the wing factors w = c / h (c = hbar f, h = |N| / L
-            // the wing's distance from the edge line) and w times the position a
-            // of the wing's foot on the edge, B + a (C - B)
-            const R c = (R)gat(T->hbar, e) * f * (R)L;
-            const R wA = c * rsqrt_r((R)fmadd(n1x, n1x, fmadd(n1y, n1y, n1z * n1z)));
-            const R wD = c * rsqrt_r((R)fmadd(n2x, n2x, fmadd(n2y, n2y, n2z * n2z)));
-            const R aA = (R)(-fmadd(ux, dx, fmadd(uy, dy, uz * dz)) / L2);
-            const R aD = (R)((L2 - fmadd(wx_, dx, fmadd(wy_, dy, wz_ * dz))) / L2);
-            q[0] = wA;
-            q[1] = wD;
-            q[2] = aA * wA;
-            q[3] = aD * wD;
+            // the wing's distance from the edge line) and the positions a of the
+            // wings' feet on the edge, B + a (C - B)
+            const R c = (R)gat(T->hbar, e) * f;
+            q[0] = c * (R)(L * rsqrt_of<R>(fmadd(n1x, n1x, fmadd(n1y, n1y, n1z * n1z))));
+            q[1] = c * (R)(L * rsqrt_of<R>(fmadd(n2x, n2x, fmadd(n2y, n2y, n2z * n2z))));
+            q[2] = (R)(-fmadd(ux, dx, fmadd(uy, dy, uz * dz)) / L2);
+            q[3] = (R)((L2 - fmadd(wx_, dx, fmadd(wy_, dy, wz_ * dz))) / L2);
         }
     };
     if (wave >= cw) {
@@ -808,9 +811,8 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         gst(O.geo, Sg);
         gst(O.geo + 1, Vol);
     }
-    const R cg = (R)(-T->kag * dSg / Sg);             // global area coefficient
-    const R cv = (R)(-T->kv * (Vol - T->V0) / T->V0); // volume coefficient
-    const R cv3 = cv * (R(1) / R(3));
+    const double cg = -T->kag * dSg / Sg;                               // global area coefficient
+    const double cv3 = -T->kv * (Vol - T->V0) / T->V0 * (1.0 / 3.0);   // volume coefficient, a third
 
     // 3. nodes (in the patch launch the patch's nodes are the sub-template's
     // first nn nodes, so xs and the corners take the same index).  The
@@ -820,16 +822,18 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     // that act on v through it: its own wing (edge (a, b)), the shares of the
     // hinges on (v, a) and (b, v), and the volume force.  (Gathering edges,
     // hinges and triangles by three lists read 24 entries of 8 to 16 bytes and
-    // some 150 LDS words per node where the corners take 6 entries of 12 bytes,
-    // a wave's entries contiguous, and some 75 words.  With the shorter
-    // arithmetic of div_r and its kin: launch of 500 spheres of 642 nodes, FP32,
-    // 79.2 -> 72.4 us; FP64, 120 conservative ones 64.2 -> 55.8 us.)
+    // some 150 LDS words per node where the corners take 6 entries of 16 bytes,
+    // a wave's entries contiguous, and some 75 words.  Together with the reciprocals
+    // of recip and its kin in place of division sequences: launch of 500 spheres
+    // of 642 nodes, FP32, 79.2 -> 72.4 us; FP64, 120 conservative ones 64.2 -> 55.8 us.)
     typedef typename Lists<WIDE>::Raw Raw;
     const int rmax = T->rmax;
     R F0x = 0, F0y = 0, F0z = 0;
     for (int i = tid; i < nn; i += bd) {
         const double px = xs[3 * i], py = xs[3 * i + 1], pz = xs[3 * i + 2];
-        R Fx = 0, Fy = 0, Fz = 0;
+        // (a corner's terms are one-sided and much larger than the node's force,
+        // so their sum is FP64 in every form)
+        double Fx = 0, Fy = 0, Fz = 0;
         auto corner = [&](const Raw& raw) {
 #pragma clang fp contract(off)
             const Corner c = Lists<WIDE>::corner(raw);
@@ -840,39 +844,39 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
             // bending: wings along their triangle's normal, edge ends minus
             // half the sum ("Bending force"; conservative model: minus the wing
             // forces split by the positions of the wings' feet)
-            R cn;
+            R bend;
             if (!cons) {
-                cn = fh[c.o] - R(0.5) * (fh[c.ea] + fh[c.eb]);
+                bend = fh[c.o] - R(0.5) * (fh[c.ea] + fh[c.eb]);
             } else {
-                const R* qa = fh + 4 * c.ea;  // v is the edge's B where the triangle is its T1, else C
-                const R* qb = fh + 4 * c.eb;  // v is the edge's C where the triangle is its T1, else B
-                cn = fh[4 * c.o + (c.t2o ? 1 : 0)];
-                cn -= c.t2a ? qa[3] : qa[0] - qa[2];
-                cn -= c.t2b ? qb[1] - qb[3] : qb[2];
+                const R* qa = fh + 4 * c.ea + (c.t2a ? 1 : 0);  // v is the edge's B where the triangle is its T1, else C
+                const R* qb = fh + 4 * c.eb + (c.t2b ? 1 : 0);  // v is the edge's C where the triangle is its T1, else B
+                bend = fh[4 * c.o + (c.t2o ? 1 : 0)];
+                bend = fmadd(c.t2a ? -qa[2] : qa[2] - R(1), qa[0], bend);
+                bend = fmadd(c.t2b ? qb[2] - R(1) : -qb[2], qb[0], bend);
             }
             // volume: -kv dV/V0 S n_out / 3
-            cn = fmadd(-cv3, S, cn);
+            double cn = fmadd(-cv3, (double)S, (double)bend);
             // local area (-kal dS/S w), global area (-kag dSg/Sg w); w = centroid
             // -> vertex over its length (three times it: (v - a) + (v - b)), or
             // (conservative model) over the RMS length of the triangle's three
-            const R wx = (R)(ax + bx), wy = (R)(ay + by), wz = (R)(az + bz);
-            R w2 = fmadd(wx, wx, fmadd(wy, wy, wz * wz));
+            const double wx = ax + bx, wy = ay + by, wz = az + bz;
+            double w2 = fmadd(wx, wx, fmadd(wy, wy, wz * wz));
             if (cons) {
-                const R cx_ = (R)(bx - ax - ax), cy_ = (R)(by - ay - ay), cz_ = (R)(bz - az - az);
-                const R dx = (R)(ax - bx - bx), dy = (R)(ay - by - by), dz = (R)(az - bz - bz);
+                const double cx_ = bx - ax - ax, cy_ = by - ay - ay, cz_ = bz - az - az;
+                const double dx = ax - bx - bx, dy = ay - by - by, dz = az - bz - bz;
                 w2 += fmadd(cx_, cx_, fmadd(cy_, cy_, cz_ * cz_)) + fmadd(dx, dx, fmadd(dy, dy, dz * dz));
-                w2 *= R(1) / R(3);
+                w2 *= 1.0 / 3.0;
             }
-            R ct = (tr[c.t] + cg) * rsqrt_r(w2);
+            double ct = ((double)tr[c.t] + cg) * rsqrt_of<R>(w2);
             // a repeated corner adds nothing (selected, not skipped: without
             // branches the corners' LDS reads overlap)
-            ct = c.valid ? ct : R(0);
-            cn = c.valid ? cn : R(0);
+            ct = c.valid ? ct : 0.0;
+            cn = c.valid ? cn : 0.0;
             s = c.valid ? s : R(0);
             // F_v += ks kappa (L - L0)/L0 (x_a - x_v)/L  ("Stretching force")
-            Fx = fmadd(ct, wx, fmadd(cn, n0, fmadd(-s, (R)ax, Fx)));
-            Fy = fmadd(ct, wy, fmadd(cn, n1, fmadd(-s, (R)ay, Fy)));
-            Fz = fmadd(ct, wz, fmadd(cn, n2, fmadd(-s, (R)az, Fz)));
+            Fx = fmadd(ct, wx, fmadd(cn, (double)n0, fmadd(-(double)s, ax, Fx)));
+            Fy = fmadd(ct, wy, fmadd(cn, (double)n1, fmadd(-(double)s, ay, Fy)));
+            Fz = fmadd(ct, wz, fmadd(cn, (double)n2, fmadd(-(double)s, az, Fz)));
         };
         if (CONS) {
             // (with the conservative terms six corners side by side spill a
@@ -898,14 +902,14 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
 
         // the first node's force stays with its thread
         if (i == tid) {
-            F0x = Fx;
-            F0y = Fy;
-            F0z = Fz;
+            F0x = (R)Fx;
+            F0y = (R)Fy;
+            F0z = (R)Fz;
         } else {
             R* f = O.fel + 3 * node_of(i);
-            gst(f, Fx);
-            gst(f + 1, Fy);
-            gst(f + 2, Fz);
+            gst(f, (R)Fx);
+            gst(f + 1, (R)Fy);
+            gst(f + 2, (R)Fz);
         }
     }
 
@@ -988,9 +992,9 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
                     const int idx = b0 + dz * exy + dy * ex + dx;
                     const uint2 w = pw[idx >> 5];
                     cr[kk] = (int)(w.y + __popc(w.x & ((1u << (idx & 31)) - 1u)));
-                    ujx += wr[kk] * ug[3 * cr[kk]];
-                    ujy += wr[kk] * ug[3 * cr[kk] + 1];
-                    ujz += wr[kk] * ug[3 * cr[kk] + 2];
+                    ujx = fmadd(wr[kk], ug[3 * cr[kk]], ujx);
+                    ujy = fmadd(wr[kk], ug[3 * cr[kk] + 1], ujy);
+                    ujz = fmadd(wr[kk], ug[3 * cr[kk] + 2], ujz);
                 }
                 // eq. dragforce: the fluid receives xi (v - u), the point its opposite
                 dgx = xi * (vx - ujx);
@@ -1030,9 +1034,9 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
                     R ux, uy, uz;
                     ask(qk, raw);
                     velocity(qk, raw, ux, uy, uz);
-                    ujx += wk * ux;
-                    ujy += wk * uy;
-                    ujz += wk * uz;
+                    ujx = fmadd(wk, ux, ujx);
+                    ujy = fmadd(wk, uy, ujy);
+                    ujz = fmadd(wk, uz, ujz);
                 }
                 dgx = xi * (vx - ujx);
                 dgy = xi * (vy - ujy);
@@ -1065,16 +1069,16 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         const R fty = F0y - dgy + O.fext[1] + ry;
         const R ftz = F0z - dgz + O.fext[2] + rz;
         if (O.F) {
-            vx += ftx * half_im;
-            vy += fty * half_im;
-            vz += ftz * half_im;
+            vx = fmadd(ftx, half_im, vx);
+            vy = fmadd(fty, half_im, vy);
+            vz = fmadd(ftz, half_im, vz);
             gst(O.F + 3 * v, ftx);
             gst(O.F + 3 * v + 1, fty);
             gst(O.F + 3 * v + 2, ftz);
         } else {
-            vx += ftx * O.inv_mass;
-            vy += fty * O.inv_mass;
-            vz += ftz * O.inv_mass;
+            vx = fmadd(ftx, O.inv_mass, vx);
+            vy = fmadd(fty, O.inv_mass, vy);
+            vz = fmadd(ftz, O.inv_mass, vz);
         }
         gst(O.V + 3 * v, vx);
         gst(O.V + 3 * v + 1, vy);

@@ -134,8 +134,8 @@ struct TmplDev {
 //             se   stretching coefficient per edge, R [ne]
 //             fh   bending coefficients per edge: R [ne] (the paper's
 //                  magnitude) or R [ne][4] (conservative model: wing
-//                  factors w = c/h_A, c/h_D and a_A w_A, a_D w_D, a the
-//                  feet's positions on the edge)
+//                  factors c/h_A, c/h_D and the feet's positions a_A, a_D
+//                  on the edge)
 //             sums area and volume sums of each 64 triangles, FP64 [..][2]
 //   coupling: gacc summed reaction force at the touched lattice nodes, 8-byte
 //                  accumulators [ccap][3] (FP64 form [ccap][6])
