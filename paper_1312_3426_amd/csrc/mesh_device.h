@@ -393,13 +393,19 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     // the nodes this launch updates: all, or the patch (its sub-template's
     // first nodes; T->order maps them to the object's node numbers)
     const int nsl = SPLIT ? T->nslice : 1;
-    const int n0 = 0;
     const int nn = PH == PH_PATCH ? gld(T->slice_off + 1) : nv;
     auto node_of = [&](int i) -> int { return PH == PH_PATCH ? gld(T->order + i) : i; };
     // the slices' area and volume sums, after the object's mesh layout in its scratch
     double* part = SPLIT ? (double*)(O.scratch + split_part_offset(mesh_layout(sizeof(R), Tp->nv, Tp->nt, Tp->ne,
                                                                                 ucap, ccap, cons, false)))
                          : nullptr;  // [nslice][2]
+    // The staged positions of a split object, in its scratch's forces part: the
+    // sums launch leaves them there (each slice its share of the nodes) and the
+    // patch launch takes them from there.  A patch stages nodes of its neighbours
+    // too, whose workgroups may by then have written their new positions to O.X:
+    // not all patches of an object run at once when a launch has more of them than
+    // the device holds.
+    double* xsplit = SPLIT ? (double*)O.scratch : nullptr;  // [nv of the object][3]
 
     // When the membrane kernel clears G (B->g_by_mesh): the G slots this object
     // added to in the previous step (G[parity ^ 1], which the lattice kernel
@@ -450,12 +456,20 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     // The stencil box is found on the way: each wave's bounds are reduced in
     // its lanes and meet in LDS.
     int blo[3] = {INT_MAX, INT_MAX, INT_MAX}, bhi[3] = {INT_MIN, INT_MIN, INT_MIN};
+    const int x0 = PH == PH_SUMS ? (int)((long long)nv * slice / nsl) : 0;  // the slice's share of xsplit
+    const int x1 = PH == PH_SUMS ? (int)((long long)nv * (slice + 1) / nsl) : 0;
     for (int i = tid; i < nv; i += bd) {
         const int v = PH == PH_PATCH ? gld(T->order + i) : i;
-        const double px = stage(3 * v), py = stage(3 * v + 1), pz = stage(3 * v + 2);
+        auto at = [&](int k) -> double { return PH == PH_PATCH ? gat(xsplit, k) : stage(k); };
+        const double px = at(3 * v), py = at(3 * v + 1), pz = at(3 * v + 2);
         xs[3 * i] = px;
         xs[3 * i + 1] = py;
         xs[3 * i + 2] = pz;
+        if (PH == PH_SUMS && i >= x0 && i < x1) {
+            gst(xsplit + 3 * i, px);
+            gst(xsplit + 3 * i + 1, py);
+            gst(xsplit + 3 * i + 2, pz);
+        }
         if (PH == PH_SUMS || i >= nn) continue;
         int b[3];
         if (stencil_corner(px, py, pz, O.anchor, b)) {
@@ -743,9 +757,8 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
                 velocity(qv[d], raw[d % VDEPTH], uv[d][0], uv[d][1], uv[d][2]);
         }
     } else {
-        // node 0 of the object: the apex of the signed tetrahedra in every launch
-        const double r0x = PH == PH_PATCH ? stage(0) : xs[0], r0y = PH == PH_PATCH ? stage(1) : xs[1],
-                     r0z = PH == PH_PATCH ? stage(2) : xs[2];
+        // node 0 of the object: the apex of the signed tetrahedra (the patch launch sums none)
+        const double r0x = xs[0], r0y = xs[1], r0z = xs[2];
         const int t0 = PH == PH_SUMS ? (int)((long long)nt * slice / nsl) : 0;
         const int t1 = PH == PH_SUMS ? (int)((long long)nt * (slice + 1) / nsl) : nt;
         const int ntc = (t1 - t0 + 63) >> 6;                            // waves of triangles,
@@ -1127,7 +1140,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     }
     // split stepping: the stencils of the new positions, for the next step
     if (mark_next)  // (mark_object begins with a barrier: every new position is written)
-        mark_object(O.X, SPLIT ? T->order + n0 : nullptr, nn, O.anchor, B, ucap, need, sh.bbox,
+        mark_object(O.X, SPLIT ? T->order : nullptr, nn, O.anchor, B, ucap, need, sh.bbox,
                     B->touch[parity ^ 1]);
     if (flags) gatomic_or(B->status, flags);
 }

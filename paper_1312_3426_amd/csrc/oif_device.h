@@ -193,9 +193,11 @@ __host__ __device__ inline size_t sums_lds_bytes(int nv, int nt) {
 // phase a membrane launch runs (all of it, or one of the two split launches)
 enum { PH_ALL = 0, PH_SUMS = 1, PH_PATCH = 2 };
 // LDS of the split launches: the sums launch holds the object's positions
-// (FP64 [nv][3]) and the sums of each 64 triangles of its slice; the patch launch the mesh layout of the patch's
-// sub-template.  The object's scratch: its mesh layout (both parts), then the
-// area and volume sums of each slice (double [nslice][2]).
+// (FP64 [nv][3]) and the sums of each 64 triangles of its slice; the patch
+// launch the mesh layout of the patch's sub-template.  The object's scratch: its
+// mesh layout (both parts), of which the split launches use xs, to hand the
+// staged positions over, then the area and volume sums of each slice
+// (double [nslice][2]).
 __host__ __device__ inline size_t split_part_offset(const MeshLayout& L) { return L.total; }
 
 template <typename real>
