@@ -215,10 +215,13 @@ struct Lists;
 template <>
 struct Lists<false> {
     typedef uint4 Raw;
-    const uint4 *tri, *edge, *ring;
+    const uint4 *tri, *edge, *ring, *rest;
     int rstride;
     template <class TP>
-    __device__ __forceinline__ explicit Lists(TP T) : tri(T->tri16), edge(T->edge16), ring(T->ring16), rstride(T->rstride) {}
+    __device__ __forceinline__ explicit Lists(TP T)
+        : tri(T->tri16), edge(T->edge16), ring(T->ring16), rest(T->rest16), rstride(T->rstride) {}
+    template <typename V>
+    __device__ __forceinline__ static V at(const V* base, int i) { return gat(base, i); }
     __device__ __forceinline__ TriRec triangle(int t) const {
         const uint4 r = gat(tri, t);
         return TriRec{(int)(r.x & 0xffffu), (int)(r.x >> 16), (int)r.y, double_of(r.z, r.w)};
@@ -228,6 +231,7 @@ struct Lists<false> {
         return EdgeRec{(int)(r.x & 0xffffu), (int)(r.x >> 16), (int)(r.y & 0xffffu), (int)(r.y >> 16), double_of(r.z, r.w)};
     }
     __device__ __forceinline__ Raw raw(int j, int v) const { return gat(ring, j * rstride + v); }
+    __device__ __forceinline__ Raw more(int k) const { return gat(rest, k); }
     __device__ __forceinline__ static Corner corner(const Raw& r) {
         return Corner{(int)(r.x & 0xffffu), (int)(r.x >> 16), (int)(r.y & 0xffffu), (int)((r.y >> 16) & 0x7fffu),
                       (int)(r.z & 0x7fffu), (int)((r.z >> 16) & 0x7fffu),
@@ -239,24 +243,26 @@ struct Lists<true> {
     struct Raw {
         int4 p, q;
     };
-    const int4 *tri, *edge, *ring;
+    const int4 *tri, *edge, *ring, *rest;
     const double *S0, *L0;
     int rstride;
     template <class TP>
     __device__ __forceinline__ explicit Lists(TP T)
-        : tri(T->tri32), edge(T->hinge32), ring(T->ring32), S0(T->S0), L0(T->L0), rstride(T->rstride) {}
+        : tri(T->tri32), edge(T->hinge32), ring(T->ring32), rest(T->rest32), S0(T->S0), L0(T->L0), rstride(T->rstride) {}
+    // (64-bit offsets: a mesh that is not in LDS may have arrays beyond 4 GiB)
+    template <typename V>
+    __device__ __forceinline__ static V at(const V* base, int i) { return gld(base + i); }
     __device__ __forceinline__ TriRec triangle(int t) const {
-        const int4 r = gat(tri, t);
-        return TriRec{r.x, r.y, r.z, gat(S0, t)};
+        const int4 r = gld(tri + t);
+        return TriRec{r.x, r.y, r.z, gld(S0 + t)};
     }
     __device__ __forceinline__ EdgeRec hinge(int e) const {
-        const int4 r = gat(edge, e);
-        return EdgeRec{r.x, r.y, r.z, r.w, gat(L0, e)};
+        const int4 r = gld(edge + e);
+        return EdgeRec{r.x, r.y, r.z, r.w, gld(L0 + e)};
     }
-    __device__ __forceinline__ Raw raw(int j, int v) const {
-        const int k = 2 * (j * rstride + v);
-        return Raw{gat(ring, k), gat(ring, k + 1)};
-    }
+    __device__ __forceinline__ Raw pair(const int4* p) const { return Raw{gld(p), gld(p + 1)}; }
+    __device__ __forceinline__ Raw raw(int j, int v) const { return pair(ring + 2 * ((size_t)j * rstride + v)); }
+    __device__ __forceinline__ Raw more(int k) const { return pair(rest + 2 * (size_t)k); }
     __device__ __forceinline__ static Corner corner(const Raw& r) {
         return Corner{r.p.x, r.p.y, r.p.z, r.p.w & 0x7fffffff, r.q.x & 0x7fffffff, r.q.y & 0x7fffffff,
                       r.p.w < 0, r.q.x < 0, r.q.y < 0, r.q.z != 0};
@@ -371,6 +377,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     static_assert(PH != PH_PATCH || (USE_LDS && !CPL), "patch launch: the patch's sub-template in LDS");
     typedef typename Prec<P>::S S;
     typedef typename Prec<P>::R R;
+    typedef Lists<!USE_LDS && PH == PH_ALL> L;  // mesh in the global scratch: 32-bit lists
     const gptr<const TmplDev<R>> Tp = (gptr<const TmplDev<R>>)O.t;  // the object's template
     const gptr<const TmplDev<R>> T = PH == PH_PATCH ? (gptr<const TmplDev<R>>)(Tp->subs + slice) : Tp;
     const gptr<const BoxDev> B = (gptr<const BoxDev>)O.box;
@@ -451,7 +458,8 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     // same bits).
     const R half_im = R(0.5) * O.inv_mass;
     auto stage = [&](int k) -> double {
-        return O.F ? gat(O.X, k) + (double)fmadd(gat(O.F, k), half_im, gat(O.V, k)) : gat(O.X, k);
+        const double x = L::at((const double*)O.X, k);
+        return O.F ? x + (double)fmadd(L::at((const R*)O.F, k), half_im, L::at((const R*)O.V, k)) : x;
     };
     // The stencil box is found on the way: each wave's bounds are reduced in
     // its lanes and meet in LDS.
@@ -651,8 +659,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     R uv[VROUNDS][3];
     const int vt = tid - 64 * cw, vn = 64 * nvw;  // this lane's first touched node, nodes a round
 
-    constexpr bool WIDE = !USE_LDS && PH == PH_ALL;  // mesh in the global scratch: 32-bit lists
-    const Lists<WIDE> lists_of(T);
+    const L lists_of(T);
     const double kal = T->kal, ks = T->ks;
     const bool do_s = T->ks != 0.0, do_b = T->kb != 0.0, linear = T->linear != 0;
     auto triangle = [&](int t, const TriRec& q, double r0x, double r0y, double r0z, double& sdarea, double& svol) {
@@ -736,7 +743,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
             // gradient form: the wing factors w = c / h (c = hbar f, h = |N| / L
             // the wing's distance from the edge line) and the positions a of the
             // wings' feet on the edge, B + a (C - B)
-            const R c = (R)gat(T->hbar, e) * f;
+            const R c = (R)lists_of.at(T->hbar, e) * f;
             q[0] = c * (R)(L * rsqrt_of<R>(fmadd(n1x, n1x, fmadd(n1y, n1y, n1z * n1z))));
             q[1] = c * (R)(L * rsqrt_of<R>(fmadd(n2x, n2x, fmadd(n2y, n2y, n2z * n2z))));
             q[2] = (R)(-fmadd(ux, dx, fmadd(uy, dy, uz * dz)) / L2);
@@ -780,7 +787,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
                 }
             } else {
                 const int e = 64 * (ch - ntc) + lane;
-                if (e < ne) edge(e, lists_of.hinge(e), gat(cs0, e), gat(kth, e));
+                if (e < ne) edge(e, lists_of.hinge(e), lists_of.at(cs0, e), lists_of.at(kth, e));
             }
         }
     }
@@ -839,8 +846,9 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     // a wave's entries contiguous, and some 75 words.  Together with the reciprocals
     // of recip and its kin in place of division sequences: launch of 500 spheres
     // of 642 nodes, FP32, 79.2 -> 72.4 us; FP64, 120 conservative ones 64.2 -> 55.8 us.)
-    typedef typename Lists<WIDE>::Raw Raw;
+    typedef typename L::Raw Raw;
     const int rmax = T->rmax;
+    const int* xoff = T->xoff;
     R F0x = 0, F0y = 0, F0z = 0;
     for (int i = tid; i < nn; i += bd) {
         const double px = xs[3 * i], py = xs[3 * i + 1], pz = xs[3 * i + 2];
@@ -849,7 +857,7 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         double Fx = 0, Fy = 0, Fz = 0;
         auto corner = [&](const Raw& raw) {
 #pragma clang fp contract(off)
-            const Corner c = Lists<WIDE>::corner(raw);
+            const Corner c = L::corner(raw);
             const double ax = px - xs[3 * c.a], ay = py - xs[3 * c.a + 1], az = pz - xs[3 * c.a + 2];
             const double bx = px - xs[3 * c.b], by = py - xs[3 * c.b + 1], bz = pz - xs[3 * c.b + 2];
             R s = se[c.ea];
@@ -910,7 +918,19 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
 #pragma unroll
             for (int j = 0; j < 6; ++j) corner(raw[j]);
             if (rmax > 6) corner(raw[6]);
-            for (int j = 7; j < rmax; ++j) corner(lists_of.raw(j, i));
+        }
+        if (xoff) {  // some node has more than seven corners
+            const int k1 = gld(xoff + i + 1);
+            int k = gld(xoff + i);
+            if (k < k1) {
+                Raw raw = lists_of.more(k);
+#pragma unroll 1
+                for (; k < k1; ++k) {
+                    const Raw cur = raw;
+                    raw = lists_of.more(min(k + 1, k1 - 1));
+                    corner(cur);
+                }
+            }
         }
 
         // the first node's force stays with its thread
@@ -934,12 +954,12 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     R vx = 0, vy = 0, vz = 0;
     auto fetch = [&](int i) {
         const int v = node_of(i);
-        px = gat(O.X, 3 * v);
-        py = gat(O.X, 3 * v + 1);
-        pz = gat(O.X, 3 * v + 2);
-        vx = gat(O.V, 3 * v);
-        vy = gat(O.V, 3 * v + 1);
-        vz = gat(O.V, 3 * v + 2);
+        px = lists_of.at((const double*)O.X, 3 * v);
+        py = lists_of.at((const double*)O.X, 3 * v + 1);
+        pz = lists_of.at((const double*)O.X, 3 * v + 2);
+        vx = lists_of.at((const R*)O.V, 3 * v);
+        vy = lists_of.at((const R*)O.V, 3 * v + 1);
+        vz = lists_of.at((const R*)O.V, 3 * v + 2);
         if (O.F) {  // the half-step velocity, as staged
             vx = fmadd(gld(O.F + 3 * v), half_im, vx);
             vy = fmadd(gld(O.F + 3 * v + 1), half_im, vy);
@@ -978,9 +998,9 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         const int v = node_of(i);
         if (i >= bd) {
             fetch(i);
-            F0x = gat(O.fel, 3 * v);
-            F0y = gat(O.fel, 3 * v + 1);
-            F0z = gat(O.fel, 3 * v + 2);
+            F0x = lists_of.at((const R*)O.fel, 3 * v);
+            F0y = lists_of.at((const R*)O.fel, 3 * v + 1);
+            F0z = lists_of.at((const R*)O.fel, 3 * v + 2);
         }
         R dgx = 0, dgy = 0, dgz = 0;
         int sb[3];

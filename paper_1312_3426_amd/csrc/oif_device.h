@@ -87,23 +87,30 @@ template <typename real>
 struct TmplDev {
     int nv, nt, ne;
     int linear;
-    // Records of the triangles, edges and corners, with node, triangle and
-    // edge numbers in 16 bits where the mesh runs in LDS (they fit then; null
-    // when they do not) and in 32 bits for meshes in the global scratch.
+    // Records of the triangles, edges and corners: with node, triangle and
+    // edge numbers in 16 bits where the launch has the mesh in LDS (they fit
+    // then), in 32 bits for meshes in the global scratch; what no launch reads is
+    // null.
     const uint4* tri16;       // [nt] a | b << 16, c, S0 (FP64: S - S0 cancels near the relaxed shape)
     const int4* tri32;        // [nt] (a, b, c, 0), inward
     const double* S0;         // [nt]
     const uint4* edge16;      // [ne] A | B << 16, C | D << 16, L0 (FP64, as S0)
     const int4* hinge32;      // [ne] (A, B, C, D): T1 = (A, B, C) runs B -> C, T2 has wing D
     const double* L0;         // [ne]
-    // Corners of each node: corner j of node v is entry j * rstride + v (so a
-    // wave reads 64 consecutive entries), j < rmax (at least 6).  A corner is a
-    // triangle (v, a, b) in its order: a, b, the triangle t, and its edges
-    // ea = (v, a), eb = (b, v), o = (a, b), each with its top bit set where the
-    // triangle is the edge's T2.  A node with fewer corners repeats its first
-    // one with the validity word 0.
-    const uint4* ring16;      // a | b << 16, t | ea << 16, eb | o << 16, valid
-    const int4* ring32;       // [..][2]: (a, b, t, ea), (eb, o, valid, 0)
+    // Corners of each node.  The first rmax (6, or 7 where some node has more):
+    // corner j of node v is entry j * rstride + v of the ring, so a wave reads 64
+    // consecutive entries; a node with fewer repeats its first one with the
+    // validity word 0.  The others, of the few nodes that have more than seven:
+    // entries xoff[v] ... xoff[v + 1] - 1 of the rest (xoff null: no such node).
+    // So the table stays linear in the mesh, and only waves that hold such a node
+    // walk more than seven corners: launch of 500 latitude-longitude spheres of 64
+    // meridians and 770 nodes 70 us, 113 with a ring as deep as the poles need.
+    // A corner is a triangle (v, a, b) in its order: a, b, the triangle t, and its
+    // edges ea = (v, a), eb = (b, v), o = (a, b), each with its top bit set where
+    // the triangle is the edge's T2.
+    const uint4 *ring16, *rest16;   // a | b << 16, t | ea << 16, eb | o << 16, valid
+    const int4 *ring32, *rest32;    // [..][2]: (a, b, t, ea), (eb, o, valid, 0)
+    const int* xoff;                // [nodes with corners + 1]
     int rstride, rmax;
     const double* kth;     // [ne] kb / theta0, theta0 the relaxed inner dihedral angle
     const double2* cs0;    // [ne] cos and sin of theta0 - pi (FP64)

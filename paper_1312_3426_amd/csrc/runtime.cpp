@@ -771,12 +771,13 @@ struct TArr {
     std::vector<double> kth, cs0;   // [ne], [ne][2]: kb / theta0; cos, sin of theta0 - pi
     std::vector<double> S0;         // [nt]
     std::vector<double> hbar;       // [ne]
-    // corners (TmplDev::ring32): [rmax][rstride]
+    // corners (TmplDev::ring32, rest32): [rmax][rstride], and those beyond seven
     int rstride = 0, rmax = 0;
-    std::vector<int4> ring;         // two per entry
+    std::vector<int4> ring, rest;   // two per entry
+    std::vector<int> xoff;          // empty: no node has more than seven
     std::vector<int> order, slice_off;
-    // the same records in 16 bits (empty when some number does not fit)
-    std::vector<uint4> tri16, edge16, ring16;
+    // the same records in 16 bits
+    std::vector<uint4> tri16, edge16, ring16, rest16;
 };
 
 // Corner of triangle t at position s3 in device form; nl, tl, el map node,
@@ -795,33 +796,50 @@ void corner_entry(const Template& T, int code, const int* nl, const int* tl, con
     p[1] = make_int4(edge(2), edge(1), 1, 0);
 }
 
-// The 16-bit records from the 32-bit ones.
-void narrow(TArr& A) {
+// The 16-bit records in place of the 32-bit ones (with `all` false the triangles'
+// alone, beside them); the mesh runs in LDS, where its numbers fit.
+void narrow(TArr& A, bool all) {
     auto two = [](int a, int b) { return (unsigned)a | (unsigned)b << 16; };
     auto rec = [](unsigned a, unsigned b, double d) {
         unsigned w[2];
         std::memcpy(w, &d, 8);
         return make_uint4(a, b, w[0], w[1]);
     };
-    if (A.nv > 0xffff) return;
     for (int t = 0; t < A.nt; ++t) A.tri16.push_back(rec(two(A.tri[t].x, A.tri[t].y), (unsigned)A.tri[t].z, A.S0[t]));
-    if (A.nt > 0xffff || A.ne > 0x7fff) return;
+    if (!all) return;
     for (int e = 0; e < A.ne; ++e)
         A.edge16.push_back(rec(two(A.hv[e].x, A.hv[e].y), two(A.hv[e].z, A.hv[e].w), A.L0[e]));
     auto e16 = [](int e) { return ((unsigned)e & 0x7fffu) | (e < 0 ? 0x8000u : 0u); };
-    for (size_t k = 0; k < A.ring.size(); k += 2) {
-        const int4 p = A.ring[k], q = A.ring[k + 1];
-        A.ring16.push_back(make_uint4(two(p.x, p.y), (unsigned)p.z | e16(p.w) << 16, e16(q.x) | e16(q.y) << 16, (unsigned)q.z));
-    }
+    auto corners = [&](std::vector<int4>& from, std::vector<uint4>& to) {
+        for (size_t k = 0; k < from.size(); k += 2) {
+            const int4 p = from[k], q = from[k + 1];
+            to.push_back(make_uint4(two(p.x, p.y), (unsigned)p.z | e16(p.w) << 16, e16(q.x) | e16(q.y) << 16, (unsigned)q.z));
+        }
+        from.clear();
+    };
+    corners(A.ring, A.ring16);
+    corners(A.rest, A.rest16);
+    A.tri.clear();
+    A.hv.clear();
+    A.S0.clear();
+    A.L0.clear();
 }
 
-// Corners of the nodes whose triangles `corners(i)` lists, in wave-sized columns.
+// Corners of the nodes whose triangles `corners(i)` lists.
 template <typename F, typename G>
 void fill_rings(TArr& A, int n, const F& corners, const G& entry) {
+    constexpr int DEPTH = 7;
+    size_t most = 0, beyond = 0;
+    for (int i = 0; i < n; ++i) {
+        const size_t c = corners(i).size();
+        most = std::max(most, c);
+        beyond += c > DEPTH ? c - DEPTH : 0;
+    }
     A.rstride = (n + 63) & ~63;
-    A.rmax = 6;
-    for (int i = 0; i < n; ++i) A.rmax = std::max(A.rmax, (int)corners(i).size());
+    A.rmax = most > 6 ? DEPTH : 6;
     A.ring.assign(2 * (size_t)A.rmax * A.rstride, make_int4(0, 0, 0, 0));
+    A.rest.reserve(2 * beyond);
+    if (beyond) A.xoff.push_back(0);
     for (int i = 0; i < n; ++i) {
         const std::vector<int>& c = corners(i);
         for (int j = 0; j < A.rmax && !c.empty(); ++j) {
@@ -829,6 +847,12 @@ void fill_rings(TArr& A, int n, const F& corners, const G& entry) {
             entry(c[j < (int)c.size() ? j : 0], p);
             if (j >= (int)c.size()) p[1].z = 0;  // repeated, not valid
         }
+        for (size_t j = DEPTH; j < c.size(); ++j) {
+            int4 p[2];
+            entry(c[j], p);
+            A.rest.insert(A.rest.end(), p, p + 2);
+        }
+        if (beyond) A.xoff.push_back((int)(A.rest.size() / 2));
     }
 }
 
@@ -854,7 +878,6 @@ TArr template_arrays(const Template& T) {
                [&](int code, int4* p) { corner_entry(T, code, nullptr, nullptr, nullptr, p); });
     A.order = T.order;
     A.slice_off = T.slice_off;
-    narrow(A);
     return A;
 }
 
@@ -906,7 +929,6 @@ TArr patch_arrays(const Template& T, const TArr& A, int k) {
     fill_rings(P, np, [&](int i) -> const std::vector<int>& { return T.corner[P.order[i]]; },
                [&](int code, int4* p) { corner_entry(T, code, nl.data(), tl.data(), el.data(), p); });
     P.slice_off = {0, np};
-    narrow(P);
     return P;
 }
 
@@ -916,8 +938,8 @@ size_t vbytes(const std::vector<V>& v) {
 }
 
 size_t tarr_bytes(const TArr& A) {
-    return vbytes(A.tri) + vbytes(A.hv) + vbytes(A.ring) + vbytes(A.tri16) + vbytes(A.edge16) + vbytes(A.ring16) +
-           vbytes(A.L0) + vbytes(A.kth) + vbytes(A.cs0) + vbytes(A.S0) + vbytes(A.hbar) + vbytes(A.order) +
+    return vbytes(A.tri) + vbytes(A.hv) + vbytes(A.ring) + vbytes(A.rest) + vbytes(A.tri16) + vbytes(A.edge16) +
+           vbytes(A.ring16) + vbytes(A.rest16) + vbytes(A.xoff) + vbytes(A.L0) + vbytes(A.kth) + vbytes(A.cs0) + vbytes(A.S0) + vbytes(A.hbar) + vbytes(A.order) +
            vbytes(A.slice_off);
 }
 
@@ -927,7 +949,8 @@ template <typename real>
 void tarr_place(const TArr& A, unsigned char* host, unsigned char* dev, TmplDev<real>& D) {
     size_t off = 0;
     auto put = [&](const auto& v) -> const void* {
-        if (!v.empty()) std::memcpy(host + off, v.data(), v.size() * sizeof(v[0]));
+        if (v.empty()) return nullptr;
+        std::memcpy(host + off, v.data(), v.size() * sizeof(v[0]));
         const void* p = dev + off;
         off += vbytes(v);
         return p;
@@ -940,9 +963,12 @@ void tarr_place(const TArr& A, unsigned char* host, unsigned char* dev, TmplDev<
     D.tri32 = (const int4*)put(A.tri);
     D.hinge32 = (const int4*)put(A.hv);
     D.ring32 = (const int4*)put(A.ring);
+    D.rest32 = (const int4*)put(A.rest);
     D.tri16 = (const uint4*)put(A.tri16);
     D.edge16 = (const uint4*)put(A.edge16);
     D.ring16 = (const uint4*)put(A.ring16);
+    D.rest16 = (const uint4*)put(A.rest16);
+    D.xoff = (const int*)put(A.xoff);
     D.L0 = (const double*)put(A.L0);
     D.kth = (const double*)put(A.kth);
     D.cs0 = (const double2*)put(A.cs0);
@@ -979,6 +1005,17 @@ size_t split_need_bytes(int precision, const Template& T) {
         need = std::max(need, mesh_lds_bytes(precision, T.pnv[k], T.pnt[k], T.pne[k], T.ucap, T.ccap,
                                              tmpl_conservative(T)));
     return need;
+}
+
+// The launch group of a template's objects with `budget` bytes of LDS: 0 meshes
+// staged in LDS whole, 1 split over several workgroups (positions, slice forces
+// and coupling area in LDS, element arrays of a patch in LDS), 2 in the global
+// scratch with their coupling area in LDS, 3 entirely in the scratch.
+int mesh_group(int precision, const Template& T, size_t budget) {
+    const int cons = tmpl_conservative(T);
+    if (mesh_lds_bytes(precision, T.nv, T.nt, T.ne, T.ucap, T.ccap, cons) <= budget) return 0;
+    if (split_need_bytes(precision, T) <= budget) return 1;
+    return mesh_cpl_lds_bytes(precision, T.nv, T.nt, T.ne, T.ucap, T.ccap, cons) <= budget ? 2 : 3;
 }
 
 // Where each object is: the strip in z, the strip in y and the place in x of its
@@ -1031,7 +1068,7 @@ int upload_mesh_t(oif_ctx* c) {
     std::vector<TmplDev<real>> td(c->tmpl.size());
     for (size_t t = 0; t < c->tmpl.size(); ++t) {
         Template& T = c->tmpl[t];
-        const TArr A = template_arrays(T);
+        TArr A = template_arrays(T);
         std::vector<TArr> pa;
         if (T.nslice > 1)
             for (int k = 0; k < T.nslice; ++k) pa.push_back(patch_arrays(T, A, k));
@@ -1043,6 +1080,13 @@ int upload_mesh_t(oif_ctx* c) {
             T.pnt.push_back(P.nt);
             T.pne.push_back(P.ne);
         }
+        // what the group's launches read: 16-bit records in LDS, the triangles'
+        // and the patches' for a split mesh (and its 32-bit ones, which the
+        // persistent batch form runs whole), 32-bit ones in the scratch
+        const int g = mesh_group(c->d.precision, T, c->max_lds);
+        if (g != 1) pa.clear();
+        if (g <= 1) narrow(A, g == 0);
+        for (TArr& P : pa) narrow(P, true);
         // one allocation: the template's arrays, each patch's arrays, then the
         // patches' descriptors; sub-arrays 16-byte aligned
         size_t total = 0;
@@ -1102,12 +1146,8 @@ int upload_mesh_t(oif_ctx* c) {
     HIPCALL(c, hipMemcpy(c->X_dev.p, xl.data(), n * sizeof(double), hipMemcpyHostToDevice));
     HIPCALL(c, hipMemcpy(c->V_dev.p, vl.data(), n * sizeof(real), hipMemcpyHostToDevice));
 
-    // objects in four groups, each launched on its own and sorted largest
-    // mesh first: meshes staged in LDS whole; meshes split over several
-    // workgroups (positions, slice forces and coupling area in LDS, element
-    // arrays in the scratch); meshes in the global scratch whose coupling area
-    // fits in LDS; meshes entirely in the scratch
-    const size_t budget = c->max_lds;
+    // objects in four groups (mesh_group), each launched on its own and sorted
+    // largest mesh first
     std::vector<int> order(c->obj.size());
     for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
     auto need = [&](int i) {
@@ -1119,9 +1159,7 @@ int upload_mesh_t(oif_ctx* c) {
         return mesh_cpl_lds_bytes(c->d.precision, T.nv, T.nt, T.ne, T.ucap, T.ccap, tmpl_conservative(T));
     };
     auto split = [&](int i) { return split_need_bytes(c->d.precision, c->tmpl[c->obj[i].tid]); };
-    auto group = [&](int i) {
-        return need(i) <= budget ? 0 : (split(i) <= budget ? 1 : (cpl(i) <= budget ? 2 : 3));
-    };
+    auto group = [&](int i) { return mesh_group(c->d.precision, c->tmpl[c->obj[i].tid], c->max_lds); };
     // scratch of an object outside LDS: the mesh layout, then the slices' sums
     auto scratch_bytes = [&](int i) {
         const Template& T = c->tmpl[c->obj[i].tid];

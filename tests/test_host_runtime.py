@@ -1,0 +1,65 @@
+"""Host code of the runtime (liboif.so) on the CPU, against a stand-in for the HIP runtime (fake_hip.cpp): what it
+allocates, which device and which threads' captures it depends on, and how it hands results over.  Each test runs in a
+child process, which loads the stand-in ahead of the real runtime."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+HEAD = """
+import ctypes, os, sys, time
+fake = ctypes.CDLL({fake!r}, mode=os.RTLD_NOW | os.RTLD_GLOBAL)
+sys.path[:0] = [{root!r}, {here!r}]
+import numpy as np
+from paper_1312_3426_amd import oif, synth
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    from paper_1312_3426_amd import oif
+    if not os.path.exists(oif.LIB_PATH):
+        pytest.fail("liboif.so is not built")
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run([gxx, "-std=c++17", "-O1", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(HERE, "fake_hip.cpp"), "-o", so], check=True)
+    return so
+
+
+def run(fake, script):
+    r = subprocess.run([sys.executable, "-u", "-c", HEAD.format(fake=fake, root=ROOT, here=HERE) + script],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+@pytest.mark.parametrize("sides", [500, 3000])  # in LDS, in the global scratch
+def test_corner_table_is_linear_in_the_mesh(fake, sides):
+    """A node that all triangles of its half of the mesh share: the device arrays grow with the nodes, some hundred
+    bytes each, not with their number times the largest count of corners."""
+    run(fake, f"""
+from test_gpu_corner_tables import bipyramid
+nodes, tris = bipyramid({sides})
+box = synth.Box(24, 24, 24, templates=[synth.Template(nodes, tris)], objects=[])
+def bytes_of(objects):
+    box.objects = [synth.ObjectSpec(0, np.array([12.0, 12.0, 12.0]))] * objects
+    c = oif.Context.from_box(box, precision="fp32")
+    c.step(1)
+    n = c.info().device_bytes
+    c.close()
+    return n
+box.templates, t = [synth.Template(*synth.tetrahedron(4.0))], box.templates
+small = bytes_of(1)
+box.templates = t
+grown = bytes_of(1) - small
+# per node: two corners in a ring of seven (32 bytes each), edges, triangles, state; the rest is per box
+assert grown < 1000 * len(nodes) + (1 << 20), (grown, len(nodes))
+""")
