@@ -13,13 +13,13 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <fstream>
 #include <functional>
 #include <map>
 #include <memory>
 #include <sstream>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <unordered_map>
 #include <vector>
@@ -583,6 +583,20 @@ void stage_users(int d) {
     if (!g_stage_users) g_stage_kept.clear();
 }
 
+// The context's device as the calling thread's current one, as kernels on the
+// context's stream and events of the slots need, until the end of the scope.
+struct OnDevice {
+    int before = -1;
+    hipError_t err;
+    explicit OnDevice(int device) : err(hipGetDevice(&before)) {
+        if (err != hipSuccess || before == device) before = -1;
+        else err = hipSetDevice(device);
+    }
+    ~OnDevice() {
+        if (before >= 0) (void)hipSetDevice(before);
+    }
+};
+
 // `items` results of `item_bytes` each: put(slot, first, n) enqueues on the
 // context's stream what writes n of them to the slot's device address,
 // take(slot, first, n) reads them from its host address; take runs on several
@@ -590,8 +604,9 @@ void stage_users(int d) {
 template <typename Put, typename Take>
 hipError_t stage_out(oif_ctx* c, size_t items, size_t item_bytes, Put put, Take take) {
     if (!items) return hipSuccess;
+    const OnDevice on(c->d.device);
     std::unique_ptr<Stage> st;
-    hipError_t e = stage_get(c->d.device, st);
+    hipError_t e = on.err == hipSuccess ? stage_get(c->d.device, st) : on.err;
     if (e != hipSuccess) return e;
     const size_t per = STAGE_SLOT / item_bytes;
     const int nw = items * item_bytes >= STAGE_SPLIT ? STAGE_WORKERS : 1;
@@ -624,7 +639,7 @@ hipError_t stage_out(oif_ctx* c, size_t items, size_t item_bytes, Put put, Take 
                 err[w] = hipSetDevice(c->d.device);
                 if (err[w] == hipSuccess) range(w);
             });
-        } catch (const std::system_error&) {
+        } catch (const std::exception&) {
             own[w] = true;  // no thread to be had: this one does it
         }
     }
@@ -635,8 +650,8 @@ hipError_t stage_out(oif_ctx* c, size_t items, size_t item_bytes, Put put, Take 
     }
     for (hipError_t x : err)
         if (e == hipSuccess) e = x;
-    if (e != hipSuccess) (void)hipStreamSynchronize(c->stream);  // no kernel may write to the slots any more
-    stage_put(c->d.device, st);
+    if (e == hipSuccess) stage_put(c->d.device, st);
+    else (void)hipStreamSynchronize(c->stream);  // no kernel may write to the slots any more; they are given back
     return e;
 }
 

@@ -1,8 +1,7 @@
 // A stand-in for the HIP runtime calls that liboif.so makes, for tests of its host code without a GPU: two devices
 // whose memory is host memory, no kernel run but the one that hands results to the host.  It enforces what the real
-// one does about devices (a kernel launch needs the stream's device current, an event belongs to the device it was
-// created on) and about captures in other threads (allocations are refused, unless the calling thread's capture mode
-// is relaxed).  Loaded ahead of the real runtime with RTLD_GLOBAL.
+// one does about devices: a kernel launch needs the stream's device current, an event belongs to the device it was
+// created on.  Loaded ahead of the real runtime with RTLD_GLOBAL.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdlib>
@@ -15,18 +14,9 @@ struct ihipEvent_t { int device; };
 
 namespace {
 thread_local int current = 0;
-thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
-bool capturing = false;  // a thread other than the caller's captures in the global mode
-int refused = 0;         // calls that would have ended that capture
 std::map<const void*, std::string> kernels;
 std::map<const void*, char*> vars;
-bool in_capture() {
-    if (!capturing || mode == hipStreamCaptureModeRelaxed) return false;
-    ++refused;
-    return true;
-}
 hipError_t get(void** p, size_t n) {
-    if (in_capture()) return hipErrorStreamCaptureUnsupported;
     *p = std::aligned_alloc(256, (n + 255) / 256 * 256 + 256);
     if (!*p) return hipErrorOutOfMemory;
     std::memset(*p, 0, n);
@@ -43,8 +33,6 @@ struct Gather {  // GatherSrc of oif_device.h
 }  // namespace
 
 extern "C" {
-void fake_capture(int on) { capturing = on != 0; }
-int fake_refused() { return refused; }
 int fake_current() { return current; }
 void fake_set_current(int d) { current = d; }
 
@@ -64,10 +52,6 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = new ihipStr
 hipError_t hipStreamDestroy(hipStream_t s) { delete s; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
-    std::swap(*m, mode);
-    return hipSuccess;
-}
 hipError_t hipEventCreate(hipEvent_t* e) { return event(e); }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return event(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { delete e; return hipSuccess; }

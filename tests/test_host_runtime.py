@@ -1,6 +1,6 @@
 """Host code of the runtime (liboif.so) on the CPU, against a stand-in for the HIP runtime (fake_hip.cpp): what it
-allocates, which device and which threads' captures it depends on, and how it hands results over.  Each test runs in a
-child process, which loads the stand-in ahead of the real runtime."""
+allocates, which device it works on, and how it hands results over.  Each test runs in a child process, which loads
+the stand-in ahead of the real runtime."""
 import os
 import shutil
 import subprocess
@@ -62,4 +62,24 @@ box.templates = t
 grown = bytes_of(1) - small
 # per node: two corners in a ring of seven (32 bytes each), edges, triangles, state; the rest is per box
 assert grown < 1000 * len(nodes) + (1 << 20), (grown, len(nodes))
+""")
+
+
+@pytest.mark.parametrize("what", ["read_mesh", "read_velocity", "read_density"])
+def test_reads_do_not_depend_on_the_current_device(fake, what):
+    """One thread with contexts on two devices reads from both, whichever device is current, and finds its own device
+    current afterwards."""
+    run(fake, f"""
+boxes = [synth.Box(16, 16, 16, templates=[synth.Template(*synth.tetrahedron(4.0))],
+                   objects=[synth.ObjectSpec(0, np.array([8.0, 8.0, 8.0]))]) for _ in range(2)]
+ctxs = [oif.Context.from_box(b, precision="fp32", device=d) for d, b in enumerate(boxes)]
+for order in ((0, 1), (1, 0)):
+    for d, c in enumerate(ctxs):
+        fake.fake_set_current(d)
+        c.step(1)
+    for current in (0, 1):
+        fake.fake_set_current(current)
+        for d in order:
+            getattr(ctxs[d], {what!r})()
+            assert fake.fake_current() == current
 """)
