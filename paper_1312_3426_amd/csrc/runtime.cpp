@@ -678,7 +678,11 @@ int pull_mesh(oif_ctx* c, double* Xu = nullptr, double* Vu = nullptr, bool* done
             else
                 for (size_t i = 0; i < 3 * n; ++i) dst[i] = ((const float*)src)[i];
         };
-        for (const Object& o : c->obj) {
+        // (the objects' nodes follow one another: from the one that holds `first`)
+        auto it = std::upper_bound(c->obj.begin(), c->obj.end(), first,
+                                   [](size_t f, const Object& o) { return f < (size_t)o.off + o.nv; });
+        for (; it != c->obj.end() && (size_t)it->off < first + n; ++it) {
+            const Object& o = *it;
             const size_t lo = std::max(first, (size_t)o.off), hi = std::min(first + n, (size_t)o.off + o.nv);
             const double a[3] = {(double)o.anchor[0], (double)o.anchor[1], (double)o.anchor[2]};
             for (size_t j = lo; j < hi; ++j)
