@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <array>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -410,6 +411,7 @@ struct oif_ctx {
     int n_split_obj = 0;        // the next n_split_obj run split over several workgroups each
     int n_cpl_obj = 0;          // the next n_cpl_obj keep their coupling area in LDS
     size_t lds_need = 0;
+    int lds_nv = 0;             // nodes of the largest mesh in LDS
     size_t split_need = 0;      // LDS per workgroup of the split launches
     size_t cpl_need = 0;        // LDS for the coupling area of the CPL objects
     DevBuf split_work;          // (object, slice) per workgroup of the split launches
@@ -470,6 +472,7 @@ struct oif_batch {
     // (obstacles, MRT collision): one launch per group
     int var_off[5] = {0, 0, 0, 0, 0};
     size_t lds_need = 0;
+    int lds_nv = 0;
     size_t cpl_need = 0;
     int any_conservative = 0;
     int lb_block = 256, mesh_block = 0, remap = 1;
@@ -1206,6 +1209,7 @@ int upload_mesh_t(oif_ctx* c) {
     c->n_split_obj = 0;
     c->n_cpl_obj = 0;
     c->lds_need = 0;
+    c->lds_nv = 0;
     c->split_need = 0;
     c->cpl_need = 0;
     c->any_conservative = 0;
@@ -1219,6 +1223,7 @@ int upload_mesh_t(oif_ctx* c) {
         if (g == 0) {
             ++c->n_lds_obj;
             c->lds_need = std::max(c->lds_need, need(i));
+            c->lds_nv = std::max(c->lds_nv, c->obj[i].nv);
         } else {
             scratch_total += scratch_bytes(i);
             if (g == 1) {
@@ -1323,29 +1328,32 @@ inline void rec(hipEvent_t e, hipStream_t s) {
 
 // Threads of a membrane workgroup when none are set: the waves a compute unit
 // holds of this kernel (24 with its 80 registers, 16 in the FP64 form) shared
-// among the workgroups it gets, between 512 and 1024 threads.  It gets as many
-// as its LDS holds, or fewer when the launch has fewer.  Measured (us, FP32
-// unless said): 1 sphere of 642 nodes 1024 threads 23.3, 768 24.0, 256 36.2; 200
-// of them 28.2, 29.3, 42.4; 2000 (two to a unit) 768 183.5, 512 197.8, 1024
-// 225.6, 256 236.8; 2000 cells of 393 (three) 512 129.1, 768 138.7, 256 151.9;
-// FP64 500 spheres of 642 (one) 1024 76.5, 512 88.6; 500 cells of 393 (two) 512
-// 47.4, 768 56.4.  Below 512 the phases of a small mesh get longer than the
-// extra workgroups gain (2000 spheres of 162 nodes: 256 123.8, 512 127.4; FP64
-// 213, 190).
-int membrane_block(int set, int precision, size_t lds_bytes, int nwg, int n_cu) {
+// among the workgroups it gets, at most 1024 threads.  It gets as many as its LDS
+// holds (160 KB on gfx950, the only device a context is made for), or fewer when
+// the launch has fewer.  Measured (us, FP32 unless said): 1 sphere of 642 nodes
+// 1024 threads 23.3, 768 24.0, 256 36.2; 500 (one or two to a unit) 768 57.2, 512
+// 60.0, 1024 69.6; 2000 768 176.5, 512 194.2, 1024 229.3, 256 238.8; 2000 cells
+// of 393 (three) 512 111.1, 768 122.8, 256 114.6; FP64 500 spheres of 642 (one)
+// 1024 85.9, 512 100.0; 500 cells of 393 (two) 512 51.6, 768 60.6.
+// Where the share is small, no fewer than the launch's largest mesh, of `nv`
+// nodes, has work for: 512 threads, up to 256 nodes 256, up to 64 nodes 128.
+// 6000 spheres of 162 nodes: 256 146.8, 128 153.1, 512 198.7 (FP64 193, 210, 244;
+// 2000 of radius 4, which touch more of the lattice: 118.1, 148.4, 129.9); 20000
+// of 42 nodes: 128 192, 64 193, 256 260, 512 437; 20000 of 4 nodes: 113, 89, 167, 344.
+int membrane_block(int set, int precision, size_t lds_bytes, int nwg, int n_cu, int nv) {
     if (set > 0) return set;
-    const int waves = precision == OIF_PREC_FP64 ? 16 : 24;
+    const int waves = precision == OIF_PREC_FP64 ? 16 : 24, least = nv <= 64 ? 2 : (nv <= 256 ? 4 : 8);
     const int fit = lds_bytes ? std::max(1, (int)(163840 / (lds_bytes + 1024))) : waves;
     const int per_cu = std::max(1, std::min(fit, (nwg + n_cu - 1) / n_cu));
-    return 64 * std::min(16, std::max(8, waves / per_cu));
+    return 64 * std::min(16, std::max(least, waves / per_cu));
 }
 
 // The membrane workgroup size of the context's first launch group.
 int first_membrane_block(const oif_ctx* c) {
     if (c->n_lds_obj || (!c->n_split_obj && !c->n_cpl_obj))
-        return membrane_block(c->mesh_block, c->d.precision, c->lds_need, c->n_lds_obj, c->n_cu);
-    return c->n_split_obj ? membrane_block(c->mesh_block, c->d.precision, c->split_need, c->n_split_work, c->n_cu)
-                          : membrane_block(c->mesh_block, c->d.precision, c->cpl_need, c->n_cpl_obj, c->n_cu);
+        return membrane_block(c->mesh_block, c->d.precision, c->lds_need, c->n_lds_obj, c->n_cu, c->lds_nv);
+    return c->n_split_obj ? membrane_block(c->mesh_block, c->d.precision, c->split_need, c->n_split_work, c->n_cu, INT_MAX)
+                          : membrane_block(c->mesh_block, c->d.precision, c->cpl_need, c->n_cpl_obj, c->n_cu, INT_MAX);
 }
 
 int enqueue_mesh(oif_ctx* c, int par, hipStream_t s, int mark_next) {
@@ -1354,7 +1362,9 @@ int enqueue_mesh(oif_ctx* c, int par, hipStream_t s, int mark_next) {
         HIPCALL(c, launch_repulsion(c->rep_h, (const RepDev*)c->rep_desc.p, c->obj_dev.p, (int)c->obj.size(),
                                     c->rep_max_nv, par, c->d.precision, s));
     MeshLaunch ml{};
-    auto block = [&](size_t lds, int nwg) { return membrane_block(c->mesh_block, c->d.precision, lds, nwg, c->n_cu); };
+    auto block = [&](size_t lds, int nwg, int nv = INT_MAX) {
+        return membrane_block(c->mesh_block, c->d.precision, lds, nwg, c->n_cu, nv);
+    };
     ml.parity = par;
     ml.mark_next = mark_next;
     ml.conservative = c->any_conservative;
@@ -1365,7 +1375,7 @@ int enqueue_mesh(oif_ctx* c, int par, hipStream_t s, int mark_next) {
         ml.objs = c->obj_dev.p;
         ml.nobj = c->n_lds_obj;
         ml.lds_bytes = c->lds_need;
-        ml.block = block(ml.lds_bytes, ml.nobj);
+        ml.block = block(ml.lds_bytes, ml.nobj, c->lds_nv);
         HIPCALL(c, launch_mesh(ml));
     }
     if (c->n_split_obj > 0) {
@@ -2842,6 +2852,7 @@ int batch_build(oif_batch* b) {
     b->n_split_obj = 0;
     b->n_cpl_obj = 0;
     b->lds_need = 0;
+    b->lds_nv = 0;
     b->split_need = 0;
     b->cpl_need = 0;
     b->p_cpl_need = 0;
@@ -2856,6 +2867,7 @@ int batch_build(oif_batch* b) {
         if (ents[k].group == 0) {
             ++b->n_lds_obj;
             b->lds_need = std::max(b->lds_need, ents[k].need);
+            b->lds_nv = std::max(b->lds_nv, ents[k].nv);
         } else if (ents[k].group == 1) {
             for (int sl = 0; sl < ents[k].nslice; ++sl) sw.push_back(make_int2(b->n_split_obj, sl));
             ++b->n_split_obj;
@@ -2986,7 +2998,9 @@ int batch_enqueue(oif_batch* b, int n, int parity0, hipStream_t s, std::vector<h
         }
         MeshLaunch ml{};
         const int n_cu = b->ctx[0]->n_cu;
-        auto block = [&](size_t lds, int nwg) { return membrane_block(b->mesh_block, b->precision, lds, nwg, n_cu); };
+        auto block = [&](size_t lds, int nwg, int nv = INT_MAX) {
+            return membrane_block(b->mesh_block, b->precision, lds, nwg, n_cu, nv);
+        };
         ml.parity = par;
         ml.precision = b->precision;
         ml.conservative = b->any_conservative;
@@ -2996,7 +3010,7 @@ int batch_enqueue(oif_batch* b, int n, int parity0, hipStream_t s, std::vector<h
             ml.objs = b->obj_dev.p;
             ml.nobj = b->n_lds_obj;
             ml.lds_bytes = b->lds_need;
-            ml.block = block(ml.lds_bytes, ml.nobj);
+            ml.block = block(ml.lds_bytes, ml.nobj, b->lds_nv);
             BHIP(b, launch_mesh(ml));
         }
         if (b->n_split_obj > 0) {

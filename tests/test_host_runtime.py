@@ -107,3 +107,20 @@ small, large = timed(synth.tetrahedron(2.0), 400000), timed(synth.icosphere(3, 2
 print(small, large)
 assert small < 3 * large, (small, large)
 """)
+
+
+@pytest.mark.parametrize("level,count,prec,threads", [(0, 6000, "fp32", 128), (1, 6000, "fp64", 128), (2, 6000, "fp32", 256),
+                                                      (2, 6000, "fp64", 256), (2, 500, "fp32", 768), (3, 500, "fp32", 768),
+                                                      (3, 4000, "fp32", 768), (3, 1, "fp64", 1024)])
+def test_default_workgroup_of_the_membranes(fake, level, count, prec, threads):
+    """Spheres of 12 to 642 nodes: few to a compute unit share its waves; of many, each gets what its mesh has work
+    for, or a launch of thousands of small meshes is slowed down by waves without any."""
+    run(fake, f"""
+box = synth.Box(16, 16, 16, templates=[synth.Template(*synth.icosphere({level}, {(1.5, 1.8, 2.0, 4.0)[level]}))],
+                objects=[synth.ObjectSpec(0, np.array([8.0, 8.0, 8.0]))] * {count})
+c = oif.Context.from_box(box, precision={prec!r})
+c.step(1)
+assert c.info().mesh_block == {threads}, c.info().mesh_block
+c.set_launch(-1, 320, -1)
+assert c.info().mesh_block == 320
+""")
