@@ -46,7 +46,7 @@ lb_kernel(const BoxDev* __restrict__ boxes, const int2* __restrict__ work, int n
 }
 
 // The sums of a state in one launch: blocks below `nlat` take lattice nodes,
-// each of the others one object, and the last block to end adds the partials
+// each of the others `per` objects, and the last block to end adds the partials
 // up and writes the ten totals and the status word to host memory.  Every sum
 // has a fixed order (a thread's nodes in turn, a tree over the wave, the waves
 // in turn; the partials likewise), so which block comes last does not show in
@@ -54,11 +54,13 @@ lb_kernel(const BoxDev* __restrict__ boxes, const int2* __restrict__ work, int n
 // it is one launch: a call takes 23 us at half a million nodes (12 of them the
 // kernel), as three kernels and two copies 50.  1024 threads per block: sixteen
 // waves per compute unit keep enough population loads in flight over the
-// grid-stride loop.
+// grid-stride loop.  Objects share blocks where there are too many for blocks of
+// their own to start together: 20000 meshes of 42 nodes in four million lattice nodes
+// 80 us a call, 314 with a block each.
 template <int P>
 __global__ void __launch_bounds__(1024)
 diag_kernel(const BoxDev* __restrict__ B, const ObjDev<typename Prec<P>::R>* __restrict__ objs, int nlat, int nobj,
-            int parity, double* part, double* out) {
+            int per, int parity, double* part, double* out) {
     typedef typename Prec<P>::S S;
     __shared__ double red[5][16];
     __shared__ bool last;
@@ -84,10 +86,10 @@ diag_kernel(const BoxDev* __restrict__ B, const ObjDev<typename Prec<P>::R>* __r
                 s[3] += cz(i) * d[i];
             }
         }
-    } else {
-        const ObjDev<typename Prec<P>::R>& O = objs[blk - nlat];
+    } else if (const int w = 16 / per, o = (blk - nlat) * per + wave / w; o < nobj) {  // w waves an object
+        const ObjDev<typename Prec<P>::R>& O = objs[o];
         const int nv = O.t->nv;
-        for (int v = t; v < nv; v += 1024) {
+        for (int v = (wave % w) * 64 + (t & 63); v < nv; v += 64 * w) {
             const double a = O.V[3 * v], b = O.V[3 * v + 1], c = O.V[3 * v + 2];
             s[1] += a;
             s[2] += b;
@@ -99,13 +101,12 @@ diag_kernel(const BoxDev* __restrict__ B, const ObjDev<typename Prec<P>::R>* __r
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
         const double w = wave_sum(s[c]);
-        if ((t & 63) == 63) red[c][wave] = w;
+        if ((t & 63) == 63) red[c][wave] = c > 0 && c < 4 ? scale * w : w;
     }
     __syncthreads();
     if (t < 5) {
         double tot = 0.0;
         for (int k = 0; k < 16; ++k) tot += red[t][k];
-        if (t > 0 && t < 4) tot *= scale;
         // an exchange whose old value has come back is in device memory, so no
         // fence is needed before the count (a release here writes each XCD's L2
         // back, and with it what the step left there: 84 us instead of 12 at half a
@@ -122,7 +123,7 @@ diag_kernel(const BoxDev* __restrict__ B, const ObjDev<typename Prec<P>::R>* __r
     __syncthreads();
     if (!last) return;
     // the lower half of the block adds the lattice's partials, the upper half the objects'
-    const int g = t >> 9, n = g ? nobj : nlat;
+    const int g = t >> 9, n = g ? (int)gridDim.x - nlat : nlat;
     const double* p = part + (g ? 5 * (size_t)nlat : 0);
     double q[5] = {0, 0, 0, 0, 0};
     for (int k = t & 511; k < n; k += 512)
@@ -284,13 +285,16 @@ hipError_t launch_lb(const LbLaunch& L) {
     return hipGetLastError();
 }
 
-hipError_t launch_diag(const BoxDev* box_dev, int N, const void* objs, int nobj, int precision, int parity,
+hipError_t launch_diag(const BoxDev* box_dev, int N, const void* objs, int nobj, int max_nv, int precision, int parity,
                        double* partials, double* out, hipStream_t s) {
     const int nlat = diag_lattice_blocks(N);
+    // objects a block takes: one while all blocks start together (two to a
+    // compute unit), of more as many as leave a thread about four nodes
+    const int per = nobj <= 512 || max_nv > 1024 ? 1 : (max_nv > 256 ? 4 : 16);
 #define OIF_DIAG(P)                                                                                               \
     case P:                                                                                                       \
-        hipLaunchKernelGGL(diag_kernel<P>, dim3(nlat + nobj), dim3(1024), 0, s, box_dev,                          \
-                           (const ObjDev<typename Prec<P>::R>*)objs, nlat, nobj, parity, partials, out);          \
+        hipLaunchKernelGGL(diag_kernel<P>, dim3(nlat + (nobj + per - 1) / per), dim3(1024), 0, s, box_dev,        \
+                           (const ObjDev<typename Prec<P>::R>*)objs, nlat, nobj, per, parity, partials, out);     \
         break
     switch (precision) {
         OIF_DIAG(PREC_FP64);

@@ -347,12 +347,12 @@ size_t mesh_scratch_bytes(int precision, int nv, int nt, int ne, int ucap, int c
 hipError_t mesh_set_max_lds(size_t bytes);
 
 // FP64 diagnostics.  Lattice partials: per block [sum dev, jx, jy, jz, nonfinite];
-// mesh partials: per object [0, m vx, m vy, m vz, nonfinite], stored after the
-// lattice partials; out (memory that the host can read) [0..4] lattice sums,
+// mesh partials: per block of objects [0, m vx, m vy, m vz, nonfinite], stored
+// after the lattice partials; max_nv the nodes of the largest object; out (memory that the host can read) [0..4] lattice sums,
 // [5..9] mesh sums, [10] the status word.
 constexpr int DIAG_BLOCKS = 256;  // most lattice blocks (of 1024 nodes at a time) it takes
 inline int diag_lattice_blocks(int N) { return N > 1024 * DIAG_BLOCKS ? DIAG_BLOCKS : (N + 1023) / 1024; }
-hipError_t launch_diag(const BoxDev* box_dev, int N, const void* objs, int nobj, int precision, int parity,
+hipError_t launch_diag(const BoxDev* box_dev, int N, const void* objs, int nobj, int max_nv, int precision, int parity,
                        double* partials, double* out, hipStream_t s);
 
 // plain device-to-device copy kernel of `bytes` (a multiple of 16)

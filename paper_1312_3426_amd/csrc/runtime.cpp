@@ -398,7 +398,7 @@ struct oif_ctx {
     bool rep_on = false;
     RepDev rep_h{};
     DevBuf rep_desc, rep_node, rep_pos, rep_cell, rep_head, rep_frep, rep_type, rep_shape;
-    int rep_max_nv = 0;         // nodes of the largest object
+    int max_nv = 0;             // nodes of the largest object
     bool host_stale = false;
     bool mesh_dirty = true;     // device mesh arrays must be rebuilt
 
@@ -760,8 +760,6 @@ int setup_repulsion(oif_ctx* c, size_t real_bytes) {
     // empty lists, no node in any
     HIPCALL(c, hipMemset(c->rep_head.p, 0xff, 2 * NC * 4));
     HIPCALL(c, hipMemset(c->rep_cell.p, 0xff, M * 4));
-    c->rep_max_nv = 0;
-    for (const Object& o : c->obj) c->rep_max_nv = std::max(c->rep_max_nv, o.nv);
     std::vector<unsigned char> types(M);
     for (const Object& o : c->obj)
         for (int v = 0; v < o.nv; ++v) types[(size_t)o.off + v] = (unsigned char)o.ptype;
@@ -1144,6 +1142,8 @@ int upload_mesh_t(oif_ctx* c) {
 
     // mesh state (object-local) and per-object descriptors
     const size_t n = 3 * (size_t)c->M;
+    c->max_nv = 0;
+    for (const Object& o : c->obj) c->max_nv = std::max(c->max_nv, o.nv);
     std::vector<double> xl(n);
     std::vector<real> vl(n);
     for (const Object& o : c->obj)
@@ -1360,7 +1360,7 @@ int enqueue_mesh(oif_ctx* c, int par, hipStream_t s, int mark_next) {
     const size_t osz = objdev_size(c->d.precision);
     if (c->rep_on)
         HIPCALL(c, launch_repulsion(c->rep_h, (const RepDev*)c->rep_desc.p, c->obj_dev.p, (int)c->obj.size(),
-                                    c->rep_max_nv, par, c->d.precision, s));
+                                    c->max_nv, par, c->d.precision, s));
     MeshLaunch ml{};
     auto block = [&](size_t lds, int nwg, int nv = INT_MAX) {
         return membrane_block(c->mesh_block, c->d.precision, lds, nwg, c->n_cu, nv);
@@ -1491,7 +1491,7 @@ int enqueue_steps(oif_ctx* c, int n, int parity0, hipStream_t s) {
 // partials in `part` (5 doubles each), the ten totals and the status word in
 // the context's pinned words, to be read once `s` has been waited for.
 int enqueue_diag(oif_ctx* c, double* part, hipStream_t s) {
-    HIPCALL(c, launch_diag(c->box_dev, c->N, c->obj_dev.p, (int)c->obj.size(), c->d.precision, c->parity, part,
+    HIPCALL(c, launch_diag(c->box_dev, c->N, c->obj_dev.p, (int)c->obj.size(), c->max_nv, c->d.precision, c->parity, part,
                            c->diag_out, s));
     return OIF_OK;
 }
@@ -2984,7 +2984,7 @@ int batch_enqueue(oif_batch* b, int n, int parity0, hipStream_t s, std::vector<h
         for (oif_ctx* c : b->ctx)
             if (c->rep_on)
                 BHIP(b, launch_repulsion(c->rep_h, (const RepDev*)c->rep_desc.p, c->obj_dev.p,
-                                         (int)c->obj.size(), c->rep_max_nv, par, c->d.precision, s));
+                                         (int)c->obj.size(), c->max_nv, par, c->d.precision, s));
         if (b->persistent) {  // the membranes and the lattice of every box in one launch
             BatchLaunch bl{(const BatchSched*)b->sched_dev.p, b->p_grid, persistent_block(b), b->p_lds, par,
                            b->precision, b->lb_nt, s};

@@ -124,3 +124,15 @@ assert c.info().mesh_block == {threads}, c.info().mesh_block
 c.set_launch(-1, 320, -1)
 assert c.info().mesh_block == 320
 """)
+
+
+@pytest.mark.parametrize("level,count,blocks", [(0, 512, 512), (2, 513, 33), (3, 516, 129), (3, 20000, 5000), (1, 20000, 1250)])
+def test_blocks_of_the_diagnostics(fake, level, count, blocks):
+    """Up to 512 objects have a block of 1024 threads each; more of them share blocks, by the largest one's nodes."""
+    run(fake, f"""
+box = synth.Box(16, 16, 16, templates=[synth.Template(*synth.icosphere({level}, 4.0))],
+                objects=[synth.ObjectSpec(0, np.array([8.0, 8.0, 8.0]))] * {count})
+c = oif.Context.from_box(box, precision="fp32")
+c.diagnostics()
+assert fake.fake_blocks(b"diag_kernel") == 4 + {blocks}, fake.fake_blocks(b"diag_kernel")
+""")
