@@ -275,6 +275,15 @@ struct RepDev {
     double* pos;                // [M][3] positions, wrapped into the box along periodic axes
     int* cell;                  // [M] cell of each node in the last step (-1: none yet)
     int* head[2];               // [ncell] first node of each cell, -1: empty
+    // The nodes in cell order instead of the lists (the arrays above, node and
+    // head, are null then): nodes per cell, which the scan turns into the cells'
+    // first slots; the next free slot of each cell; block sums of the scan; and by
+    // slot the node, its position and type.
+    int sorted;
+    int *cnt, *cursor, *bsum;   // [ncell + 1], [ncell], [blocks of 4096 cells]
+    int* list;                  // [M]
+    double* spos;               // [M][3]
+    unsigned char* stype;       // [M]
     void* frep;                 // [M][3] force, arithmetic type
     unsigned* status;           // the box's watchdog word (ST_OVERFLOW: a force out of range)
 };

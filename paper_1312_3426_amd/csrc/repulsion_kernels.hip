@@ -5,7 +5,8 @@
 // offset < d < offset + cutoff, pushing the partners apart.
 //
 // Per step, before the membrane kernel (which adds the result to each node's
-// total force), two launches:
+// total force), two launches where the cells hold less than a node and a half on
+// average:
 //   rep_bin     the positions the membrane kernel takes its forces at (those
 //               of the step start, or advanced by the half-step velocity with
 //               velocity Verlet), wrapped into the box along periodic axes,
@@ -22,6 +23,14 @@
 //               so the result does not depend on the order of the lists.
 // What bounds it: the round trips of the atomics (bin) and of the lists (force),
 // a few dependent loads a node with all nodes in flight at once.
+// With more nodes to a cell (RepDev::sorted: ranges of several mesh edges) the
+// lists' nodes, one place in memory each, cost more than a counting sort over the
+// few cells: rep_bin counts, a scan, rep_scatter and rep_gather put the nodes in
+// cell order, and rep_sorted runs one thread per node in that order, so that a wave
+// reads its partners as the same contiguous runs.  Steps of 500 spheres of 642 nodes
+// in 256x128x128 (us, lists and sorted): range 2 (0.6 nodes a cell) 953 and 1008,
+// 3 (2.1) 2021 and 1773, 5 (9.8) 4803 and 3776; 400 cells of 393 nodes: range 3
+// (1.0) 966 and 1085, 5 (4.8) 1917 and 1712.
 #include <limits.h>
 
 #include "device_common.h"
@@ -67,15 +76,19 @@ rep_bin_kernel(const ObjDev<R>* __restrict__ objs, const RepDev* __restrict__ Dp
         if (c < 2 || !D.walls_z) p[c] = wrapped(p[c], D.L[c]);
         D.pos[3 * j + c] = p[c];
     }
-    int next = -1;
     if (D.pairs) {
         const int cx = cell_coord(D, 0, p[0]), cy = cell_coord(D, 1, p[1]), cz = cell_coord(D, 2, p[2]);
         const int cell = (cz * D.nc[1] + cy) * D.nc[0] + cx, old = D.cell[j];
+        if (D.sorted) {
+            D.cell[j] = cell;
+            atomicAdd(&D.cnt[cell], 1);
+            return;
+        }
         if (old >= 0) D.head[parity ^ 1][old] = -1;
         D.cell[j] = cell;
-        next = atomicExch(&D.head[parity][cell], j);
+        const int next = atomicExch(&D.head[parity][cell], j);
+        D.node[j] = RepNode{(float)p[0], (float)p[1], (float)p[2], next};
     }
-    if (D.pairs) D.node[j] = RepNode{(float)p[0], (float)p[1], (float)p[2], next};
 }
 
 __device__ __forceinline__ double dot3(const double* a, const double* b) {
@@ -170,6 +183,31 @@ __device__ __forceinline__ void soft_sphere(const SoftSphereDev& ss, double d, c
     if (!(e > 0.0 && e < ss.cutoff)) return;
     const double m = ss.a * ss.n * pow(e, -(ss.n + 1.0));
     f.add(m * dir[0], m * dir[1], m * dir[2]);
+}
+
+// Pair force on a node of type tj from the node w of type tw, r their distance
+// vector.
+__device__ __forceinline__ void pair_force(const RepDev& D, int tj, int tw, const double r[3], ForceSum& f) {
+    const double d2 = dot3(r, r);
+    if (!(d2 < D.range2)) return;  // beyond every pair range
+    const SoftSphereDev& ss = D.pair[tj][tw];
+    if (ss.a == 0.0) return;
+    const double d = sqrt(d2), id = 1.0 / d;
+    const double dir[3] = {r[0] * id, r[1] * id, r[2] * id};
+    soft_sphere(ss, d, dir, f);
+}
+
+// Forces of the obstacle shapes and the z walls on a node at p (wrapped).
+__device__ __forceinline__ void wall_forces(const RepDev& D, const SoftSphereDev& ws, const double p[3], ForceSum& f) {
+    for (int k = 0; k < D.n_shape; ++k) {
+        double d, dir[3];
+        if (shape_distance(D.shape[k], p, d, dir)) soft_sphere(ws, d, dir, f);
+    }
+    if (D.walls_z) {
+        const double up[3] = {0.0, 0.0, 1.0}, down[3] = {0.0, 0.0, -1.0};
+        if (p[2] > 0.0) soft_sphere(ws, p[2], up, f);
+        if (p[2] < D.L[2]) soft_sphere(ws, D.L[2] - p[2], down, f);
+    }
 }
 
 // Neighbour cell offsets along one axis that hold nodes within the range of w
@@ -278,38 +316,206 @@ rep_force_kernel(const RepDev* __restrict__ Dp, int parity) {
             if (round_x) r[0] -= D.L[0] * rint(r[0] / D.L[0]);
             if (round_y) r[1] -= D.L[1] * rint(r[1] / D.L[1]);
             if (round_z) r[2] -= D.L[2] * rint(r[2] / D.L[2]);
-            const double d2 = dot3(r, r);
-            if (!(d2 < D.range2)) continue;  // beyond every pair range
-            const SoftSphereDev& ss = D.pair[tj][D.type[w]];
-            if (ss.a == 0.0) continue;
-            const double d = sqrt(d2), id = 1.0 / d;
-            const double dir[3] = {r[0] * id, r[1] * id, r[2] * id};
-            soft_sphere(ss, d, dir, f);
+            pair_force(D, tj, D.type[w], r, f);
         }
     }
     const SoftSphereDev& ws = D.wall[tj];
-    if (WALLS && ws.a != 0.0) {
-        for (int k = 0; k < D.n_shape; ++k) {
-            double d, dir[3];
-            if (shape_distance(D.shape[k], p, d, dir)) soft_sphere(ws, d, dir, f);
-        }
-        if (D.walls_z) {
-            const double up[3] = {0.0, 0.0, 1.0}, down[3] = {0.0, 0.0, -1.0};
-            if (p[2] > 0.0) soft_sphere(ws, p[2], up, f);
-            if (p[2] < D.L[2]) soft_sphere(ws, D.L[2] - p[2], down, f);
-        }
-    }
+    if (WALLS && ws.a != 0.0) wall_forces(D, ws, p, f);
     R* out = (R*)D.frep;
     for (int c = 0; c < 3; ++c) out[3 * j + c] = (R)fx_value(f.hi[c], f.lo[c]);
     if (!f.ok) atomicOr(D.status, ST_OVERFLOW);
+}
+
+// ---- the nodes in cell order ----
+
+// exclusive scan of the 1024-thread block's values (wave scans, then the
+// wave totals); all threads of the block must call it
+__device__ __forceinline__ int block_exclusive_scan(int v, int* wsum) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int incl = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += o;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    int before = 0;
+    for (int k = 0; k < w; ++k) before += wsum[k];
+    return before + incl - v;
+}
+
+// The four counts of thread t of a block: cnt[4 (1024 b + t) ...], one 16-byte
+// access where all four lie below n (cnt is 16-byte aligned).
+__device__ __forceinline__ void load4(const int* cnt, int i, int n, int (&v)[4]) {
+    if (i + 3 < n) {
+        const int4 q = *(const int4*)(cnt + i);
+        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+    } else {
+        for (int k = 0; k < 4; ++k) v[k] = i + k < n ? cnt[i + k] : 0;
+    }
+}
+__device__ __forceinline__ void store4(int* a, int i, int n, const int (&v)[4]) {
+    if (i + 3 < n) {
+        *(int4*)(a + i) = make_int4(v[0], v[1], v[2], v[3]);
+    } else {
+        for (int k = 0; k < 4; ++k)
+            if (i + k < n) a[i + k] = v[k];
+    }
+}
+
+// exclusive prefix sum of cnt[0, n) in place, per block of 4096 counts (four
+// per thread); the block totals go to bsum
+__global__ void __launch_bounds__(1024) scan_block_kernel(int* __restrict__ cnt, int* __restrict__ bsum, int n) {
+    __shared__ int wsum[16];
+    const int i = 4 * (blockIdx.x * 1024 + threadIdx.x);
+    int v[4];
+    load4(cnt, i, n, v);
+    const int t = v[0] + v[1] + v[2] + v[3];
+    int acc = block_exclusive_scan(t, wsum);
+    int e[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        e[k] = acc;
+        acc += v[k];
+    }
+    store4(cnt, i, n, e);
+    if (threadIdx.x == 1023) bsum[blockIdx.x] = acc;
+}
+
+__global__ void __launch_bounds__(1024) scan_top_kernel(int* __restrict__ bsum, int nb) {
+    // one workgroup: every thread sums a contiguous run, the run sums are
+    // scanned across the block, then every thread writes its run's prefixes
+    __shared__ int wsum[16];
+    const int per = (nb + 1023) / 1024;
+    const int b0 = threadIdx.x * per;
+    int s = 0;
+    for (int k = b0; k < b0 + per && k < nb; ++k) s += bsum[k];
+    int acc = block_exclusive_scan(s, wsum);
+    for (int k = b0; k < b0 + per && k < nb; ++k) {
+        const int t = bsum[k];
+        bsum[k] = acc;
+        acc += t;
+    }
+}
+
+// add the block offsets: cnt = cell starts, cursor = a copy for the scatter;
+// cnt[n] = total
+__global__ void __launch_bounds__(1024) scan_add_kernel(int* __restrict__ cnt, int* __restrict__ cursor,
+                                                        const int* __restrict__ bsum, int n, int total) {
+    const int i = 4 * (blockIdx.x * 1024 + threadIdx.x);
+    if (i < n) {
+        int v[4];
+        load4(cnt, i, n, v);
+        const int b = bsum[blockIdx.x];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] += b;
+        store4(cnt, i, n, v);
+        store4(cursor, i, n, v);
+    }
+    if (i == 0) cnt[n] = total;
+}
+
+__global__ void __launch_bounds__(256) rep_scatter_kernel(const RepDev* __restrict__ Dp) {
+    const RepDev& D = *Dp;
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= D.M) return;
+    const int slot = atomicAdd(&D.cursor[D.cell[j]], 1);
+    D.list[slot] = j;
+}
+
+__global__ void __launch_bounds__(256) rep_gather_kernel(const RepDev* __restrict__ Dp) {
+    const RepDev& D = *Dp;
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= D.M) return;
+    const int j = D.list[s];
+    for (int c = 0; c < 3; ++c) D.spos[3 * s + c] = D.pos[3 * j + c];
+    D.stype[s] = D.type[j];
+}
+
+// One thread per node, in cell order (slot s holds node list[s]): the partners in
+// the 27 surrounding cells, a neighbour cell across a periodic face shifted by the
+// box length; on an axis of one or two cells each cell once, the image by rounding.
+template <typename R>
+__global__ void __launch_bounds__(256) rep_sorted_kernel(const RepDev* __restrict__ Dp) {
+    const RepDev& D = *Dp;
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= D.M) return;
+    const int j = D.list[s], tj = D.stype[s], cell = D.cell[j];
+    const bool pz = !D.walls_z;
+    const double p[3] = {D.spos[3 * s], D.spos[3 * s + 1], D.spos[3 * s + 2]};
+    ForceSum f;
+    const int cx = cell % D.nc[0], t = cell / D.nc[0], cy = t % D.nc[1], cz = t / D.nc[1];
+    const bool round_x = D.nc[0] < 3, round_y = D.nc[1] < 3, round_z = pz && D.nc[2] < 3;
+    const int lx = round_x ? 0 : -1, hx = round_x ? D.nc[0] - 1 : 1, ly = round_y ? 0 : -1, hy = round_y ? D.nc[1] - 1 : 1,
+              lz = round_z ? 0 : -1, hz = round_z ? D.nc[2] - 1 : 1;
+    // the cells x - 1 .. x + 1 of a row without a wrap are one contiguous run of slots
+    const bool run3 = !round_x && cx > 0 && cx + 1 < D.nc[0];
+    for (int dz = lz; dz <= hz; ++dz) {
+        int z = cz + dz;
+        double sz = 0.0;  // shift of the neighbour cell's nodes (periodic image)
+        if (pz) {
+            if (z < 0) { z += D.nc[2]; sz = -D.L[2]; }
+            else if (z >= D.nc[2]) { z -= D.nc[2]; sz = D.L[2]; }
+        } else if (z < 0 || z >= D.nc[2]) {
+            continue;
+        }
+        for (int dy = ly; dy <= hy; ++dy) {
+            int y = cy + dy;
+            double sy = 0.0;
+            if (y < 0) { y += D.nc[1]; sy = -D.L[1]; }
+            else if (y >= D.nc[1]) { y -= D.nc[1]; sy = D.L[1]; }
+            const int row = (z * D.nc[1] + y) * D.nc[0];
+            for (int dx = run3 ? 0 : lx; dx <= (run3 ? 0 : hx); ++dx) {
+                int x = cx + dx;
+                double sx = 0.0;
+                if (x < 0) { x += D.nc[0]; sx = -D.L[0]; }
+                else if (x >= D.nc[0]) { x -= D.nc[0]; sx = D.L[0]; }
+                const int u1 = D.cnt[row + (run3 ? cx + 2 : x + 1)];
+                for (int u = D.cnt[row + (run3 ? cx - 1 : x)]; u < u1; ++u) {
+                    if (u == s) continue;
+                    double r[3] = {p[0] - (D.spos[3 * u] + sx), p[1] - (D.spos[3 * u + 1] + sy),
+                                   p[2] - (D.spos[3 * u + 2] + sz)};
+                    if (round_x) r[0] -= D.L[0] * rint(r[0] / D.L[0]);
+                    if (round_y) r[1] -= D.L[1] * rint(r[1] / D.L[1]);
+                    if (round_z) r[2] -= D.L[2] * rint(r[2] / D.L[2]);
+                    pair_force(D, tj, D.stype[u], r, f);
+                }
+            }
+        }
+    }
+    const SoftSphereDev& ws = D.wall[tj];
+    if (ws.a != 0.0) wall_forces(D, ws, p, f);
+    R* out = (R*)D.frep;
+    for (int c = 0; c < 3; ++c) out[3 * j + c] = (R)fx_value(f.hi[c], f.lo[c]);
+    if (!f.ok) atomicOr(D.status, ST_OVERFLOW);
+}
+
+// a[0, n) = v, four per thread (a 16-byte aligned)
+__global__ void __launch_bounds__(256) fill_int_kernel(int* __restrict__ a, int n, int v) {
+    const int i = 4 * (blockIdx.x * blockDim.x + threadIdx.x);
+    const int f[4] = {v, v, v, v};
+    if (i < n) store4(a, i, n, f);
 }
 
 template <typename R>
 hipError_t launch_rep_t(const RepDev& h, const RepDev* d, const void* objs, int nobj, int max_nv, int parity,
                         hipStream_t s) {
     if (h.M == 0) return hipSuccess;
+    if (h.sorted)
+        hipLaunchKernelGGL(fill_int_kernel, dim3((h.ncell + 1 + 1023) / 1024), dim3(256), 0, s, h.cnt, h.ncell + 1, 0);
     hipLaunchKernelGGL((rep_bin_kernel<R>), dim3(nobj, (max_nv + 255) / 256), dim3(256), 0, s, (const ObjDev<R>*)objs, d,
                        parity);
+    if (h.sorted) {
+        const int nb = (h.ncell + 4095) / 4096, gm = (h.M + 255) / 256;
+        hipLaunchKernelGGL(scan_block_kernel, dim3(nb), dim3(1024), 0, s, h.cnt, h.bsum, h.ncell);
+        hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(1024), 0, s, h.bsum, nb);
+        hipLaunchKernelGGL(scan_add_kernel, dim3(nb), dim3(1024), 0, s, h.cnt, h.cursor, (const int*)h.bsum, h.ncell, h.M);
+        hipLaunchKernelGGL(rep_scatter_kernel, dim3(gm), dim3(256), 0, s, d);
+        hipLaunchKernelGGL(rep_gather_kernel, dim3(gm), dim3(256), 0, s, d);
+        hipLaunchKernelGGL(rep_sorted_kernel<R>, dim3(gm), dim3(256), 0, s, d);
+        return hipGetLastError();
+    }
     bool walls = false, two = true;
     for (const SoftSphereDev& w : h.wall) walls = walls || w.a != 0.0;
     for (int a = 0; a < 3; ++a) two = two && (h.nc[a] < 3 || h.hc[a] >= 2.0 * (sqrt(h.range2) + 2e-6 * h.hc[a]));

@@ -750,15 +750,20 @@ int setup_repulsion(oif_ctx* c, size_t real_bytes) {
     std::memcpy(R.pair, c->rep_pair, sizeof(R.pair));
     std::memcpy(R.wall, c->rep_wall, sizeof(R.wall));
     const size_t M = c->M, NC = (size_t)R.ncell;
+    R.sorted = pairs && 2 * M >= 3 * NC;  // a node and a half to a cell (why there: repulsion_kernels.hip)
+    // the lists' nodes and heads; or by slot the positions, nodes and types, and the
+    // counts, next slots and block sums, 16-byte aligned
+    const size_t cnt4 = (NC + 4) & ~(size_t)3, slot_bytes = M * (24 + 4 + 1), cell_bytes = 4 * (2 * cnt4 + NC / 4096 + 1);
     int rc_ = 0;
-    if ((rc_ = dev_alloc(c, c->rep_node, M * sizeof(RepNode))) || (rc_ = dev_alloc(c, c->rep_pos, 3 * M * 8)) || (rc_ = dev_alloc(c, c->rep_cell, M * 4)) ||
-        (rc_ = dev_alloc(c, c->rep_head, 2 * NC * 4)) || (rc_ = dev_alloc(c, c->rep_frep, 3 * M * real_bytes)) ||
-        (rc_ = dev_alloc(c, c->rep_type, M)) ||
+    if ((rc_ = dev_alloc(c, c->rep_node, R.sorted ? slot_bytes : M * sizeof(RepNode))) ||
+        (rc_ = dev_alloc(c, c->rep_pos, 3 * M * 8)) || (rc_ = dev_alloc(c, c->rep_cell, M * 4)) ||
+        (rc_ = dev_alloc(c, c->rep_head, R.sorted ? cell_bytes : 2 * NC * 4)) ||
+        (rc_ = dev_alloc(c, c->rep_frep, 3 * M * real_bytes)) || (rc_ = dev_alloc(c, c->rep_type, M)) ||
         (rc_ = dev_alloc(c, c->rep_shape, (c->shapes.size() + 1) * sizeof(ShapeDev))) ||
         (rc_ = dev_alloc(c, c->rep_desc, sizeof(RepDev))))
         return rc_;
     // empty lists, no node in any
-    HIPCALL(c, hipMemset(c->rep_head.p, 0xff, 2 * NC * 4));
+    if (!R.sorted) HIPCALL(c, hipMemset(c->rep_head.p, 0xff, 2 * NC * 4));
     HIPCALL(c, hipMemset(c->rep_cell.p, 0xff, M * 4));
     std::vector<unsigned char> types(M);
     for (const Object& o : c->obj)
@@ -770,11 +775,20 @@ int setup_repulsion(oif_ctx* c, size_t real_bytes) {
     R.n_shape = (int)c->shapes.size();
     R.shape = (const ShapeDev*)c->rep_shape.p;
     R.type = (const unsigned char*)c->rep_type.p;
-    R.node = (RepNode*)c->rep_node.p;
     R.pos = (double*)c->rep_pos.p;
     R.cell = (int*)c->rep_cell.p;
-    R.head[0] = (int*)c->rep_head.p;
-    R.head[1] = (int*)c->rep_head.p + NC;
+    if (R.sorted) {
+        R.spos = (double*)c->rep_node.p;
+        R.list = (int*)(R.spos + 3 * M);
+        R.stype = (unsigned char*)(R.list + M);
+        R.cnt = (int*)c->rep_head.p;
+        R.cursor = R.cnt + cnt4;
+        R.bsum = R.cursor + cnt4;
+    } else {
+        R.node = (RepNode*)c->rep_node.p;
+        R.head[0] = (int*)c->rep_head.p;
+        R.head[1] = (int*)c->rep_head.p + NC;
+    }
     R.frep = c->rep_frep.p;
     R.status = c->status;
     HIPCALL(c, hipMemcpy(c->rep_desc.p, &R, sizeof(RepDev), hipMemcpyHostToDevice));

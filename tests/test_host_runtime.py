@@ -136,3 +136,17 @@ c = oif.Context.from_box(box, precision="fp32")
 c.diagnostics()
 assert fake.fake_blocks(b"diag_kernel") == 4 + {blocks}, fake.fake_blocks(b"diag_kernel")
 """)
+
+
+@pytest.mark.parametrize("cutoff,sorted_", [(0.3, False), (2.0, False), (2.9, True), (5.0, True)])
+def test_search_of_the_pair_partners(fake, cutoff, sorted_):
+    """Lists by cell up to a node and a half in each, the nodes in cell order beyond (9630 nodes in 64x32x32)."""
+    run(fake, f"""
+box = synth.Box(64, 32, 32, templates=[synth.Template(*synth.icosphere(3, 4.0))],
+                objects=[synth.ObjectSpec(0, np.array([8.0, 8.0, 8.0]))] * 15,
+                repulsion=[synth.SoftSphere(0, 0, a=1e-6, n=2.0, cutoff={cutoff})])
+c = oif.Context.from_box(box, precision="fp32")
+c.step(1)
+launched = fake.fake_blocks(b"rep_sorted_kernel"), fake.fake_blocks(b"rep_force_kernel")
+assert [n > 0 for n in launched] == [{sorted_}, not {sorted_}], launched
+""")
