@@ -104,7 +104,7 @@ hipError_t hipGetSymbolAddress(void** p, const void* sym) {
 hipError_t hipLaunchKernel(const void* f, dim3 g, dim3, void** args, size_t, hipStream_t s) {
     if (s && s->device != current) return hipErrorInvalidHandle;
     blocks[kernels[f]] = g.x;
-    if (kernels[f].find("gather_kernel") != std::string::npos) {
+    if (kernels[f].find("GatherSrc") != std::string::npos) {
         const Gather& g = *(const Gather*)args[0];
         char* dst = *(char**)args[1];
         for (int a = 0; a < 3; ++a) {
