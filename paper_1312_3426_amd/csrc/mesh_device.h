@@ -883,10 +883,10 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
             const double wx = ax + bx, wy = ay + by, wz = az + bz;
             double w2 = fmadd(wx, wx, fmadd(wy, wy, wz * wz));
             if (cons) {
-                const double cx_ = bx - ax - ax, cy_ = by - ay - ay, cz_ = bz - az - az;
-                const double dx = ax - bx - bx, dy = ay - by - by, dz = az - bz - bz;
-                w2 += fmadd(cx_, cx_, fmadd(cy_, cy_, cz_ * cz_)) + fmadd(dx, dx, fmadd(dy, dy, dz * dz));
-                w2 *= 1.0 / 3.0;
+                // the mean of |a + b|^2, |b - 2 a|^2 and |a - 2 b|^2, a = v - a and
+                // b = v - b: |a + b|^2 / 2 + 3 |b - a|^2 / 2
+                const double ux = bx - ax, uy = by - ay, uz = bz - az;
+                w2 = fmadd(0.5, w2, 1.5 * fmadd(ux, ux, fmadd(uy, uy, uz * uz)));
             }
             double ct = ((double)tr[c.t] + cg) * rsqrt_of<R>(w2);
             // a repeated corner adds nothing (selected, not skipped: without
