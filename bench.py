@@ -497,7 +497,7 @@ def main():
         "membrane_kernel": {"bytes": 48 * M + 100 * T, "ms": round(r32["mesh_ms"], 5),
                             "GB/s": round((48 * M + 100 * T) / (r32["mesh_ms"] * 1e-3) / 1e9, 1),
                             "frac": round((48 * M + 100 * T) / (r32["mesh_ms"] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                            "bound": "latency of each object's dependent LDS and memory round trips"},
+                            "bound": "the 128-byte population lines fetched for a few touched nodes each"},
         "graph": {p: (round(N / (res[p]["graph_ms_per_step"] * 1e-3) / 1e6, 2) if "graph_ms_per_step" in res[p] else None)
                   for p in res},
         "storage": {},

@@ -146,14 +146,17 @@ __device__ __forceinline__ bool stencil_corner(double px, double py, double pz, 
     return true;
 }
 
-// Arithmetic of the element forces.  FP64 form: the library's square root and
-// division.  FP32 forms: FP64 as well (additions, products and their sums run at
-// the FP32 rate of unpacked instructions), rounded to FP32 once where a value is
-// stored.  The hardware's reciprocal and reciprocal square root (good to some
-// 2^-23) are refined once, far below that rounding.  Root mean square error of
-// the FP32 form's force over the nodes, all moduli: 0.49 units of 2^-24 of the
-// force, where correctly rounded FP32 operations give 1.9 and FP32 estimates refined
-// once 2.3; pass of 500 spheres 92.2 ms, with those 92.8 (FP16 storage 59.6, 58.5).
+// Arithmetic of the elements.  FP64 form: the library's square root and division.
+// FP32 forms: FP64 as well (additions, products and their sums run at the FP32
+// rate of unpacked instructions), rounded to FP32 once where a value is stored.
+// The hardware's reciprocal and reciprocal square root (good to some 2^-23) are
+// refined once, far below that rounding.  The nodes' sums over their corners are
+// FP32 in those forms.  Root mean square error of the FP32 form's force over the
+// nodes, all moduli: 1.6 units of 2^-24 of the force, where correctly rounded FP32
+// operations on the plain rules give 1.9 and FP32 estimates refined once, summed in
+// one order or another, 2.3; launch of 500 spheres 56.1 us, with those 55.9 (FP16
+// storage 42.8, 41.3).  Sums over the corners in FP64: 0.49 units, 57.2 and 44.1 us
+// (5000 cells 565 us, 552 so).
 __device__ __forceinline__ double recip(double x) {
     const double r = __builtin_amdgcn_rcp(x);
     return fmadd(r, fmadd(-x, r, 1.0), r);
@@ -180,6 +183,15 @@ __device__ __forceinline__ void length_of(double L2, double& L, double& rL) {
     L = L2 * r;
     L = fmadd(fmadd(-L, L, L2), 0.5 * r, L);
     rL = r;
+}
+// 1 / sqrt(x) in the arithmetic type.  FP32: the estimate r refined once with the
+// rounding of x r carried along, so that the result is off by half a unit in the
+// last place, as the correctly rounded quotient would be
+__device__ __forceinline__ double rsqrt_r(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ float rsqrt_r(float x) {
+    const float r = __builtin_amdgcn_rsqf(x), s = x * r;
+    const float e = fmadd(-fmadd(x, r, -s), r, fmadd(-s, r, 1.0f));
+    return fmadd(0.5f * r, e, r);
 }
 // angle of (x, y).  FP32 forms: near the relaxed shape the Taylor series of
 // atan (terms to t^7 leave 7e-9 of t at |t| = 1/8), the library's atan2 beyond
@@ -647,8 +659,8 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     // Waves of their own because a wave's loads return in order: a fetching
     // wave that also read element records would wait for its populations
     // first.  (The populations of a 642-node sphere lie in some 2000 lines of
-    // 128 bytes; all objects of a launch fetch at once: 500 of them move 170 MB,
-    // half of the launch's time at the memory's rate.)  With one 16-byte record
+    // 128 bytes; all objects of a launch fetch at once: 500 of them read 141 MB and
+    // write 23, at the memory's rate half of the launch's time.)  With one 16-byte record
     // per triangle, edge and corner in place of two or three loads, and no
     // branches between a node's corners: 500 spheres FP16 46.7 -> 43.4 us (FP32
     // 58.0 -> 57.3, bound by the fetch), 120 conservative ones FP64 53.1 -> 48.0,
@@ -831,8 +843,10 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
         gst(O.geo, Sg);
         gst(O.geo + 1, Vol);
     }
-    const double cg = -T->kag * dSg / Sg;                               // global area coefficient
-    const double cv3 = -T->kv * (Vol - T->V0) / T->V0 * (1.0 / 3.0);   // volume coefficient, a third
+    const double cg = -T->kag * dSg / Sg;                             // global area coefficient
+    const double cv3 = -T->kv * (Vol - T->V0) / T->V0 * (1.0 / 3.0);  // volume coefficient, a third
+    // (in two parts: their rounding would be the same relative error at every node)
+    const R cgh = (R)cg, cgl = (R)(cg - (double)cgh), cvh = (R)cv3, cvl = (R)(cv3 - (double)cvh);
 
     // 3. nodes (in the patch launch the patch's nodes are the sub-template's
     // first nn nodes, so xs and the corners take the same index).  The
@@ -852,9 +866,10 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
     R F0x = 0, F0y = 0, F0z = 0;
     for (int i = tid; i < nn; i += bd) {
         const double px = xs[3 * i], py = xs[3 * i + 1], pz = xs[3 * i + 2];
-        // (a corner's terms are one-sided and much larger than the node's force,
-        // so their sum is FP64 in every form)
-        double Fx = 0, Fy = 0, Fz = 0;
+        // (a corner's terms are one-sided and much larger than the node's force;
+        // the host lists opposite corners one after the other, and stretching has a
+        // sum of its own, so that the partial sums stay small)
+        R Fx = 0, Fy = 0, Fz = 0, Sx = 0, Sy = 0, Sz = 0;
         auto corner = [&](const Raw& raw) {
 #pragma clang fp contract(off)
             const Corner c = L::corner(raw);
@@ -876,28 +891,31 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
                 bend = fmadd(c.t2b ? qb[2] - R(1) : -qb[2], qb[0], bend);
             }
             // volume: -kv dV/V0 S n_out / 3
-            double cn = fmadd(-cv3, (double)S, (double)bend);
+            R cn = fmadd(-cvh, S, fmadd(-cvl, S, bend));
             // local area (-kal dS/S w), global area (-kag dSg/Sg w); w = centroid
             // -> vertex over its length (three times it: (v - a) + (v - b)), or
             // (conservative model) over the RMS length of the triangle's three
-            const double wx = ax + bx, wy = ay + by, wz = az + bz;
-            double w2 = fmadd(wx, wx, fmadd(wy, wy, wz * wz));
+            const R wx = (R)(ax + bx), wy = (R)(ay + by), wz = (R)(az + bz);
+            R w2 = fmadd(wx, wx, fmadd(wy, wy, wz * wz));
             if (cons) {
                 // the mean of |a + b|^2, |b - 2 a|^2 and |a - 2 b|^2, a = v - a and
                 // b = v - b: |a + b|^2 / 2 + 3 |b - a|^2 / 2
-                const double ux = bx - ax, uy = by - ay, uz = bz - az;
-                w2 = fmadd(0.5, w2, 1.5 * fmadd(ux, ux, fmadd(uy, uy, uz * uz)));
+                const R ux = (R)(bx - ax), uy = (R)(by - ay), uz = (R)(bz - az);
+                w2 = fmadd(R(0.5), w2, R(1.5) * fmadd(ux, ux, fmadd(uy, uy, uz * uz)));
             }
-            double ct = ((double)tr[c.t] + cg) * rsqrt_of<R>(w2);
+            R ct = (tr[c.t] + cgl + cgh) * rsqrt_r(w2);
             // a repeated corner adds nothing (selected, not skipped: without
             // branches the corners' LDS reads overlap)
-            ct = c.valid ? ct : 0.0;
-            cn = c.valid ? cn : 0.0;
+            ct = c.valid ? ct : R(0);
+            cn = c.valid ? cn : R(0);
             s = c.valid ? s : R(0);
             // F_v += ks kappa (L - L0)/L0 (x_a - x_v)/L  ("Stretching force")
-            Fx = fmadd(ct, wx, fmadd(cn, (double)n0, fmadd(-(double)s, ax, Fx)));
-            Fy = fmadd(ct, wy, fmadd(cn, (double)n1, fmadd(-(double)s, ay, Fy)));
-            Fz = fmadd(ct, wz, fmadd(cn, (double)n2, fmadd(-(double)s, az, Fz)));
+            Sx = fmadd(-s, (R)ax, Sx);
+            Sy = fmadd(-s, (R)ay, Sy);
+            Sz = fmadd(-s, (R)az, Sz);
+            Fx = fmadd(ct, wx, fmadd(cn, n0, Fx));
+            Fy = fmadd(ct, wy, fmadd(cn, n1, Fy));
+            Fz = fmadd(ct, wz, fmadd(cn, n2, Fz));
         };
         if (CONS) {
             // (with the conservative terms six corners side by side spill a
@@ -933,16 +951,19 @@ __device__ __forceinline__ void mesh_object(const ObjDev<typename Prec<P>::R>& O
             }
         }
 
+        Fx += Sx;
+        Fy += Sy;
+        Fz += Sz;
         // the first node's force stays with its thread
         if (i == tid) {
-            F0x = (R)Fx;
-            F0y = (R)Fy;
-            F0z = (R)Fz;
+            F0x = Fx;
+            F0y = Fy;
+            F0z = Fz;
         } else {
             R* f = O.fel + 3 * node_of(i);
-            gst(f, (R)Fx);
-            gst(f + 1, (R)Fy);
-            gst(f + 2, (R)Fz);
+            gst(f, Fx);
+            gst(f + 1, Fy);
+            gst(f + 2, Fz);
         }
     }
 

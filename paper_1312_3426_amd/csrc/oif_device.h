@@ -8,14 +8,18 @@
 //          ((p / 64) * 19 + i) * 64 + p % 64, N rounded up to whole tiles);
 //          the step reads f[parity] and writes f[parity ^ 1]
 //   G[2]   coupling force density per step parity (a step of parity k spreads
-//          into G[k]), [N][4] (x, y, z, unused: one 32-byte slot per node):
-//          double (FP64 form) or int64 fixed point with resolution 2^-e (FP32
-//          forms, order-independent sums).  The lattice kernel only reads it:
-//          each membrane workgroup keeps the list of slots it added to and
-//          zeroes them in the next step, when the lattice kernel is done with
-//          them (gclear covers a workgroup that spread corner by corner)
-//   mask   one bit per node, set where G is non-zero; the lattice kernel reads
-//          G only where a bit is set and clears the bit
+//          into G[k]), int64 fixed point (order-independent sums), one slot per
+//          node: x, y, z and an unused word, resolution 2^-e, 32 bytes (FP32
+//          forms); two words a component, in units of 2^-30 and 2^-80, and two
+//          unused, 64 bytes (FP64 form).  Cleared in one of two ways
+//          (g_by_mesh).  By the lattice kernel where it reads it, G[0] and G[1]
+//          being one buffer; or by the membrane kernel: each of its workgroups
+//          keeps the list of slots it added to and zeroes them in the next step,
+//          when the lattice kernel is done with them (gclear covers a workgroup
+//          that spread corner by corner), and the lattice kernel only reads
+//   mask   one bit per node; the lattice kernel reads G only where a bit is set
+//          and clears the bit.  Set for every node that a stencil touches, also
+//          where the force is zero or the node an obstacle, which takes none
 //   X, V   mesh node positions (absolute, unwrapped, FP64 in every form, so
 //          that edge lengths and areas near their relaxed values do not lose
 //          their digits to position round-off; an integer per-object anchor is
@@ -105,6 +109,7 @@ struct TmplDev {
     // So the table stays linear in the mesh, and only waves that hold such a node
     // walk more than seven corners: launch of 500 latitude-longitude spheres of 64
     // meridians and 770 nodes 70 us, 113 with a ring as deep as the poles need.
+    // Opposite corners follow each other (their forces cancel for the most part).
     // A corner is a triangle (v, a, b) in its order: a, b, the triangle t, and its
     // edges ea = (v, a), eb = (b, v), o = (a, b), each with its top bit set where
     // the triangle is the edge's T2.

@@ -95,7 +95,7 @@ struct Template {
     // template is uploaded)
     std::vector<int> pnv, pnt, pne;
     std::vector<int> side;              // [nt][3] edge of side (v_s, v_s+1), complemented where the triangle is its T2
-    std::vector<std::vector<int>> corner;  // per node: (triangle << 2) | position, ascending
+    std::vector<std::vector<int>> corner;  // per node: (triangle << 2) | position, opposite ones one after the other
 };
 
 inline int tmpl_conservative(const Template& T) { return T.k.force_model == OIF_FORCES_CONSERVATIVE ? 1 : 0; }
@@ -324,6 +324,32 @@ int build_template(const double* nodes, int nv, const int32_t* tris, int nt, con
     T.corner.resize(nv);
     for (int t = 0; t < nt; ++t)
         for (int s3 = 0; s3 < 3; ++s3) T.corner[T.tri[3 * t + s3]].push_back((t << 2) | s3);
+    // around each node (corner (v, a, b) is followed by the one whose a is this b;
+    // a node that several closed surfaces share has a ring of each), then the
+    // corners half a ring apart side by side
+    std::vector<std::pair<int, int>> by_a;
+    std::vector<int> ring;
+    for (std::vector<int>& c : T.corner) {
+        const int n = (int)c.size();
+        auto vertex = [&](int k, int i) { return T.tri[3 * (c[k] >> 2) + ((c[k] & 3) + i) % 3]; };
+        by_a.clear();
+        for (int k = 0; k < n; ++k) by_a.push_back({vertex(k, 1), k});
+        std::sort(by_a.begin(), by_a.end());
+        ring.clear();
+        std::vector<char> used(n, 0);
+        for (int k0 = 0; k0 < n; ++k0)
+            for (int k = k0; k >= 0 && !used[k];) {
+                used[k] = 1;
+                ring.push_back(c[k]);
+                const auto next = std::lower_bound(by_a.begin(), by_a.end(), std::make_pair(vertex(k, 2), 0));
+                k = next != by_a.end() && next->first == vertex(k, 2) ? next->second : -1;
+            }
+        const int half = (n + 1) / 2;
+        for (int i = 0, k = 0; i < half; ++i) {
+            c[k++] = ring[i];
+            if (i + half < n) c[k++] = ring[i + half];
+        }
+    }
     return OIF_OK;
 }
 
@@ -1086,7 +1112,10 @@ std::vector<std::array<int, 3>> object_places(const oif_ctx* c) {
 // membrane kernel of 5000 cells of 642 nodes at random in 512x256x256 nodes, FP32:
 // 722 us as created, 725 with a run of them to each XCD, 578 with neighbours;
 // where all objects run at once it changes little (500 cells, 2-byte storage: 46
-// and 44).  The order is that of the last upload; the results do not depend on it.
+// and 44).  The order is that of the last upload (as cells move, neighbours drift
+// apart until the next one) and made for launches of one workgroup per object of one
+// box; it fits neither the split launches, with several to an object, nor batches,
+// whose objects of all boxes are sorted by size.  The results do not depend on it.
 void deal_to_xcds(int* objs, int first, int n) {
     const std::vector<int> sorted(objs, objs + n);
     int k = 0;
