@@ -27,10 +27,10 @@
 // lists' nodes, one place in memory each, cost more than a counting sort over the
 // few cells: rep_bin counts, a scan, rep_scatter and rep_gather put the nodes in
 // cell order, and rep_sorted runs one thread per node in that order, so that a wave
-// reads its partners as the same contiguous runs.  Steps of 500 spheres of 642 nodes
-// in 256x128x128 (us, lists and sorted): range 2 (0.6 nodes a cell) 953 and 1008,
-// 3 (2.1) 2021 and 1773, 5 (9.8) 4803 and 3776; 400 cells of 393 nodes: range 3
-// (1.0) 966 and 1085, 5 (4.8) 1917 and 1712.
+// reads its partners as the same contiguous runs.  Repulsion of 500 spheres of 642
+// nodes in 256x128x128 (us a step, lists and sorted): range 1.5 (0.3 nodes a cell) 487
+// and 538, 2 (0.6) 903 and 906, 3 (2.1) 1984 and 1656, 5 (9.8) 4759 and 3638; 400
+// cells of 393 nodes: range 3 (1.0) 927 and 1024, 5 (4.8) 1925 and 1650.
 #include <limits.h>
 
 #include "device_common.h"
