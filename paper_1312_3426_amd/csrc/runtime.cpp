@@ -1129,6 +1129,7 @@ int upload_mesh_t(oif_ctx* c) {
     for (auto& b : c->tbufs) b.release();
     c->tbufs.assign(c->tmpl.size(), DevBuf());
     std::vector<TmplDev<real>> td(c->tmpl.size());
+    std::vector<int> tgroup;  // launch group of each template's objects
     for (size_t t = 0; t < c->tmpl.size(); ++t) {
         Template& T = c->tmpl[t];
         TArr A = template_arrays(T);
@@ -1147,6 +1148,7 @@ int upload_mesh_t(oif_ctx* c) {
         // and the patches' for a split mesh (and its 32-bit ones, which the
         // persistent batch form runs whole), 32-bit ones in the scratch
         const int g = mesh_group(c->d.precision, T, c->max_lds);
+        tgroup.push_back(g);
         if (g != 1) pa.clear();
         if (g <= 1) narrow(A, g == 0);
         for (TArr& P : pa) narrow(P, true);
@@ -1224,7 +1226,7 @@ int upload_mesh_t(oif_ctx* c) {
         return mesh_cpl_lds_bytes(c->d.precision, T.nv, T.nt, T.ne, T.ucap, T.ccap, tmpl_conservative(T));
     };
     auto split = [&](int i) { return split_need_bytes(c->d.precision, c->tmpl[c->obj[i].tid]); };
-    auto group = [&](int i) { return mesh_group(c->d.precision, c->tmpl[c->obj[i].tid], c->max_lds); };
+    auto group = [&](int i) { return tgroup[c->obj[i].tid]; };
     // scratch of an object outside LDS: the mesh layout, then the slices' sums
     auto scratch_bytes = [&](int i) {
         const Template& T = c->tmpl[c->obj[i].tid];
