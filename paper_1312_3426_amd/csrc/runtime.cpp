@@ -330,24 +330,24 @@ int build_template(const double* nodes, int nv, const int32_t* tris, int nt, con
     std::vector<std::pair<int, int>> by_a;
     std::vector<int> ring;
     for (std::vector<int>& c : T.corner) {
-        const int n = (int)c.size();
-        auto vertex = [&](int k, int i) { return T.tri[3 * (c[k] >> 2) + ((c[k] & 3) + i) % 3]; };
+        const int nc = (int)c.size();
+        auto vertex = [&](int q, int i) { return T.tri[3 * (c[q] >> 2) + ((c[q] & 3) + i) % 3]; };
         by_a.clear();
-        for (int k = 0; k < n; ++k) by_a.push_back({vertex(k, 1), k});
+        for (int q = 0; q < nc; ++q) by_a.push_back({vertex(q, 1), q});
         std::sort(by_a.begin(), by_a.end());
         ring.clear();
-        std::vector<char> used(n, 0);
-        for (int k0 = 0; k0 < n; ++k0)
-            for (int k = k0; k >= 0 && !used[k];) {
-                used[k] = 1;
-                ring.push_back(c[k]);
-                const auto next = std::lower_bound(by_a.begin(), by_a.end(), std::make_pair(vertex(k, 2), 0));
-                k = next != by_a.end() && next->first == vertex(k, 2) ? next->second : -1;
+        std::vector<char> used(nc, 0);
+        for (int q0 = 0; q0 < nc; ++q0)
+            for (int q = q0; q >= 0 && !used[q];) {
+                used[q] = 1;
+                ring.push_back(c[q]);
+                const auto next = std::lower_bound(by_a.begin(), by_a.end(), std::make_pair(vertex(q, 2), 0));
+                q = next != by_a.end() && next->first == vertex(q, 2) ? next->second : -1;
             }
-        const int half = (n + 1) / 2;
-        for (int i = 0, k = 0; i < half; ++i) {
-            c[k++] = ring[i];
-            if (i + half < n) c[k++] = ring[i + half];
+        const int half = (nc + 1) / 2;
+        for (int i = 0, q = 0; i < half; ++i) {
+            c[q++] = ring[i];
+            if (i + half < nc) c[q++] = ring[i + half];
         }
     }
     return OIF_OK;
